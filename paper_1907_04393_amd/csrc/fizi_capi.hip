@@ -125,6 +125,29 @@ struct fizi_ctx {
 
 namespace {
 
+// The span of n consecutive frames whose first job is J (raw masks
+// raw_words 64-bit words apart).
+FrameSpan frame_span(const Job &J, int n, size_t frame_stride, size_t raw_words)
+{
+    FrameSpan F{};
+    F.frames = J.frame;
+    F.frame_stride = frame_stride;
+    F.raw = J.raw;
+    F.raw_words = raw_words;
+    F.bgmin = J.bgmin;
+    F.bgmax = J.bgmax;
+    F.npx = (uint32_t)J.W * (uint32_t)J.H;
+    F.n = n;
+    F.delta = J.delta;
+    F.S1 = J.S1;
+    F.S0 = J.S0;
+    F.scaled = J.scaled;
+    F.lum2 = J.lum2;
+    F.S_q16 = J.S_q16;
+    F.hue = hue_form(J.hue);
+    return F;
+}
+
 // Calls on different streams run one after the other.
 int order_after_previous(fizi_ctx *c, hipStream_t s)
 {
@@ -364,6 +387,8 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
             J.frame_index = fbase + (uint64_t)i;
         }
         set_prefixes(T, k, c->tune);
+        const FrameSpan span = frame_span(
+            T.jobs[0], k, px * 3, (pipelined && par ? c->L.raw2_stride : c->L.slot_stride) / sizeof(uint64_t));
         // the stream the chunk's back half goes to
         hipStream_t bs = s;
         if (pipelined) {
@@ -371,7 +396,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
             FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(k), hipMemcpyHostToDevice, c->up));
             FIZI_HIP(hipEventRecord(c->up_ev[par], c->up));
             FIZI_HIP(hipStreamWaitEvent(s, c->up_ev[par], 0));
-            FIZI_TRY(run_front(c->ring.d[slot], T, k, c->tune, c->n_cu, false, s, &c->clk));
+            FIZI_TRY(run_front(c->ring.d[slot], T, k, c->tune, c->n_cu, false, s, &c->clk, nullptr, &span));
             FIZI_HIP(hipEventRecord(c->cls_ev[par], s));
             FIZI_HIP(hipStreamWaitEvent(c->side, c->cls_ev[par], 0));
             bs = c->side;
@@ -394,14 +419,14 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
             if (!reuse)
                 FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(1), hipMemcpyHostToDevice, s));
             FIZI_TRY(run_pipeline(c->ring.d[slot], T, k, k, (int)(W / 64), morph_ops(c->m.p), c->tune, c->n_cu,
-                                  false, s, &c->clk, &P));
+                                  false, s, &c->clk, &P, &span));
             c->shadow[slot] = key;
             c->shadow_gen[slot] = c->gen;
         } else {
             c->shadow_gen[slot] = 0;
             FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(k), hipMemcpyHostToDevice, s));
             FIZI_TRY(run_pipeline(c->ring.d[slot], T, k, k, (int)(W / 64), morph_ops(c->m.p), c->tune, c->n_cu,
-                                  false, s, &c->clk));
+                                  false, s, &c->clk, nullptr, &span));
         }
         FIZI_TRY(c->ring.finish(slot, bs));
         if (pipelined) {

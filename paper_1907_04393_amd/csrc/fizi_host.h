@@ -36,6 +36,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 int validate(const fizi_geom *g, const fizi_params *p);
 HueTest make_hue(int a1, int a2);
+HueForm hue_form(const HueTest &h);
 // Launch shapes for frames up to max_width wide and max_ops morphology steps,
 // for a multi-stream batch or a single-stream context.
 Tuning tuning_for(int max_width, int max_ops, bool batch);
@@ -135,18 +136,20 @@ int learn_model(Model &m, TableRing &ring, const Tuning &t, int n_cu, const uint
 // Enqueues gain, classify, morphology and components for the jobs of the
 // table in device memory. With fixed_grid the launch shapes do not depend on
 // the number of jobs (for graph capture); max_jobs bounds the resolve grid.
+// span: the jobs are consecutive frames of one stream (see FrameSpan): classify
+// takes the kernel that keeps the model in registers across them.
 // patch: a one-frame launch whose slot was not uploaded again (job 0's
 // per-call fields go with the gain launch, and the component stage zeroes
 // the job's accumulators after use, for the next such launch).
 int run_pipeline(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
                  const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk,
-                 const CallPatch *patch = nullptr);
+                 const CallPatch *patch = nullptr, const FrameSpan *span = nullptr);
 // Its two halves: gain and classify (the front, which reads the frames and
 // writes the raw bits), then morphology and components (the back, which
 // reads the raw bits and writes I_FIZI and the pointers). beside: the back
 // half runs beside another step's front (smaller component workgroups).
 int run_front(const Table *d_tab, const Table &h, int njobs, const Tuning &t, int n_cu, bool fixed_grid,
-              hipStream_t s, StageClock *clk, const CallPatch *patch = nullptr);
+              hipStream_t s, StageClock *clk, const CallPatch *patch = nullptr, const FrameSpan *span = nullptr);
 int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
              const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, bool beside = false,
              bool clear_acc = false);

@@ -47,6 +47,16 @@ struct HueTest {
     int32_t pad;
 };
 
+// The same test without a case distinction: hue in [a1, a2] exactly when
+// (D1' >= 0 and D2' <= 0 and D3' > 0) differs from flip, each D' a form
+// k (R - B) + k (G - B) + c. 0 < L < 180: D1, D2, and D3' = 1. L = 180: D2' = 0.
+// L > 180, the complement of D1 < 0 and D2 > 0: D1' = -D1 - 1, D2' = 1 - D2,
+// flipped. L = 0: D1' = D2' = D1 and D3' = 3 d.p - sum(d) sum(p), which does
+// not change when a gray is added to p and so is such a form too. |k| <= 18000.
+struct HueForm {
+    int32_t k1r, k1g, c1, k2r, k2g, c2, k3r, k3g, c3, flip;
+};
+
 // Temporal tracking state of one stream (device memory): the previous
 // frame's centroid pixel, valid when that frame had a hand, and the click
 // debouncer (bit 0: the reported click; bits 8..15: consecutive frames whose
@@ -120,6 +130,22 @@ struct Table {
 
 static_assert(sizeof(TableHeader) % 8 == 0, "job array alignment");
 
+// Consecutive frames of one stream whose jobs a table holds in order (a
+// context's launch): one model, one geometry, one set of thresholds, frames
+// and raw masks at fixed strides. Passed to kernels by value.
+struct FrameSpan {
+    const uint8_t *frames;     // frame i at frames + i * frame_stride
+    size_t frame_stride;
+    uint64_t *raw;             // raw mask of frame i at raw + i * raw_words
+    size_t raw_words;
+    const uint8_t *bgmin, *bgmax;
+    uint32_t npx;
+    int32_t n;
+    int32_t delta, S1, S0, scaled, lum2;
+    uint32_t S_q16;
+    HueForm hue;
+};
+
 // Launch shapes (tunable per resolution class).
 struct Tuning {
     int cls_iters;      // classify tile = 1024 * cls_iters pixels (1, 2, 4, 8)
@@ -178,6 +204,8 @@ hipError_t launch_minmax(const Table *d_tab, int njobs, uint8_t *bgmin, uint8_t 
                          int npx, int reset, bool masked, int n_cu, hipStream_t s, StageEvents ev = {});
 hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                            hipStream_t s, StageEvents ev = {});
+hipError_t launch_classify_span(const Table *d_tab, const FrameSpan &F, int n_cu, hipStream_t s,
+                                StageEvents ev = {});
 hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max_ops, int n_cu,
                         const Tuning &t, hipStream_t s, StageEvents ev = {});
 // serial: one workgroup takes the jobs in table order (consecutive frames of

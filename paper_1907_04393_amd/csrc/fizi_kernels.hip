@@ -139,11 +139,13 @@ __device__ __forceinline__ uint32_t inv_gain(unsigned long long num, unsigned lo
 // The frame's inverse gain from its gain accumulators. `same_launch`: the
 // sums were written earlier in the same launch (persistent step), so they
 // are read with device-scope atomic loads; after a kernel boundary plain
-// (scalar) loads see them.
+// (scalar) loads see them. U: sums loaded together (fewer hold fewer
+// registers).
+template <int U = kGainSlots>
 __device__ __forceinline__ uint32_t job_gain(const Job *J, bool same_launch)
 {
     unsigned long long n = 0, d = 0;
-#pragma unroll
+#pragma unroll U
     for (int i = 0; i < kGainSlots; ++i) {
         n += same_launch ? ld_dev(&J->num[i]) : J->num[i];
         d += same_launch ? ld_dev(&J->den[i]) : J->den[i];
@@ -183,6 +185,16 @@ __device__ __forceinline__ bool hue_in_mode(int r, int g, int b, const HueTest &
         return d1 >= 0;
     const int dp = __mul24(h.dr, r) + __mul24(h.dg, g) + __mul24(h.db, b);
     return (d1 == 0) & (3 * dp - __mul24(h.dsum, r + g + b) > 0);
+}
+
+// The hue interval's four cases as one straight-line test; see HueForm.
+__device__ __forceinline__ bool hue_in_form(int r, int g, int b, const HueForm &h)
+{
+    const int rb = r - b, gb = g - b;
+    const int d1 = __mul24(h.k1r, rb) + h.c1 + __mul24(h.k1g, gb);
+    const int d2 = __mul24(h.k2r, rb) + h.c2 + __mul24(h.k2g, gb);
+    const int d3 = __mul24(h.k3r, rb) + h.c3 + __mul24(h.k3g, gb);
+    return ((d1 >= 0) & (d2 <= 0) & (d3 > 0)) != (h.flip != 0);
 }
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t w0, uint32_t w1, uint32_t w2, int i)
@@ -510,8 +522,8 @@ __device__ __forceinline__ int cls_kind(const ClsJob &c)
 // (510 - 2 lum_hi) / (510 - max - min); not gray when that chroma reaches S,
 // compared without division. Chroma > 0 is required in both cases (the hue
 // test needs it).
-template <bool LUM>
-__device__ __forceinline__ bool not_gray(const ClsJob &c, int mx, int mn)
+template <bool LUM, typename C>
+__device__ __forceinline__ bool not_gray(const C &c, int mx, int mn)
 {
     const int ch = mx - mn;
     if (LUM) {
@@ -722,6 +734,139 @@ __global__ __launch_bounds__(256) void k_classify(Table *__restrict__ T)
         s_pre[i] = T->h.cls_pre[i];
     __syncthreads();
     classify_tiles<ITERS>(T, nj, s_pre);
+}
+
+// ---------------------------------------------------------------------------
+// Classify of consecutive frames of one stream (a context's launch): a lane
+// keeps the background box of its 4 pixels in registers as exact integer
+// bounds and tests one frame after the other against it. With x = v inv +
+// 32768 (corrected pixels; v inv for scaled thresholds), a channel is in the
+// box when Lo <= x <= Hi, Lo = max(bgmin - delta, 0) 2^16 and Hi the last x
+// of the upper bound (none when bgmax + delta >= 255: the correction
+// saturates there): one multiply-add and one unsigned compare of x - Lo
+// against Hi - Lo per channel. A frame on its own (k_classify) also takes the
+// whole unpacking of the model: 29 instructions per pixel in all, against 9
+// here plus the box (170 per lane) and the pixels outside it.
+// Bound by HBM and the VALU together: 64 frames of 1920x1080 (398 MB) take 92
+// us (174 us frame by frame), moving 4.9 TB/s with the VALU two thirds busy;
+// without the pixels outside the box it would take 78 us.
+struct Box4 {
+    uint32_t a[12];            // (32768 or 0) - Lo, wrapping
+    uint32_t r[12];            // Hi - Lo
+};
+
+constexpr int kSpanFrames = 16;        // most frames of one span workgroup
+constexpr int kSpanAhead = 4;          // frames in flight per lane
+
+template <int KIND>
+__device__ __forceinline__ void box_of(const FrameSpan &F, const u32x3 l, const u32x3 u, bool valid, Box4 &b)
+{
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        const int mn = (int)byte_of(l.x, l.y, l.z, i), mx = (int)byte_of(u.x, u.y, u.z, i);
+        const uint32_t lo = (uint32_t)max(mn - F.delta, 0) << 16;
+        uint32_t hi;
+        if (KIND == kScaled)
+            hi = (uint32_t)(mx + F.delta) << 16;
+        else
+            hi = mx + F.delta >= 255 ? 0x0FFFFFFFu : ((uint32_t)(mx + F.delta + 1) << 16) - 1u;
+        b.a[i] = (KIND == kScaled ? 0u : 32768u) - lo;
+        b.r[i] = valid ? hi - lo : 0xFFFFFFFFu;      // lanes past the frame's end: never outside
+        // one register per bound: the compiler would otherwise split the
+        // constant off again and add it for every frame
+        asm("" : "+v"(b.a[i]));
+        asm("" : "+v"(b.r[i]));
+    }
+}
+
+// Bits of the lane's 4 pixels of one frame: outside the box, not gray, skin.
+template <int KIND>
+__device__ __forceinline__ uint32_t span_bits(const FrameSpan &F, const Box4 &box, const u32x3 w, uint32_t inv)
+{
+    bool out[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        out[k] = false;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            const int i = 3 * k + ch;
+            out[k] = out[k] | (__umul24(byte_of(w.x, w.y, w.z, i), inv) + box.a[i] > box.r[i]);
+        }
+    }
+    uint32_t bits = 0;
+    if (out[0] | out[1] | out[2] | out[3]) {
+        // a pixel of the four that no lane has outside is skipped; the rest
+        // is straight-line, without a branch on the hue interval's case
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!out[k])
+                continue;
+            const uint32_t r8 = byte_of(w.x, w.y, w.z, 3 * k), g8 = byte_of(w.x, w.y, w.z, 3 * k + 1),
+                           b8 = byte_of(w.x, w.y, w.z, 3 * k + 2);
+            int r = (int)r8, g = (int)g8, b = (int)b8;
+            if (KIND != kScaled) {
+                r = (int)corr(r8, inv);
+                g = (int)corr(g8, inv);
+                b = (int)corr(b8, inv);
+            }
+            const int mx = max(max(r, g), b), mn = min(min(r, g), b);
+            const bool colour = KIND == kScaled ? __umul24((uint32_t)(mx - mn), inv) >= F.S_q16
+                                                : not_gray<KIND == kCorrectedLum>(F, mx, mn);
+            bits |= (uint32_t)(colour & hue_in_form(r, g, b, F.hue)) << k;
+        }
+    }
+    return bits;
+}
+
+// Workgroup (x, y): pixel tile x (1024 pixels, 256 per wave), frames
+// [y per, (y + 1) per).
+template <int KIND>
+__global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__ T, const FrameSpan F, int per)
+{
+    __shared__ uint32_t s_inv[kSpanFrames];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int f0 = (int)blockIdx.y * per, nf = min(per, F.n - f0);
+    const uint32_t base = blockIdx.x * 1024u + (uint32_t)wave * 256u;
+    const uint32_t p = base + 4u * (uint32_t)lane;
+    // lanes past the frame's end read its last pixels and never test as outside
+    const uint32_t off = 3u * min(p, F.npx - 4u);
+    const u32x3 l = *at_byte(G(reinterpret_cast<const u32x3 *>(F.bgmin)), off);
+    const u32x3 u = *at_byte(G(reinterpret_cast<const u32x3 *>(F.bgmax)), off);
+    const GLOBAL uint8_t *frames = G(F.frames) + (size_t)f0 * F.frame_stride;
+    auto load = [&](int f) __attribute__((always_inline)) {
+        return __builtin_nontemporal_load(
+            at_byte(reinterpret_cast<const GLOBAL u32x3 *>(frames + (size_t)f * F.frame_stride), off));
+    };
+    // a ring of kSpanAhead frames in flight: a frame's registers take the
+    // frame kSpanAhead later as soon as it is tested
+    u32x3 ring[kSpanAhead];
+#pragma unroll
+    for (int q = 0; q < kSpanAhead; ++q)
+        ring[q] = load(min(q, nf - 1));
+    if ((int)threadIdx.x < nf)
+        s_inv[threadIdx.x] = job_gain<4>(&T->jobs[f0 + threadIdx.x], false);
+    __syncthreads();
+    Box4 box;
+    box_of<KIND>(F, l, u, p < F.npx, box);
+    const uint32_t word = (base >> 6) + (uint32_t)(lane >> 4);
+    const bool store = (lane & 15) == 0 && word < (F.npx >> 6);
+    GLOBAL uint64_t *raw = G(F.raw) + (size_t)f0 * F.raw_words;
+    for (int f = 0; f < nf; f += kSpanAhead) {
+#pragma unroll
+        for (int q = 0; q < kSpanAhead; ++q) {
+            if (f + q < nf) {
+                const uint32_t bits = span_bits<KIND>(F, box, ring[q], s_inv[f + q]);
+                if (f + q + kSpanAhead < nf)
+                    ring[q] = load(f + q + kSpanAhead);
+                uint64_t w = 0;
+                if (__builtin_amdgcn_ballot_w64(bits != 0u))
+                    w = row_word(bits);
+                if (store)
+                    (raw + (size_t)(f + q) * F.raw_words)[word] = w;
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2267,6 +2412,30 @@ hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const 
     case 8: FIZI_LAUNCH(k_classify<8>, grid, 256, 0, s, ev, tab); break;
     default: FIZI_LAUNCH(k_classify<4>, grid, 256, 0, s, ev, tab); break;
     }
+    return hipGetLastError();
+}
+
+// Frames of one span workgroup: 16, so that a pixel's box is unpacked once
+// for 16 frames, unless that leaves fewer workgroups than about one resident
+// round (seven 256-thread workgroups per CU): then 8, or 4. Measured for 64
+// frames of 1920x1080 with 4 / 8 / 16 / 32 / 64 frames: 124 / 98 / 92 / 98 /
+// 118 us; for 16 frames of 1280x720 (900 tiles) with 8 / 16: 17 / 21 us.
+hipError_t launch_classify_span(const Table *d_tab, const FrameSpan &F, int n_cu, hipStream_t s, StageEvents ev)
+{
+    if (F.n <= 0)
+        return hipSuccess;
+    const int tiles = (int)((F.npx + 1023u) / 1024u);
+    int per = kSpanFrames;
+    while (per > 4 && (long long)tiles * ((F.n + per - 1) / per) < 7ll * n_cu)
+        per /= 2;
+    per = std::min(per, F.n);
+    const dim3 grid((unsigned)tiles, (unsigned)((F.n + per - 1) / per));
+    if (F.scaled)
+        FIZI_LAUNCH(k_classify_span<kScaled>, grid, 256, 0, s, ev, d_tab, F, per);
+    else if (F.lum2)
+        FIZI_LAUNCH(k_classify_span<kCorrectedLum>, grid, 256, 0, s, ev, d_tab, F, per);
+    else
+        FIZI_LAUNCH(k_classify_span<kCorrected>, grid, 256, 0, s, ev, d_tab, F, per);
     return hipGetLastError();
 }
 
