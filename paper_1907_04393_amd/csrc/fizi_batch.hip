@@ -26,6 +26,7 @@ struct fizi_batch {
     hipStream_t cap = nullptr;                 // capture stream for graphs
     hipGraphExec_t graph[kTabSlots] = {};
     uint8_t *persist = nullptr;                // fused-kernel barrier state
+    uint32_t *arrived = nullptr;               // gain counts of the learning launches
     hipEvent_t order_ev = nullptr;
     hipStream_t last_stream = nullptr;
     bool have_last = false;
@@ -50,7 +51,7 @@ struct fizi_batch {
 namespace {
 
 struct BatchLayout {
-    size_t tables, persist;
+    size_t tables, persist, arrived;
     std::vector<size_t> model, slot, raw2;
     size_t total;
 };
@@ -80,6 +81,8 @@ BatchLayout batch_layout(int32_t n, const fizi_geom *geoms, const fizi_params *p
     off += TableRing::device_bytes();
     L.persist = off;
     off += align256(persist_state_bytes());
+    L.arrived = off;
+    off += align256(kArrivedWords * sizeof(uint32_t));
     L.model.resize(n);
     L.slot.resize(n);
     L.raw2.resize(n);
@@ -327,6 +330,7 @@ int fizi_batch_create(int32_t n_streams, const fizi_geom *geoms, const fizi_para
     b->max_wd = max_w / 64;
     b->tune = tuning_for(max_w, b->max_ops, true);
     b->persist = b->d + L.persist;
+    b->arrived = reinterpret_cast<uint32_t *>(b->d + L.arrived);
     int rc = device_cu_count(&b->device, &b->n_cu);
     if (rc == FIZI_OK)
         rc = b->ring.init(b->d + L.tables);
@@ -344,6 +348,8 @@ int fizi_batch_create(int32_t n_streams, const fizi_geom *geoms, const fizi_para
         if (e == hipSuccess)
             e = (hipError_t)launch_fill_u32(reinterpret_cast<uint32_t *>(b->persist), 0u,
                                              persist_state_bytes() / 4, nullptr);
+        if (e == hipSuccess)
+            e = launch_fill_u32(b->arrived, 0u, kArrivedWords, nullptr);
         // band flags hold no epoch yet (epochs start at 1)
         for (int i = 0; i < n_streams && e == hipSuccess; ++i)
             e = (hipError_t)launch_fill_u32(b->slot[i].bflag, 0u, b->slot[i].nflags, nullptr);
@@ -378,7 +384,10 @@ int fizi_batch_learn(fizi_batch *b, int32_t stream_id, const uint8_t *d_frames, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     FIZI_TRY(flush_pending(b, s));
     FIZI_TRY(order_after_previous(b, s));
-    FIZI_TRY(learn_model(m, b->ring, b->tune, b->n_cu, d_frames, n_frames, reset, s, &b->clk));
+    int slot;
+    FIZI_TRY(b->ring.take(&slot));
+    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, b->n_cu, d_frames, n_frames, reset, s, &b->clk));
+    FIZI_TRY(b->ring.finish(slot, s));
     return mark_last(b, s);
 }
 
@@ -399,7 +408,10 @@ int fizi_batch_relearn(fizi_batch *b, int32_t stream_id, const uint8_t *d_frames
     hipStream_t s = static_cast<hipStream_t>(stream);
     FIZI_TRY(flush_pending(b, s));
     FIZI_TRY(order_after_previous(b, s));
-    FIZI_TRY(learn_model(m, b->ring, b->tune, b->n_cu, d_frames, n_frames, 0, s, &b->clk, d_fizi_bits));
+    int slot;
+    FIZI_TRY(b->ring.take(&slot));
+    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, b->n_cu, d_frames, n_frames, 0, s, &b->clk, d_fizi_bits));
+    FIZI_TRY(b->ring.finish(slot, s));
     return mark_last(b, s);
 }
 

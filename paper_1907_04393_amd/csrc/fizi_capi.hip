@@ -10,15 +10,15 @@ using namespace fizi;
 
 namespace {
 
-constexpr int kRing = 65536;   // pointers kept for get_pointer
+constexpr int kRing = 65536;   // pointers kept for get_pointer (a power of two)
 constexpr int kRecs = 64;
 
-// State block: model | job tables | chunk pointers | chunk scratch slots |
-// a second raw-mask buffer per slot (consecutive chunks of a call alternate
+// State block: model | job tables | base job | gain counts | chunk
+// pointers | chunk scratch slots | a second raw-mask buffer per slot (consecutive chunks of a call alternate
 // between the two, so that a chunk's classify never writes the bits the
 // previous chunk's morphology is reading).
 struct CtxLayout {
-    size_t model, tables, ptrs, slots, slot_stride, raw2, raw2_stride, total;
+    size_t model, tables, base, arrived, ptrs, slots, slot_stride, raw2, raw2_stride, total;
 };
 
 CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
@@ -29,6 +29,10 @@ CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
     off += align256(model_bytes(g, p));
     L.tables = off;
     off += TableRing::device_bytes();
+    L.base = off;
+    off += align256(sizeof(Job));
+    L.arrived = off;
+    off += align256(kArrivedWords * sizeof(uint32_t));
     L.ptrs = off;
     off += align256((size_t)chunk * sizeof(fizi_pointer));
     L.slot_stride = align256(slot_bytes(g));
@@ -43,37 +47,6 @@ CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
 
 }  // namespace
 
-// Everything the kernels read of a one-job table: the header's entries for
-// one job and the job, its per-call fields cleared (the gain launch brings
-// them). Zero-filled first, so that padding compares equal.
-struct OneJobKey {
-    int32_t njobs, flow_nseg;
-    int32_t gain_pre[2], cls_pre[2], mor_pre[2], flow_pre[3], flow_seg[2];
-    Job job;
-};
-
-static OneJobKey one_job_key(const Table &T)
-{
-    OneJobKey k;
-    std::memset(&k, 0, sizeof(k));
-    k.njobs = T.h.njobs;
-    k.flow_nseg = T.h.flow_nseg;
-    for (int i = 0; i < 2; ++i) {
-        k.gain_pre[i] = T.h.gain_pre[i];
-        k.cls_pre[i] = T.h.cls_pre[i];
-        k.mor_pre[i] = T.h.mor_pre[i];
-        k.flow_seg[i] = T.h.flow_seg[i];
-    }
-    for (int i = 0; i < 3; ++i)
-        k.flow_pre[i] = T.h.flow_pre[i];
-    std::memcpy(&k.job, &T.jobs[0], sizeof(Job));
-    k.job.frame = nullptr;
-    k.job.fizi = k.job.hand = nullptr;
-    k.job.out = k.job.hout = nullptr;
-    k.job.frame_index = 0;
-    return k;
-}
-
 struct fizi_ctx {
     Model m;
     int chunk = 0;
@@ -82,14 +55,10 @@ struct fizi_ctx {
     CtxLayout L{};
     int device = 0;
     int n_cu = 0;
-    TableRing ring;
-    // what the kernels read of each table slot on the device, as its last
-    // one-frame call left it (job 0's per-call fields cleared), valid while
-    // shadow_gen[slot] == gen; any other use of the ring (learning, calls of
-    // several frames) makes it stale
-    OneJobKey shadow[kTabSlots];
-    uint64_t shadow_gen[kTabSlots] = {};
-    uint64_t gen = 1;
+    // job tables in device memory, written by the gain kernel of each launch
+    // and taken in turn: a launch's table is read until its back half is
+    // done, which the caller's stream joins before the second launch after it
+    int next_tab = 0;
     StageClock clk;
     // the last kRing pointers, indexed by frame: pinned, coherent host memory
     // that the component kernels store each final pointer into (d_ring is
@@ -105,60 +74,43 @@ struct fizi_ctx {
         bool valid;
     } recs[kRecs] = {};
     int next_rec = 0;
-    hipEvent_t order_ev = nullptr;
+    // order_ev, or the record event of a call whose last launch ran on its
+    // own stream, marks the end of the last call on its stream
+    hipEvent_t order_ev = nullptr, last_ev = nullptr;
     hipStream_t last_stream = nullptr;
     bool have_last = false;
     uint64_t next_frame = 0;
     // calls of several chunks: the back half of a chunk (morphology,
-    // components, pointer copies) on a side stream beside the next chunk's
-    // front, the job tables going up on their own stream
-    hipStream_t side = nullptr, up = nullptr;
-    hipEvent_t up_ev[2] = {}, cls_ev[2] = {}, join_ev[2] = {};
+    // components) on a side stream beside the next chunk's front
+    hipStream_t side = nullptr;
+    hipEvent_t cls_ev[2] = {};
     // pipelined calls (fizi_set_pipelined): a call leaves its last chunk's
     // back half on the side stream; the next call joins it after its first
     // classify (or fizi_flush does), and chunks keep alternating raw buffers
     // across calls
     bool pipe_calls = false;
     int parity = 0;      // raw buffer of the next chunk
-    int pend_join = -1;  // parity of the back half not yet joined, or -1
+    hipEvent_t pend_join = nullptr;  // end of the back half not yet joined, or null
 };
 
 namespace {
-
-// The span of n consecutive frames whose first job is J (raw masks
-// raw_words 64-bit words apart).
-FrameSpan frame_span(const Job &J, int n, size_t frame_stride, size_t raw_words)
-{
-    FrameSpan F{};
-    F.frames = J.frame;
-    F.frame_stride = frame_stride;
-    F.raw = J.raw;
-    F.raw_words = raw_words;
-    F.bgmin = J.bgmin;
-    F.bgmax = J.bgmax;
-    F.npx = (uint32_t)J.W * (uint32_t)J.H;
-    F.n = n;
-    F.delta = J.delta;
-    F.S1 = J.S1;
-    F.S0 = J.S0;
-    F.scaled = J.scaled;
-    F.lum2 = J.lum2;
-    F.S_q16 = J.S_q16;
-    F.hue = hue_form(J.hue);
-    return F;
-}
 
 // Calls on different streams run one after the other.
 int order_after_previous(fizi_ctx *c, hipStream_t s)
 {
     if (c->have_last && c->last_stream != s)
-        FIZI_HIP(hipStreamWaitEvent(s, c->order_ev, 0));
+        FIZI_HIP(hipStreamWaitEvent(s, c->last_ev, 0));
     return FIZI_OK;
 }
 
-int mark_last(fizi_ctx *c, hipStream_t s)
+// Marks the end of a call on s; done: an event already recorded there, or null.
+int mark_last(fizi_ctx *c, hipStream_t s, hipEvent_t done = nullptr)
 {
-    FIZI_HIP(hipEventRecord(c->order_ev, s));
+    if (!done) {
+        FIZI_HIP(hipEventRecord(c->order_ev, s));
+        done = c->order_ev;
+    }
+    c->last_ev = done;
     c->last_stream = s;
     c->have_last = true;
     return FIZI_OK;
@@ -167,9 +119,9 @@ int mark_last(fizi_ctx *c, hipStream_t s)
 // Orders s after the back half a pipelined call left pending.
 int join_pending(fizi_ctx *c, hipStream_t s)
 {
-    if (c->pend_join >= 0) {
-        FIZI_HIP(hipStreamWaitEvent(s, c->join_ev[c->pend_join], 0));
-        c->pend_join = -1;
+    if (c->pend_join) {
+        FIZI_HIP(hipStreamWaitEvent(s, c->pend_join, 0));
+        c->pend_join = nullptr;
     }
     return FIZI_OK;
 }
@@ -178,13 +130,21 @@ int join_pending(fizi_ctx *c, hipStream_t s)
 // all of the context's work.
 int drain(fizi_ctx *c)
 {
-    if (c->pend_join >= 0) {
+    if (c->pend_join) {
         FIZI_TRY(join_pending(c, c->last_stream));
         FIZI_TRY(mark_last(c, c->last_stream));
     }
     if (c->have_last)
-        FIZI_HIP(hipEventSynchronize(c->order_ev));
+        FIZI_HIP(hipEventSynchronize(c->last_ev));
     return FIZI_OK;
+}
+
+// The next table of the ring.
+Table *take_table(fizi_ctx *c)
+{
+    Table *t = reinterpret_cast<Table *>(c->d + c->L.tables + (size_t)c->next_tab * align256(sizeof(Table)));
+    c->next_tab = (c->next_tab + 1) % kTabSlots;
+    return t;
 }
 
 }  // namespace
@@ -252,7 +212,6 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
     const CtxLayout L = ctx_layout(*geom, *params, chunk_frames);
     if (state_bytes < L.total)
         return fail(FIZI_ENOMEM, "state block smaller than fizi_state_bytes()");
-    (void)stream;
     fizi_ctx *c = new (std::nothrow) fizi_ctx();
     if (!c)
         return fail(FIZI_ENOMEM, "host allocation failed");
@@ -262,8 +221,6 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
     model_at(c->m, *geom, *params, c->d + L.model);
     c->tune = tuning_for(geom->width, morph_ops(*params), false);
     int rc = device_cu_count(&c->device, &c->n_cu);
-    if (rc == FIZI_OK)
-        rc = c->ring.init(c->d + L.tables);
     if (rc == FIZI_OK) {
         hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_ring), sizeof(fizi_pointer) * kRing,
                                      hipHostMallocMapped | hipHostMallocCoherent);
@@ -273,20 +230,25 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
             e = hipEventCreateWithFlags(&c->order_ev, kDeviceOrderEvent);
         for (int i = 0; i < kRecs && e == hipSuccess; ++i)
             e = hipEventCreateWithFlags(&c->recs[i].ev, hipEventDisableTiming);
-        for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-            e = hipEventCreateWithFlags(&c->up_ev[k], hipEventDisableTiming);
-            if (e == hipSuccess)
-                e = hipEventCreateWithFlags(&c->cls_ev[k], kDeviceOrderEvent);
-            if (e == hipSuccess)
-                e = hipEventCreateWithFlags(&c->join_ev[k], kDeviceOrderEvent);
-        }
+        for (int k = 0; k < 2 && e == hipSuccess; ++k)
+            e = hipEventCreateWithFlags(&c->cls_ev[k], kDeviceOrderEvent);
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
-        if (e == hipSuccess)
-            e = hipStreamCreateWithFlags(&c->up, hipStreamNonBlocking);
+        if (e == hipSuccess) {
+            // what every job of this context has in common
+            Job J;
+            fill_job(c->m, c->tune.morph_rows, J);
+            set_scratch(J, slot_at(*geom, c->d + L.slots));
+            e = launch_put_job(reinterpret_cast<Job *>(c->d + L.base), J, static_cast<hipStream_t>(stream));
+            if (e == hipSuccess)
+                e = launch_fill_u32(reinterpret_cast<uint32_t *>(c->d + L.arrived), 0u, kArrivedWords,
+                                    static_cast<hipStream_t>(stream));
+        }
         if (e != hipSuccess)
             rc = fail(FIZI_EHIP, std::string("fizi_create: ") + hipGetErrorString(e));
     }
+    if (rc == FIZI_OK)
+        rc = mark_last(c, static_cast<hipStream_t>(stream));
     if (rc != FIZI_OK) {
         const std::string msg = fizi_last_error();
         fizi_destroy(c);
@@ -309,8 +271,7 @@ int learn_background(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     FIZI_TRY(order_after_previous(c, s));
     FIZI_TRY(join_pending(c, s));
-    ++c->gen;
-    FIZI_TRY(learn_model(c->m, c->ring, c->tune, c->n_cu, d_frames, n_frames, reset, s, &c->clk));
+    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, c->n_cu, d_frames, n_frames, reset, s, &c->clk));
     return mark_last(c, s);
 }
 
@@ -329,8 +290,7 @@ int relearn_background(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, c
     FIZI_TRY(order_after_previous(c, s));
     // the masks may come from a call whose back half is still pending
     FIZI_TRY(join_pending(c, s));
-    ++c->gen;
-    FIZI_TRY(learn_model(c->m, c->ring, c->tune, c->n_cu, d_frames, n_frames, 0, s, &c->clk, d_fizi_bits));
+    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, c->n_cu, d_frames, n_frames, 0, s, &c->clk, d_fizi_bits));
     return mark_last(c, s);
 }
 
@@ -354,12 +314,9 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
     // pipelined calls, after the next call's first classify)
     const bool pipelined = c->pipe_calls || n_frames > c->chunk;
     int par = c->pipe_calls ? c->parity : 0;
-    int prev_join = c->pipe_calls ? c->pend_join : -1;
+    hipEvent_t prev_join = c->pipe_calls ? c->pend_join : nullptr, last = nullptr;
     for (int f0 = 0; f0 < n_frames; f0 += c->chunk) {
         const int k = std::min(c->chunk, n_frames - f0);
-        int slot;
-        FIZI_TRY(c->ring.take(&slot));
-        Table &T = *c->ring.h[slot];
         const uint64_t fbase = c->next_frame + (uint64_t)f0;
         // a launch whose morphology, in short bands of one wave each, needs
         // at most one wave per SIMD is bound by the length of one wave's
@@ -368,76 +325,39 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         // keep the tuned shape, which repeats fewer halo rows.
         const bool short_chain =
             c->tune.short_bands && (size_t)k * ((H + kShortBand - 1) / kShortBand) <= (size_t)c->n_cu * 4;
-        for (int i = 0; i < k; ++i) {
-            Job &J = T.jobs[i];
-            if (short_chain)
-                fill_job(c->m, kShortBand, J, false);
-            else
-                fill_job(c->m, c->tune.morph_rows, J);
-            set_scratch(J, slot_at(c->m.g, c->d + c->L.slots + (size_t)i * c->L.slot_stride));
-            if (pipelined && par)
-                J.raw = reinterpret_cast<uint64_t *>(c->d + c->L.raw2 + (size_t)i * c->L.raw2_stride);
-            const size_t f = (size_t)(f0 + i);
-            J.frame = d_frames + f * px * 3;
-            if (d_fizi_bits)
-                J.fizi = d_fizi_bits + f * words;
-            J.hand = d_hand_bits ? d_hand_bits + f * words : nullptr;
-            J.out = d_pointers ? d_pointers + f : internal + i;
-            J.hout = c->d_ring + (size_t)((fbase + (uint64_t)i) % kRing);
-            J.frame_index = fbase + (uint64_t)i;
-        }
-        set_prefixes(T, k, c->tune);
-        const FrameSpan span = frame_span(
-            T.jobs[0], k, px * 3, (pipelined && par ? c->L.raw2_stride : c->L.slot_stride) / sizeof(uint64_t));
+        // the launch's first job, and the strides to the next ones
+        Job J;
+        if (short_chain)
+            fill_job(c->m, kShortBand, J, false);
+        else
+            fill_job(c->m, c->tune.morph_rows, J);
+        set_scratch(J, slot_at(c->m.g, c->d + c->L.slots));
+        if (pipelined && par)
+            J.raw = reinterpret_cast<uint64_t *>(c->d + c->L.raw2);
+        J.frame = d_frames + (size_t)f0 * px * 3;
+        if (d_fizi_bits)
+            J.fizi = d_fizi_bits + (size_t)f0 * words;
+        J.hand = d_hand_bits ? d_hand_bits + (size_t)f0 * words : nullptr;
+        J.out = d_pointers ? d_pointers + f0 : internal;
+        J.hout = c->d_ring;
+        J.frame_index = fbase;
+        SpanJobs S = span_jobs(J, k, reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune);
+        S.base = reinterpret_cast<const Job *>(c->d + c->L.base);
+        if (!d_fizi_bits)
+            S.fizi_words = c->L.slot_stride / sizeof(uint64_t);
+        S.slot_bytes = c->L.slot_stride;
+        S.raw_bytes = pipelined && par ? c->L.raw2_stride : c->L.slot_stride;
+        S.ring_mask = kRing - 1;
+        Table *tab = take_table(c);
+        FIZI_TRY(span_front(tab, S, J, c->tune, c->n_cu, s, &c->clk));
         // the stream the chunk's back half goes to
         hipStream_t bs = s;
         if (pipelined) {
-            c->shadow_gen[slot] = 0;
-            FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(k), hipMemcpyHostToDevice, c->up));
-            FIZI_HIP(hipEventRecord(c->up_ev[par], c->up));
-            FIZI_HIP(hipStreamWaitEvent(s, c->up_ev[par], 0));
-            FIZI_TRY(run_front(c->ring.d[slot], T, k, c->tune, c->n_cu, false, s, &c->clk, nullptr, &span));
             FIZI_HIP(hipEventRecord(c->cls_ev[par], s));
             FIZI_HIP(hipStreamWaitEvent(c->side, c->cls_ev[par], 0));
             bs = c->side;
-            FIZI_TRY(run_back(c->ring.d[slot], T, k, k, (int)(W / 64), morph_ops(c->m.p), c->tune, c->n_cu,
-                              false, bs, &c->clk, true));
-        } else if (k == 1) {
-            // a one-frame call: when the slot on the device already holds
-            // this table apart from job 0's per-call fields (the previous
-            // one-frame call in this slot left it so, its accumulators
-            // zeroed), those fields go with the gain launch instead of an
-            // upload
-            const Job &J = T.jobs[0];
-            const CallPatch P{J.frame, J.fizi, J.hand, J.out, J.hout, J.frame_index, 1};
-            const OneJobKey key = one_job_key(T);
-            const bool reuse =
-                c->shadow_gen[slot] == c->gen && std::memcmp(&c->shadow[slot], &key, sizeof(key)) == 0;
-            // stale until every kernel of this call is enqueued (a launch
-            // that fails leaves the slot to a full upload next time)
-            c->shadow_gen[slot] = 0;
-            if (!reuse)
-                FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(1), hipMemcpyHostToDevice, s));
-            FIZI_TRY(run_pipeline(c->ring.d[slot], T, k, k, (int)(W / 64), morph_ops(c->m.p), c->tune, c->n_cu,
-                                  false, s, &c->clk, &P, &span));
-            c->shadow[slot] = key;
-            c->shadow_gen[slot] = c->gen;
-        } else {
-            c->shadow_gen[slot] = 0;
-            FIZI_HIP(hipMemcpyAsync(c->ring.d[slot], &T, table_bytes(k), hipMemcpyHostToDevice, s));
-            FIZI_TRY(run_pipeline(c->ring.d[slot], T, k, k, (int)(W / 64), morph_ops(c->m.p), c->tune, c->n_cu,
-                                  false, s, &c->clk, nullptr, &span));
         }
-        FIZI_TRY(c->ring.finish(slot, bs));
-        if (pipelined) {
-            FIZI_HIP(hipEventRecord(c->join_ev[par], c->side));
-            // the chunk before this one is joined after this classify: the
-            // next classify reuses its raw buffers
-            if (prev_join >= 0)
-                FIZI_HIP(hipStreamWaitEvent(s, c->join_ev[prev_join], 0));
-            prev_join = par;
-            par ^= 1;
-        }
+        FIZI_TRY(span_back(tab, S, morph_ops(c->m.p), c->tune, c->n_cu, bs, &c->clk, pipelined));
         // the ring holds a chunk's pointers once its back half is done
         fizi_ctx::Rec &r = c->recs[c->next_rec];
         c->next_rec = (c->next_rec + 1) % kRecs;
@@ -445,16 +365,25 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         r.f1 = fbase + k;
         FIZI_HIP(hipEventRecord(r.ev, bs));
         r.valid = true;
-    }
-    if (pipelined) {
-        if (c->pipe_calls) {
-            c->pend_join = prev_join;
-            c->parity = par;
-        } else {
-            FIZI_HIP(hipStreamWaitEvent(s, c->join_ev[prev_join], 0));
+        last = r.ev;
+        if (pipelined) {
+            // the chunk before this one is joined after this classify: the
+            // next classify reuses its raw buffers
+            if (prev_join)
+                FIZI_HIP(hipStreamWaitEvent(s, prev_join, 0));
+            prev_join = r.ev;
+            par ^= 1;
         }
     }
     c->next_frame += (uint64_t)n_frames;
+    if (!pipelined)
+        return mark_last(c, s, last);
+    if (c->pipe_calls) {
+        c->pend_join = prev_join;
+        c->parity = par;
+    } else {
+        FIZI_HIP(hipStreamWaitEvent(s, prev_join, 0));
+    }
     return mark_last(c, s);
 }
 
@@ -539,24 +468,21 @@ int fizi_destroy(fizi_ctx *c)
     if (!c)
         return FIZI_OK;
     if (c->have_last)
-        (void)hipEventSynchronize(c->order_ev);
+        (void)hipEventSynchronize(c->last_ev);
     // a pending back half, without touching the stream of the last call
-    if (c->pend_join >= 0)
-        (void)hipEventSynchronize(c->join_ev[c->pend_join]);
-    c->ring.destroy();
+    if (c->pend_join)
+        (void)hipEventSynchronize(c->pend_join);
     c->clk.destroy();
     if (c->h_ring)
         (void)hipHostFree(c->h_ring);
-    for (hipEvent_t e : {c->order_ev, c->up_ev[0], c->up_ev[1], c->cls_ev[0], c->cls_ev[1], c->join_ev[0],
-                         c->join_ev[1]})
+    for (hipEvent_t e : {c->order_ev, c->cls_ev[0], c->cls_ev[1]})
         if (e)
             (void)hipEventDestroy(e);
     for (const fizi_ctx::Rec &r : c->recs)
         if (r.ev)
             (void)hipEventDestroy(r.ev);
-    for (hipStream_t st : {c->side, c->up})
-        if (st)
-            (void)hipStreamDestroy(st);
+    if (c->side)
+        (void)hipStreamDestroy(c->side);
     delete c;
     return FIZI_OK;
 }

@@ -36,11 +36,13 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 int validate(const fizi_geom *g, const fizi_params *p);
 HueTest make_hue(int a1, int a2);
-HueForm hue_form(const HueTest &h);
 // Launch shapes for frames up to max_width wide and max_ops morphology steps,
 // for a multi-stream batch or a single-stream context.
 Tuning tuning_for(int max_width, int max_ops, bool batch);
 int morph_ops(const fizi_params &p);
+
+// Arrival counts of the gain kernel, for as many frames as a launch may have.
+constexpr size_t kArrivedWords = (size_t)kMaxJobs * kArrivedStride;
 
 // Background model of one stream (Section 3.1 (i)) and its reference
 // luminance rows (Section 3.2), inside a device block.
@@ -89,7 +91,8 @@ void set_scratch(Job &J, const Slot &s);
 void set_prefixes(Table &T, int njobs, const Tuning &t);
 inline size_t table_bytes(int njobs) { return sizeof(TableHeader) + (size_t)njobs * sizeof(Job); }
 
-// Job tables: pinned staging copies, device copies, one event per slot.
+// Job tables of a batch: pinned staging copies, device copies, one event per
+// slot.
 struct TableRing {
     Table *h[kTabSlots] = {};
     Table *d[kTabSlots] = {};
@@ -127,31 +130,33 @@ struct StageClock {
 int device_cu_count(int *device, int *n_cu);
 
 // Background learning of one stream from n frames (reset: reference from
-// frames[0], model starts empty).
-// Learning (and, with masks, partial re-learning: n I_FIZI bit masks whose
-// set bits keep a frame's pixels out of the model).
-int learn_model(Model &m, TableRing &ring, const Tuning &t, int n_cu, const uint8_t *frames, int n,
-                int reset, hipStream_t s, StageClock *clk, const uint64_t *masks = nullptr);
+// frames[0], model starts empty) and, with masks, partial re-learning (n
+// I_FIZI bit masks whose set bits keep a frame's pixels out of the model).
+// d_tab: a table in device memory that no enqueued work on another stream
+// than s still reads; arrived: kArrivedWords words, 0 between launches.
+int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, int n_cu, const uint8_t *frames, int n, int reset,
+                hipStream_t s, StageClock *clk, const uint64_t *masks = nullptr);
 
 // Enqueues gain, classify, morphology and components for the jobs of the
 // table in device memory. With fixed_grid the launch shapes do not depend on
 // the number of jobs (for graph capture); max_jobs bounds the resolve grid.
-// span: the jobs are consecutive frames of one stream (see FrameSpan): classify
-// takes the kernel that keeps the model in registers across them.
-// patch: a one-frame launch whose slot was not uploaded again (job 0's
-// per-call fields go with the gain launch, and the component stage zeroes
-// the job's accumulators after use, for the next such launch).
 int run_pipeline(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
-                 const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk,
-                 const CallPatch *patch = nullptr, const FrameSpan *span = nullptr);
+                 const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk);
 // Its two halves: gain and classify (the front, which reads the frames and
 // writes the raw bits), then morphology and components (the back, which
 // reads the raw bits and writes I_FIZI and the pointers). beside: the back
 // half runs beside another step's front (smaller component workgroups).
 int run_front(const Table *d_tab, const Table &h, int njobs, const Tuning &t, int n_cu, bool fixed_grid,
-              hipStream_t s, StageClock *clk, const CallPatch *patch = nullptr, const FrameSpan *span = nullptr);
+              hipStream_t s, StageClock *clk);
 int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
-             const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, bool beside = false,
-             bool clear_acc = false);
+             const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, bool beside = false);
+
+// The same halves for consecutive frames of one stream (a context's launch):
+// the gain kernel builds the table. first: the first frame's job on the host.
+SpanJobs span_jobs(const Job &first, int n, uint32_t *arrived, const Tuning &t);
+int span_front(Table *d_tab, const SpanJobs &S, const Job &first, const Tuning &t, int n_cu, hipStream_t s,
+               StageClock *clk);
+int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &t, int n_cu, hipStream_t s,
+              StageClock *clk, bool beside);
 
 }  // namespace fizi

@@ -402,73 +402,111 @@ int device_cu_count(int *device, int *n_cu)
     return FIZI_OK;
 }
 
-int learn_model(Model &m, TableRing &ring, const Tuning &t, int n_cu, const uint8_t *frames, int n,
-                int reset, hipStream_t s, StageClock *clk, const uint64_t *masks)
+SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived, const Tuning &t)
+{
+    SpanJobs S{};
+    const size_t px = (size_t)J.W * J.H;
+    const int ctile = cls_tile_px(t), bands = (J.H + J.band - 1) / J.band, per = 64 / J.mgroup;
+    S.frame = J.frame;
+    S.frame_bytes = px * 3;
+    S.raw = J.raw;
+    S.fizi = J.fizi;
+    S.hand = J.hand;
+    S.fizi_words = S.hand_words = px / 64;
+    S.out = J.out;
+    S.ring = J.hout;
+    S.track = J.track;
+    S.frame_index = J.frame_index;
+    S.yref = const_cast<uint16_t *>(J.yref);
+    S.n = n;
+    S.W = J.W;
+    S.H = J.H;
+    S.rs = J.rs;
+    S.band = J.band;
+    S.mgroup = J.mgroup;
+    S.cls_tiles = (int)((px + ctile - 1) / ctile);
+    S.mor_items = (bands + per - 1) / per;
+    S.glo = J.glo;
+    S.ghi = J.ghi;
+    S.hue = J.hue;
+    S.arrived = arrived;
+    return S;
+}
+
+int span_front(Table *d_tab, const SpanJobs &S, const Job &first, const Tuning &t, int n_cu, hipStream_t s,
+               StageClock *clk)
+{
+    auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
+    FIZI_HIP(launch_gain_span(d_tab, S, s, ev(FIZI_STAGE_GAIN)));
+    // a single frame keeps k_classify (1920x1080: 8.7 us against 9.8: nothing
+    // to share the box between)
+    if (S.n == 1)
+        FIZI_HIP(launch_classify(d_tab, S.cls_tiles, n_cu, t, s, ev(FIZI_STAGE_CLASSIFY)));
+    else
+        FIZI_HIP(launch_classify_span(d_tab, S, first, n_cu, s, ev(FIZI_STAGE_CLASSIFY)));
+    return FIZI_OK;
+}
+
+int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &t, int n_cu, hipStream_t s,
+              StageClock *clk, bool beside)
+{
+    auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
+    FIZI_HIP(launch_morph(d_tab, S.n * S.mor_items, S.W / 64, max_ops, n_cu, t, s, ev(FIZI_STAGE_MORPH)));
+    // tracked consecutive frames are resolved in order
+    FIZI_HIP(launch_resolve(d_tab, S.n, s, ev(FIZI_STAGE_RESOLVE), S.n > 1 && S.track != nullptr, beside));
+    return FIZI_OK;
+}
+
+int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, int n_cu, const uint8_t *frames, int n, int reset,
+                hipStream_t s, StageClock *clk, const uint64_t *masks)
 {
     const size_t px = (size_t)m.g.width * m.g.height;
-    if (reset)
-        FIZI_HIP(launch_make_yref(frames, m.yref, m.g.width, m.g.height, m.p.gain_row_stride, s));
     for (int f0 = 0; f0 < n; f0 += kMaxJobs) {
         const int k = std::min(kMaxJobs, n - f0);
-        int slot;
-        FIZI_TRY(ring.take(&slot));
-        Table &T = *ring.h[slot];
-        for (int i = 0; i < k; ++i) {
-            fill_job(m, t.morph_rows, T.jobs[i]);
-            T.jobs[i].frame = frames + (size_t)(f0 + i) * px * 3;
-            if (masks)
-                T.jobs[i].fizi = const_cast<uint64_t *>(masks) + (size_t)(f0 + i) * (px / 64);
-        }
-        set_prefixes(T, k, t);
-        FIZI_HIP(hipMemcpyAsync(ring.d[slot], &T, table_bytes(k), hipMemcpyHostToDevice, s));
-        FIZI_HIP(launch_gain(ring.d[slot], T.h.gain_pre[k], n_cu, t, s));
-        FIZI_HIP(launch_minmax(ring.d[slot], k, m.bgmin, m.bgmax, (int)px, (reset && f0 == 0) ? 1 : 0,
-                               masks != nullptr, n_cu, s, clk ? clk->next(FIZI_STAGE_LEARN) : StageEvents{}));
-        FIZI_TRY(ring.finish(slot, s));
+        Job J;
+        fill_job(m, t.morph_rows, J);
+        J.frame = frames + (size_t)f0 * px * 3;
+        if (masks)
+            J.fizi = const_cast<uint64_t *>(masks) + (size_t)f0 * (px / 64);
+        SpanJobs S = span_jobs(J, k, arrived, t);
+        if (!masks)
+            S.fizi_words = 0;
+        S.make_yref = reset && f0 == 0;
+        FIZI_HIP(launch_gain_span(d_tab, S, s));
+        FIZI_HIP(launch_minmax(d_tab, k, m.bgmin, m.bgmax, (int)px, (reset && f0 == 0) ? 1 : 0, masks != nullptr,
+                               n_cu, s, clk ? clk->next(FIZI_STAGE_LEARN) : StageEvents{}));
     }
     m.learned = true;
     return FIZI_OK;
 }
 
 int run_front(const Table *d_tab, const Table &h, int njobs, const Tuning &t, int n_cu, bool fixed_grid,
-              hipStream_t s, StageClock *clk, const CallPatch *patch, const FrameSpan *span)
+              hipStream_t s, StageClock *clk)
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
     const int big = INT_MAX / 2;
-    FIZI_HIP(launch_gain(d_tab, fixed_grid ? big : h.h.gain_pre[njobs], n_cu, t, s, ev(FIZI_STAGE_GAIN), patch));
-    // a single frame keeps k_classify (1920x1080: 8.7 us against 9.8: nothing
-    // to share the box between)
-    if (span && span->n > 1) {
-        FIZI_HIP(launch_classify_span(d_tab, *span, n_cu, s, ev(FIZI_STAGE_CLASSIFY)));
-        return FIZI_OK;
-    }
+    FIZI_HIP(launch_gain(d_tab, fixed_grid ? big : h.h.gain_pre[njobs], n_cu, t, s, ev(FIZI_STAGE_GAIN)));
     FIZI_HIP(launch_classify(d_tab, fixed_grid ? big : h.h.cls_pre[njobs], n_cu, t, s,
                              ev(FIZI_STAGE_CLASSIFY)));
     return FIZI_OK;
 }
 
 int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
-             const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, bool beside,
-             bool clear_acc)
+             const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, bool beside)
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
     const int big = INT_MAX / 2;
     FIZI_HIP(launch_morph(d_tab, fixed_grid ? big : h.h.mor_pre[njobs], max_wd, max_ops, n_cu, t, s,
                           ev(FIZI_STAGE_MORPH)));
-    // tracked consecutive frames of one stream are resolved in order
-    const bool serial = njobs > 1 && h.jobs[0].track != nullptr && h.jobs[1].track == h.jobs[0].track;
-    FIZI_HIP(launch_resolve(d_tab, fixed_grid ? max_jobs : njobs, s, ev(FIZI_STAGE_RESOLVE), serial, beside,
-                            clear_acc));
+    FIZI_HIP(launch_resolve(d_tab, fixed_grid ? max_jobs : njobs, s, ev(FIZI_STAGE_RESOLVE), false, beside));
     return FIZI_OK;
 }
 
 int run_pipeline(const Table *d_tab, const Table &h, int njobs, int max_jobs, int max_wd, int max_ops,
-                 const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk, const CallPatch *patch,
-                 const FrameSpan *span)
+                 const Tuning &t, int n_cu, bool fixed_grid, hipStream_t s, StageClock *clk)
 {
-    FIZI_TRY(run_front(d_tab, h, njobs, t, n_cu, fixed_grid, s, clk, patch, span));
-    return run_back(d_tab, h, njobs, max_jobs, max_wd, max_ops, t, n_cu, fixed_grid, s, clk, false,
-                    patch != nullptr);
+    FIZI_TRY(run_front(d_tab, h, njobs, t, n_cu, fixed_grid, s, clk));
+    return run_back(d_tab, h, njobs, max_jobs, max_wd, max_ops, t, n_cu, fixed_grid, s, clk);
 }
 
 }  // namespace fizi

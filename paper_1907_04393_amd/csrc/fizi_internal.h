@@ -5,7 +5,8 @@
 // pointers to its inputs, outputs and scratch, its geometry and thresholds,
 // and a few accumulators the kernels update atomically. The host fills the
 // table in pinned memory and copies it to the device ahead of the kernels,
-// which also zeroes the accumulators for that call. Every kernel walks a flat
+// which also zeroes the accumulators for that call (batch steps), or the gain
+// kernel writes it on the device (consecutive frames of one stream). Every kernel walks a flat
 // list of tiles (grid-stride) and finds a tile's job by binary search in a
 // prefix array, so one launch covers frames of any mix of resolutions and a
 // launch's shape does not depend on the work it is given. The persistent
@@ -24,7 +25,7 @@ namespace fizi {
 constexpr int kMaxJobs = 256;          // jobs per table
 constexpr uint16_t kYrefClipped = 0xFFFFu;
 constexpr int kMaxMorphIters = 3;      // open_iters, close_iters <= 3
-constexpr int kGainSlots = 16;         // gain sums are spread over 16 accumulators
+constexpr int kGainSlots = 32;         // gain sums are spread over 32 accumulators
 constexpr int kGainRows = 4;           // sampled rows per gain tile
 
 // Skin-hue test on one RGB triple, without division (Section 3.1 (iii)).
@@ -97,12 +98,16 @@ struct Job {
     int32_t lum2;              // over-exposure filter: 2 lum_hi, 0 when off
     HueTest hue;
     // accumulators (zero when the table is uploaded)
-    // gain sums over usable sampled pixels, sampled row r adding to slot
-    // r % kGainSlots (fewer same-address atomics)
-    unsigned long long num[kGainSlots], den[kGainSlots];
+    // gain sums over usable sampled pixels, spread over kGainSlots slots:
+    // tiles of an uploaded table add to slot tile % kGainSlots (fewer
+    // same-address atomics), workgroup p of a span's frame stores slot p
+    // (32 bits hold a slot's share of the largest frame: 2^26 pixels of at
+    // most 1020, 2.1e9)
+    alignas(8) uint32_t num[kGainSlots];
+    uint32_t den[kGainSlots];
     uint32_t nruns, flags, nlinks, nflag;
     uint32_t gain_done, morph_done;   // persistent step: finished gain tiles, morphology bands
-    uint32_t ginv;                    // persistent step: 0x80000000 | inverse gain, once known
+    uint32_t ginv;                    // persistent step and spans: 0x80000000 | inverse gain, once known
     uint32_t pick;                    // deferred tracking: root of the largest component (or none)
 };
 
@@ -130,9 +135,9 @@ struct Table {
 
 static_assert(sizeof(TableHeader) % 8 == 0, "job array alignment");
 
-// Consecutive frames of one stream whose jobs a table holds in order (a
-// context's launch): one model, one geometry, one set of thresholds, frames
-// and raw masks at fixed strides. Passed to kernels by value.
+// What classify needs of consecutive frames of one stream (a context's
+// launch): one model, one geometry, one set of thresholds, frames and raw
+// masks at fixed strides. Passed by value.
 struct FrameSpan {
     const uint8_t *frames;     // frame i at frames + i * frame_stride
     size_t frame_stride;
@@ -145,6 +150,7 @@ struct FrameSpan {
     uint32_t S_q16;
     HueForm hue;
 };
+HueForm hue_form(const HueTest &h);
 
 // Launch shapes (tunable per resolution class).
 struct Tuning {
@@ -183,37 +189,54 @@ struct StageEvents {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, s, __VA_ARGS__);                \
     } while (0)
 
-// The per-call fields of job 0 of a one-frame launch, passed to the gain
-// kernel by value when the table slot on the device already holds the rest
-// of the job (valid != 0): the gain reads its frame from here, and its
-// first workgroup writes these fields into the job for the kernels after it.
-struct CallPatch {
+// A launch over n consecutive frames of one stream: the fields of its first
+// job that change from call to call, and the strides to the next ones. What
+// does not change lies in device memory (base: a job of the stream, its
+// scratch arrays those of frame slot 0). The gain kernel writes the job table
+// from both, so that nothing is uploaded. Kernel arguments are read from host
+// memory, so they are kept few: 700 bytes of them cost 8 to 15 us a launch.
+// words between the arrival counts of two frames (a cache line each: sharing
+// lines cost 6 us over 64 frames)
+constexpr int kArrivedStride = 32;
+struct SpanJobs {
+    const Job *base;                    // null when learning: no kernel but minmax follows
     const uint8_t *frame;
-    uint64_t *fizi, *hand;
-    fizi_pointer *out, *hout;
+    size_t frame_bytes;
+    uint64_t *raw, *fizi, *hand;        // hand null: none
+    size_t raw_bytes, fizi_words, hand_words, slot_bytes;
+    fizi_pointer *out, *ring;           // ring[k & ring_mask]: the host ring's place of frame index k
+    TrackState *track;
     uint64_t frame_index;
-    int32_t valid;
+    uint16_t *yref;
+    uint32_t ring_mask;
+    int32_t n, W, H, rs;
+    int32_t band, mgroup;
+    int32_t cls_tiles, mor_items;       // tiles of one frame
+    int32_t glo, ghi;
+    uint32_t *arrived;                  // one count per frame (kArrivedStride), 0 between launches
+    int32_t make_yref;                  // learning: the reference is frame 0, written to yref
+    HueTest hue;
 };
 
 // Kernel launchers (fizi_kernels.hip). Each returns the hipError_t of its launch.
-hipError_t launch_make_yref(const uint8_t *frame0, uint16_t *yref, int W, int H, int rs,
-                            hipStream_t s);
 hipError_t launch_gain(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
-                       hipStream_t s, StageEvents ev = {}, const CallPatch *patch = nullptr);
+                       hipStream_t s, StageEvents ev = {});
+hipError_t launch_put_job(Job *d_job, const Job &J, hipStream_t s);
+// Gain of a span's frames; builds its table.
+hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, StageEvents ev = {});
 hipError_t launch_minmax(const Table *d_tab, int njobs, uint8_t *bgmin, uint8_t *bgmax,
                          int npx, int reset, bool masked, int n_cu, hipStream_t s, StageEvents ev = {});
 hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                            hipStream_t s, StageEvents ev = {});
-hipError_t launch_classify_span(const Table *d_tab, const FrameSpan &F, int n_cu, hipStream_t s,
+hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s,
                                 StageEvents ev = {});
 hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max_ops, int n_cu,
                         const Tuning &t, hipStream_t s, StageEvents ev = {});
 // serial: one workgroup takes the jobs in table order (consecutive frames of
 // one tracked stream); small: 256-thread workgroups, for a launch that runs
-// beside a streaming kernel; clear_acc: each job's accumulators are zeroed
-// once read (its table slot is then reused without an upload).
+// beside a streaming kernel.
 hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev = {}, bool serial = false,
-                          bool small = false, bool clear_acc = false);
+                          bool small = false);
 hipError_t launch_persistent(const Table *d_tab, int max_wd, int max_ops, int n_cu, const Tuning &t,
                              uint8_t *persist, hipStream_t s, StageEvents ev = {});
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);

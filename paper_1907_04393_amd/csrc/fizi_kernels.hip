@@ -1,9 +1,11 @@
 // HIP kernels of the FIZI/Mouse pipeline for gfx950 (CDNA4, wave64).
 //
-//   k_make_yref  reference luminance of the sampled rows of the first
-//                learning frame (Section 2 initialisation, Section 3.2)
 //   k_gain       per-frame sums over the usable sampled pixels; each consumer
 //                turns a frame's sums into its Q16 inverse gain
+//   k_gain_span  the same for consecutive frames of one stream; writes their
+//                job table, and when learning starts also the reference
+//                luminance of the sampled rows of the first frame (Section 2
+//                initialisation, Section 3.2)
 //   k_minmax     background learning and partial re-learning: per-pixel,
 //                per-channel min/max of the gain-corrected frames, model read
 //                and written once (Section 3.1 (i), Section 3.3)
@@ -139,18 +141,65 @@ __device__ __forceinline__ uint32_t inv_gain(unsigned long long num, unsigned lo
 // The frame's inverse gain from its gain accumulators. `same_launch`: the
 // sums were written earlier in the same launch (persistent step), so they
 // are read with device-scope atomic loads; after a kernel boundary plain
-// (scalar) loads see them. U: sums loaded together (fewer hold fewer
-// registers).
-template <int U = kGainSlots>
+// (scalar) loads see them. One thread; wave_job_gain is the whole wave's.
 __device__ __forceinline__ uint32_t job_gain(const Job *J, bool same_launch)
 {
     unsigned long long n = 0, d = 0;
-#pragma unroll U
+#pragma unroll
     for (int i = 0; i < kGainSlots; ++i) {
         n += same_launch ? ld_dev(&J->num[i]) : J->num[i];
         d += same_launch ? ld_dev(&J->den[i]) : J->den[i];
     }
     return inv_gain(n, d, J->glo, J->ghi);
+}
+
+// The same for a whole wave: lane l holds one of the 2 x 32 sums. Their
+// totals go through DPP adds of 16-bit halves (each
+// lane's half sums stay below 2^21): within rows of 16 lanes, then row 0 into
+// row 1 and row 2 into row 3, so that lane 31 holds the reference's total and
+// lane 63 the frame's.
+static_assert(kGainSlots == 32 && offsetof(Job, den) == offsetof(Job, num) + 4 * kGainSlots,
+              "one gain sum per lane, num then den");
+__device__ __forceinline__ uint32_t wave_gain(uint32_t slot, int glo, int ghi)
+{
+    auto rows = [](uint32_t v) {
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+        return v;
+    };
+    const uint32_t lo = rows(slot & 0xFFFFu), hi = rows(slot >> 16);
+    auto total = [&](int lane) {
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, lane) << 16) +
+               (uint32_t)__builtin_amdgcn_readlane((int)lo, lane);
+    };
+    return inv_gain(total(31), total(63), glo, ghi);
+}
+
+// (after a kernel boundary)
+__device__ __forceinline__ uint32_t wave_job_gain(const Job *J)
+{
+    return wave_gain(G(J->num)[threadIdx.x & (kWave - 1)], J->glo, J->ghi);
+}
+
+// A frame's inverse gain after the gain kernel: k_gain_span leaves it in the
+// job, after k_gain (batch steps) each wave takes it from the sums.
+constexpr uint32_t kGainKnown = 0x80000000u;
+
+__device__ __forceinline__ uint32_t frame_gain(const Job *J)
+{
+    const uint32_t g = J->ginv;
+    return g & kGainKnown ? g & ~kGainKnown : wave_job_gain(J);
+}
+
+// Inverse gains of jobs [j0, j0 + n) of a span into s_inv (the whole
+// workgroup; it synchronises afterwards).
+__device__ __forceinline__ void span_gains(const Table *T, int j0, int n, uint32_t *s_inv)
+{
+    for (int j = threadIdx.x; j < n; j += blockDim.x)
+        s_inv[j] = T->jobs[j0 + j].ginv & ~kGainKnown;
 }
 
 // Skin-hue membership without division; see HueTest. Chroma > 0 is checked
@@ -166,22 +215,6 @@ __device__ __forceinline__ bool hue_in(int r, int g, int b, const HueTest &h)
     if (h.mode == 3)
         return (d1 >= 0) | (__mul24(h.k2r, rb) + __mul24(h.k2g, gb) <= 0);
     if (h.mode == 2)
-        return d1 >= 0;
-    const int dp = __mul24(h.dr, r) + __mul24(h.dg, g) + __mul24(h.db, b);
-    return (d1 == 0) & (3 * dp - __mul24(h.dsum, r + g + b) > 0);
-}
-
-// hue_in with the interval's case fixed at compile time (no branch on it).
-template <int MODE>
-__device__ __forceinline__ bool hue_in_mode(int r, int g, int b, const HueTest &h)
-{
-    const int rb = r - b, gb = g - b;
-    const int d1 = __mul24(h.k1r, rb) + __mul24(h.k1g, gb);
-    if constexpr (MODE == 1)
-        return (d1 >= 0) & (__mul24(h.k2r, rb) + __mul24(h.k2g, gb) <= 0);
-    if constexpr (MODE == 3)
-        return (d1 >= 0) | (__mul24(h.k2r, rb) + __mul24(h.k2g, gb) <= 0);
-    if constexpr (MODE == 2)
         return d1 >= 0;
     const int dp = __mul24(h.dr, r) + __mul24(h.dg, g) + __mul24(h.db, b);
     return (d1 == 0) & (3 * dp - __mul24(h.dsum, r + g + b) > 0);
@@ -236,35 +269,116 @@ __device__ __forceinline__ uint64_t row_word(uint32_t nib)
 }
 
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_make_yref(const uint8_t *__restrict__ frame0,
-                                                   uint16_t *__restrict__ yref, int W, int H,
-                                                   int rs)
+// The gain's usable-pixel test and sums on pairs of 16-bit halves: a pixel's
+// (R, G) and (B, B) come by one byte permute each, their difference is
+// (R - B, G - B), and each hue form is one two-element dot product of it. 21
+// instructions per pixel; byte by byte it took 30.
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+struct GainHue {
+    s16x2 k1, k2, k3;          // the forms' coefficients of (R - B, G - B); |k| <= 18000
+};
+
+__device__ __forceinline__ GainHue gain_hue(const HueTest &h)
 {
-    const int rows = (H + rs - 1) / rs;
-    const int groups = W / 4;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < rows * groups;
-         i += gridDim.x * blockDim.x) {
-        const int rr = i / groups, g = i - rr * groups;
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(frame0 + (size_t)rr * rs * W * 3) + 3 * g;
-        const uint32_t w0 = p[0], w1 = p[1], w2 = p[2];
-        uint32_t out[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t r = byte_of(w0, w1, w2, 3 * k), gg = byte_of(w0, w1, w2, 3 * k + 1),
-                           b = byte_of(w0, w1, w2, 3 * k + 2);
-            const bool ok = (r - 1u < 254u) & (gg - 1u < 254u) & (b - 1u < 254u);
-            out[k] = ok ? r + 2 * gg + b : kYrefClipped;
-        }
-        uint2 v;
-        v.x = out[0] | (out[1] << 16);
-        v.y = out[2] | (out[3] << 16);
-        reinterpret_cast<uint2 *>(yref + (size_t)rr * W)[g] = v;
+    GainHue g;
+    g.k1 = s16x2{(short)h.k1r, (short)h.k1g};
+    g.k2 = s16x2{(short)h.k2r, (short)h.k2g};
+    // mode 0: 3 d.p - sum(d) sum(p), unchanged when a gray is added to p
+    g.k3 = s16x2{(short)(3 * h.dr - h.dsum), (short)(3 * h.dg - h.dsum)};
+    return g;
+}
+
+// Pixel K of the four in 3 dwords as (R, G) and (B, B).
+template <int K>
+__device__ __forceinline__ void px_pairs(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t &rg, uint32_t &bb)
+{
+    if constexpr (K == 0) {
+        rg = __builtin_amdgcn_perm(w1, w0, 0x0c010c00u);
+        bb = __builtin_amdgcn_perm(w1, w0, 0x0c020c02u);
+    } else if constexpr (K == 1) {
+        rg = __builtin_amdgcn_perm(w1, w0, 0x0c040c03u);
+        bb = __builtin_amdgcn_perm(w1, w0, 0x0c050c05u);
+    } else if constexpr (K == 2) {
+        rg = __builtin_amdgcn_perm(w2, w1, 0x0c030c02u);
+        bb = __builtin_amdgcn_perm(w2, w1, 0x0c040c04u);
+    } else {
+        rg = __builtin_amdgcn_perm(w2, w1, 0x0c060c05u);
+        bb = __builtin_amdgcn_perm(w2, w1, 0x0c070c07u);
     }
 }
 
-// ---------------------------------------------------------------------------
-// One sampled row of one frame: sums of reference and frame luminance over
-// its usable pixels, added to the frame's accumulators.
+// R + 2 G + B plus acc.
+__device__ __forceinline__ uint32_t px_lum(uint32_t rg, uint32_t bb, uint32_t acc)
+{
+    const u16x2 one{1, 0}, two{1, 2};
+    acc = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, bb), one, acc, false);
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, rg), two, acc, false);
+}
+
+// Whether a channel is 0 or 255.
+__device__ __forceinline__ bool px_clipped(uint32_t rg, uint32_t bb)
+{
+    const u16x2 one{1, 1}, last{253, 253};
+    const u16x2 m = __builtin_elementwise_max(__builtin_bit_cast(u16x2, rg) - one, __builtin_bit_cast(u16x2, bb) - one);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(m, last)) != 0u;
+}
+
+// (reference << 16 | frame luminance) of a usable pixel, 0 of any other; yhi
+// is its reference << 16.
+template <int MODE>
+__device__ __forceinline__ uint32_t gain_px(uint32_t rg, uint32_t bb, uint32_t yhi, const GainHue &h)
+{
+    const s16x2 d = __builtin_bit_cast(s16x2, rg) - __builtin_bit_cast(s16x2, bb);
+    const int d1 = __builtin_amdgcn_sdot2(d, h.k1, 0, false);
+    bool skin = __builtin_bit_cast(uint32_t, d) != 0u;       // chroma > 0
+    if constexpr (MODE == 0)
+        skin = (d1 == 0) & (__builtin_amdgcn_sdot2(d, h.k3, 0, false) > 0);
+    else if constexpr (MODE == 1)
+        skin = skin & (d1 >= 0) & (__builtin_amdgcn_sdot2(d, h.k2, 0, false) <= 0);
+    else if constexpr (MODE == 2)
+        skin = skin & (d1 >= 0);
+    else
+        skin = skin & ((d1 >= 0) | (__builtin_amdgcn_sdot2(d, h.k2, 0, false) <= 0));
+    const bool ok = (yhi < ((uint32_t)kYrefClipped << 16)) & !px_clipped(rg, bb) & !skin;
+    return ok ? px_lum(rg, bb, yhi) : 0u;
+}
+
+// Four pixels (3 dwords) with their references (2 dwords of two): the sums of
+// gain_px, each half of at most 4 x 1020.
+template <int MODE>
+__device__ __forceinline__ uint32_t gain_px4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t y01, uint32_t y23,
+                                             const GainHue &h)
+{
+    uint32_t rg, bb, sum;
+    px_pairs<0>(w0, w1, w2, rg, bb);
+    sum = gain_px<MODE>(rg, bb, y01 << 16, h);
+    px_pairs<1>(w0, w1, w2, rg, bb);
+    sum += gain_px<MODE>(rg, bb, y01 & 0xFFFF0000u, h);
+    px_pairs<2>(w0, w1, w2, rg, bb);
+    sum += gain_px<MODE>(rg, bb, y23 << 16, h);
+    px_pairs<3>(w0, w1, w2, rg, bb);
+    return sum + gain_px<MODE>(rg, bb, y23 & 0xFFFF0000u, h);
+}
+
+// The references of four pixels, kYrefClipped where a channel is 0 or 255.
+template <int K>
+__device__ __forceinline__ uint32_t yref_px(uint32_t w0, uint32_t w1, uint32_t w2)
+{
+    uint32_t rg, bb;
+    px_pairs<K>(w0, w1, w2, rg, bb);
+    return px_clipped(rg, bb) ? kYrefClipped : px_lum(rg, bb, 0u);
+}
+
+__device__ __forceinline__ void yref_px4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t &y01, uint32_t &y23)
+{
+    y01 = yref_px<0>(w0, w1, w2) | (yref_px<1>(w0, w1, w2) << 16);
+    y23 = yref_px<2>(w0, w1, w2) | (yref_px<3>(w0, w1, w2) << 16);
+}
+
+// A tile of one frame (kGainRows sampled rows): sums of reference and frame
+// luminance over its usable pixels, added to the frame's accumulators.
 template <int MODE>
 __device__ __forceinline__ void gain_tile_mode(Table *__restrict__ T, int j, int tile, const uint8_t *fr)
 {
@@ -273,21 +387,9 @@ __device__ __forceinline__ void gain_tile_mode(Table *__restrict__ T, int j, int
     Job *J = &T->jobs[j];
     const int W = J->W;
     const int rows = (J->H + J->rs - 1) / J->rs;
-    const HueTest h = J->hue;
+    const GainHue h = gain_hue(J->hue);
     uint32_t num = 0, den = 0;
     const int r0 = tile * kGainRows, nr = min(rows, r0 + kGainRows) - r0;
-    // one usable-pixel test, summed into num/den; straight-line code (every
-    // test evaluated, the sums selected) rather than a branch per pixel
-    auto add_px = [&](uint32_t r, uint32_t gg, uint32_t b, uint32_t y) {
-        const int mx = max(max((int)r, (int)gg), (int)b);
-        const int mn = min(min((int)r, (int)gg), (int)b);
-        // every channel in 1..254
-        const bool unclipped = (y != kYrefClipped) & (mn >= 1) & (mx <= 254);
-        const bool skin = (mx > mn) & hue_in_mode<MODE>((int)r, (int)gg, (int)b, h);
-        const bool ok = unclipped & !skin;
-        num += ok ? y : 0u;
-        den += ok ? r + 2 * gg + b : 0u;
-    };
     if ((reinterpret_cast<uintptr_t>(fr) & 15u) == 0) {
         // 16 pixels per item: three 16-byte loads of the frame row, two of
         // the reference row; items of the tile's rows in one flat range
@@ -305,31 +407,24 @@ __device__ __forceinline__ void gain_tile_mode(Table *__restrict__ T, int j, int
             const GLOBAL u32x4 *fp = reinterpret_cast<const GLOBAL u32x4 *>(frame + (size_t)rr * rowb) + 3 * g;
             const GLOBAL u32x4 *yp = reinterpret_cast<const GLOBAL u32x4 *>(yref + (size_t)rr * W) + 2 * g;
             const u32x4 a = fp[0], b = fp[1], c = fp[2], ya = yp[0], yb = yp[1];
-            const uint32_t fw[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w};
-            const uint32_t yw[8] = {ya.x, ya.y, ya.z, ya.w, yb.x, yb.y, yb.z, yb.w};
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int q0 = 3 * k;
-                add_px((fw[q0 >> 2] >> (8 * (q0 & 3))) & 0xFFu, (fw[(q0 + 1) >> 2] >> (8 * ((q0 + 1) & 3))) & 0xFFu,
-                       (fw[(q0 + 2) >> 2] >> (8 * ((q0 + 2) & 3))) & 0xFFu, (yw[k >> 1] >> (16 * (k & 1))) & 0xFFFFu);
-            }
+            const uint32_t s = gain_px4<MODE>(a.x, a.y, a.z, ya.x, ya.y, h) +
+                               gain_px4<MODE>(a.w, b.x, b.y, ya.z, ya.w, h) +
+                               gain_px4<MODE>(b.z, b.w, c.x, yb.x, yb.y, h) +
+                               gain_px4<MODE>(c.y, c.z, c.w, yb.z, yb.w, h);
+            num += s >> 16;
+            den += s & 0xFFFFu;
         }
     } else {
-    const int groups = W / 4;
+        const int groups = W / 4;
 #pragma unroll 4
-    for (int it = threadIdx.x; it < nr * groups; it += blockDim.x) {
-        const int rr = r0 + it / groups, g = it - (it / groups) * groups;
-        const GLOBAL uint32_t *row = G(reinterpret_cast<const uint32_t *>(fr + (size_t)rr * J->rs * W * 3));
-        const GLOBAL uint64_t *yr = G(reinterpret_cast<const uint64_t *>(J->yref + (size_t)rr * W));
-        const uint32_t w0 = row[3 * g], w1 = row[3 * g + 1], w2 = row[3 * g + 2];
-        const uint64_t yv = yr[g];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t r = byte_of(w0, w1, w2, 3 * k), gg = byte_of(w0, w1, w2, 3 * k + 1),
-                           b = byte_of(w0, w1, w2, 3 * k + 2);
-            add_px(r, gg, b, (uint32_t)(yv >> (16 * k)) & 0xFFFFu);
+        for (int it = threadIdx.x; it < nr * groups; it += blockDim.x) {
+            const int rr = r0 + it / groups, g = it - (it / groups) * groups;
+            const GLOBAL uint32_t *row = G(reinterpret_cast<const uint32_t *>(fr + (size_t)rr * J->rs * W * 3));
+            const GLOBAL uint32_t *yr = G(reinterpret_cast<const uint32_t *>(J->yref + (size_t)rr * W));
+            const uint32_t s = gain_px4<MODE>(row[3 * g], row[3 * g + 1], row[3 * g + 2], yr[2 * g], yr[2 * g + 1], h);
+            num += s >> 16;
+            den += s & 0xFFFFu;
         }
-    }
     }
     num = wave_sum(num);
     den = wave_sum(den);
@@ -339,7 +434,7 @@ __device__ __forceinline__ void gain_tile_mode(Table *__restrict__ T, int j, int
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long n = 0, d = 0;
+        uint32_t n = 0, d = 0;
         for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
             n += s_num[w];
             d += s_den[w];
@@ -389,24 +484,185 @@ __device__ __forceinline__ void gain_tile(Table *__restrict__ T, int j, int tile
     }
 }
 
-// P.valid: job 0's per-call fields come with the launch (its table slot was
-// not uploaded again); the first workgroup stores them into the job for the
-// kernels that follow on the stream, and the tiles of job 0 take their frame
-// from P.
-__global__ __launch_bounds__(256) void k_gain(Table *__restrict__ T, CallPatch P)
+__global__ __launch_bounds__(256) void k_gain(Table *__restrict__ T)
 {
-    if (P.valid && blockIdx.x == 0 && threadIdx.x == 0) {
-        Job *J = &T->jobs[0];
-        J->frame = P.frame;
-        J->fizi = P.fizi;
-        J->hand = P.hand;
-        J->out = P.out;
-        J->hout = P.hout;
-        J->frame_index = P.frame_index;
+    for_block_tiles(T->h.gain_pre, T->h.njobs,
+                    [&](int j, int tile) { gain_tile(T, j, tile, T->jobs[j].frame); });
+}
+
+__global__ void k_put_job(Job *__restrict__ d, Job J)
+{
+    if (threadIdx.x == 0)
+        *d = J;
+}
+
+// Gain of consecutive frames of one stream: workgroup (p, i) sums part p of
+// frame i's sampled pixels, items of 16 pixels (4 where the frames are only
+// 4-byte aligned) taken p blockDim + thread, + gridDim.x blockDim, ..., and
+// stores its sums in slot p of the frame's job: nothing to zero. The frame's
+// last workgroup leaves the inverse gain in the job; every workgroup of the
+// kernels that follow would otherwise sum the slots and divide (6 us of
+// classify over 64 frames, 22 us of minmax over 50). Its addresses come by
+// value, so that its loads wait for no table. Workgroup (0, n) writes the
+// jobs for the kernels that follow, thread i job i.
+// Bound by the latency of its loads and, in between, the VALU: 64 frames of
+// 1920x1080 (50 MB of frame rows) take 19 us, 22 us tile by tile from a
+// table with atomic sums.
+__device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs &S, int i)
+{
+    Job *J = &T->jobs[i];
+    const Job *B = S.base;
+    const uint8_t *frame = S.frame + (size_t)i * S.frame_bytes;
+    uint64_t *fizi = S.fizi + (size_t)i * S.fizi_words;
+    if (!B) {
+        J->frame = frame;
+        J->fizi = fizi;
+        J->glo = S.glo;
+        J->ghi = S.ghi;
+        return;
     }
-    for_block_tiles(T->h.gain_pre, T->h.njobs, [&](int j, int tile) {
-        gain_tile(T, j, tile, P.valid && j == 0 ? P.frame : T->jobs[j].frame);
-    });
+    // every field but the gain sums, which other workgroups are writing
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(B);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(J);
+    constexpr int kHead = (int)(offsetof(Job, num) / 8);
+    static_assert(offsetof(Job, num) % 8 == 0, "whole 8-byte words");
+    Job head;
+    uint64_t *h = reinterpret_cast<uint64_t *>(&head);
+#pragma unroll
+    for (int q = 0; q < kHead; ++q)
+        h[q] = src[q];
+    const size_t so = (size_t)i * S.slot_bytes;
+    const uint64_t index = S.frame_index + (uint64_t)i;
+    auto moved = [&](auto *p, size_t bytes) {
+        return reinterpret_cast<decltype(p)>(reinterpret_cast<uint8_t *>(p) + bytes);
+    };
+    head.frame = frame;
+    head.raw = moved(S.raw, (size_t)i * S.raw_bytes);
+    head.fizi = fizi;
+    head.hand = S.hand ? S.hand + (size_t)i * S.hand_words : nullptr;
+    head.parent = moved(head.parent, so);
+    head.area = moved(head.area, so);
+    head.runs = moved(head.runs, so);
+    head.links = moved(head.links, so);
+    head.out = S.out + i;
+    head.hout = S.ring ? S.ring + (index & S.ring_mask) : nullptr;
+    head.track = S.track;
+    head.frame_index = index;
+    head.band = S.band;
+    head.mgroup = S.mgroup;
+#pragma unroll
+    for (int q = 0; q < kHead; ++q)
+        dst[q] = h[q];
+    // the accumulators but the inverse gain, which the frame's last workgroup
+    // stores
+    J->nruns = J->flags = J->nlinks = J->nflag = 0u;
+    J->gain_done = J->morph_done = J->pick = 0u;
+    T->h.cls_pre[i + 1] = (i + 1) * S.cls_tiles;
+    T->h.mor_pre[i + 1] = (i + 1) * S.mor_items;
+    if (i == 0) {
+        T->h.njobs = S.n;
+        T->h.cls_pre[0] = T->h.mor_pre[0] = 0;
+    }
+}
+
+// MODE: the hue interval's case; MAKE: the reference comes from frame 0 (and
+// frame 0's workgroups write it); WIDE: frames 16-byte aligned.
+template <int MODE, bool MAKE, bool WIDE>
+__global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const SpanJobs S)
+{
+    __shared__ uint32_t s_num[1024 / kWave], s_den[1024 / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int part = blockIdx.x, i = blockIdx.y;
+    if (i == S.n) {
+        if (part == 0)
+            for (int j = threadIdx.x; j < S.n; j += blockDim.x)
+                write_job(T, S, j);
+        return;
+    }
+    const GLOBAL uint8_t *frame0 = G(S.frame), *frame = frame0 + (size_t)i * S.frame_bytes;
+    GLOBAL uint16_t *yref = G(S.yref);
+    const GainHue h = gain_hue(S.hue);
+    const uint32_t W = (uint32_t)S.W, rows = (uint32_t)(S.H + S.rs - 1) / (uint32_t)S.rs;
+    constexpr int kQ = WIDE ? 4 : 1;             // groups of four pixels per item
+    const uint32_t per_row = W / (4 * kQ), items = rows * per_row;
+    uint32_t num = 0, den = 0;                   // at most 2^25 per lane
+    for (uint32_t it = (uint32_t)part * blockDim.x + threadIdx.x; it < items; it += gridDim.x * blockDim.x) {
+        const uint32_t row = it / per_row, g = it - row * per_row;
+        const size_t fo = (size_t)row * (size_t)S.rs * W * 3u + 12u * kQ * g;
+        const size_t yo = (size_t)row * W + 4u * kQ * g;
+        uint32_t w[3 * kQ], y[2 * kQ];
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<u32x4 *>(&w[4 * q]) = reinterpret_cast<const GLOBAL u32x4 *>(frame + fo)[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                w[q] = reinterpret_cast<const GLOBAL uint32_t *>(frame + fo)[q];
+        }
+        if constexpr (MAKE) {
+            uint32_t r[3 * kQ];
+#pragma unroll
+            for (int q = 0; q < 3 * kQ; ++q)
+                r[q] = reinterpret_cast<const GLOBAL uint32_t *>(frame0 + fo)[q];
+#pragma unroll
+            for (int q = 0; q < kQ; ++q)
+                yref_px4(r[3 * q], r[3 * q + 1], r[3 * q + 2], y[2 * q], y[2 * q + 1]);
+            if (i == 0) {
+#pragma unroll
+                for (int q = 0; q < 2 * kQ; ++q)
+                    reinterpret_cast<GLOBAL uint32_t *>(yref + yo)[q] = y[q];
+            }
+        } else if constexpr (WIDE) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                *reinterpret_cast<u32x4 *>(&y[4 * q]) = reinterpret_cast<const GLOBAL u32x4 *>(yref + yo)[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                y[q] = reinterpret_cast<const GLOBAL uint32_t *>(yref + yo)[q];
+        }
+        uint32_t s = 0;                          // halves of at most 16 x 1020
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+            s += gain_px4<MODE>(w[3 * q], w[3 * q + 1], w[3 * q + 2], y[2 * q], y[2 * q + 1], h);
+        num += s >> 16;
+        den += s & 0xFFFFu;
+    }
+    num = wave_sum(num);
+    den = wave_sum(den);
+    if (lane == 0) {
+        s_num[wave] = num;
+        s_den[wave] = den;
+    }
+    __syncthreads();
+    if (wave != 0)
+        return;
+    // the first wave alone from here on, so that the others' places are free
+    uint32_t n = 0, d = 0;
+    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
+        n += s_num[w];
+        d += s_den[w];
+    }
+    // the frame's last workgroup turns the sums into its inverse gain: the
+    // sums go through this XCD's L2, and are there before the count (which
+    // wraps to 0 for the next launch)
+    Job *J = &T->jobs[i];
+    uint32_t before = 0;
+    if (lane == 0) {
+        st_dev(G(&J->num[part]), n);
+        st_dev(G(&J->den[part]), d);
+        wait_own_memory();
+        before = atomicInc(S.arrived + i * kArrivedStride, gridDim.x - 1);
+    }
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != gridDim.x - 1)
+        return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    // slots past the parts hold nothing of this launch
+    const uint32_t slot = (uint32_t)(lane & (kGainSlots - 1)) < gridDim.x ? ld_dev(&J->num[lane]) : 0u;
+    const uint32_t inv = wave_gain(slot, S.glo, S.ghi);
+    if (lane == 0)
+        J->ginv = kGainKnown | inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -417,8 +673,7 @@ __global__ __launch_bounds__(256) void k_minmax(Table *__restrict__ T, int nj,
                                                 uint8_t *__restrict__ bgmax, int npx, int reset)
 {
     __shared__ uint32_t s_inv[kMaxJobs];
-    for (int j = threadIdx.x; j < nj; j += blockDim.x)
-        s_inv[j] = job_gain(&T->jobs[j], false);
+    span_gains(T, 0, nj, s_inv);
     __syncthreads();
     const int ngroups = npx / 4;
     for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ngroups; g += gridDim.x * blockDim.x) {
@@ -701,12 +956,11 @@ __device__ __forceinline__ void classify_tile(Table *__restrict__ T, int j, int 
 
 // Tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the frame index only grows,
 // so it is advanced, not searched. A block meets one to three frames, so a
-// frame's inverse gain (sixteen pairs of sums and a 64-bit division) is
-// computed when its first tile comes, once per block, by thread 0.
+// frame's inverse gain (32 pairs of sums and a 64-bit division) is computed
+// when its first tile comes, by each wave for itself.
 template <int ITERS>
 __device__ __forceinline__ void classify_tiles(Table *__restrict__ T, int nj, const int32_t *s_pre)
 {
-    __shared__ uint32_t s_inv;
     const int total = s_pre[nj];
     int j = 0, jinv = -1;
     uint32_t inv = 0;
@@ -714,11 +968,7 @@ __device__ __forceinline__ void classify_tiles(Table *__restrict__ T, int nj, co
         while (s_pre[j + 1] <= t)
             ++j;
         if (j != jinv) {
-            __syncthreads();
-            if (threadIdx.x == 0)
-                s_inv = job_gain(&T->jobs[j], false);
-            __syncthreads();
-            inv = s_inv;
+            inv = frame_gain(&T->jobs[j]);
             jinv = j;
         }
         classify_tile<ITERS>(T, j, t - s_pre[j], inv);
@@ -844,8 +1094,7 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
 #pragma unroll
     for (int q = 0; q < kSpanAhead; ++q)
         ring[q] = load(min(q, nf - 1));
-    if ((int)threadIdx.x < nf)
-        s_inv[threadIdx.x] = job_gain<4>(&T->jobs[f0 + threadIdx.x], false);
+    span_gains(T, f0, nf, s_inv);
     __syncthreads();
     Box4 box;
     box_of<KIND>(F, l, u, p < F.npx, box);
@@ -2024,7 +2273,7 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
     const int H = J->H, Wd = J->Wd;
     GLOBAL uint32_t *area = G(J->area);
     GLOBAL uint64_t *hand = J->hand ? G(J->hand) : nullptr;
-    const uint32_t inv = job_gain(J, same_launch);
+    const uint32_t inv = same_launch ? job_gain(J, true) : frame_gain(J);
     if (hand)
         for (int i = threadIdx.x; i < H * Wd; i += blockDim.x)
             hand[i] = 0ull;
@@ -2063,27 +2312,13 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
     __syncthreads();
 }
 
-// The job's accumulators (every field from the gain sums on) in 8-byte words.
-constexpr int kAccWords = (int)((sizeof(Job) - offsetof(Job, num)) / 8);
-static_assert((sizeof(Job) - offsetof(Job, num)) % 8 == 0 && offsetof(Job, num) % 8 == 0,
-              "the accumulators are whole 8-byte words");
-
 template <int NT>
-__global__ __launch_bounds__(NT) void k_resolve(Table *__restrict__ T, int defer, int clear_acc)
+__global__ __launch_bounds__(NT) void k_resolve(Table *__restrict__ T, int defer)
 {
-    static_assert(NT >= kAccWords, "one thread per accumulator word");
     __shared__ AreaTable s_tab;
     const int nj = T->h.njobs;
-    for (int j = blockIdx.x; j < nj; j += gridDim.x) {
+    for (int j = blockIdx.x; j < nj; j += gridDim.x)
         resolve_job(T, j, false, s_tab, defer != 0);
-        // clear_acc: zero the job's accumulators, as an upload of the table
-        // would, for a next call that reuses the slot without one. Every
-        // thread has read them (resolve_job ends on a barrier), and no later
-        // kernel of the call reads them.
-        if (clear_acc && threadIdx.x < kAccWords)
-            reinterpret_cast<unsigned long long *>(reinterpret_cast<uint8_t *>(&T->jobs[j]) +
-                                                   offsetof(Job, num))[threadIdx.x] = 0ull;
-    }
 }
 
 // Tracking of consecutive frames of one stream after a deferred component
@@ -2299,7 +2534,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX == 4 &
             if (publish_add(&J->gain_done, 1u, &s_u) + 1u == ng && threadIdx.x == 0) {
                 // the frame's last gain tile: its inverse gain, once, for every band
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                st_dev(G(&J->ginv), 0x80000000u | job_gain(J, true));
+                st_dev(G(&J->ginv), kGainKnown | job_gain(J, true));
             }
             continue;
         }
@@ -2363,26 +2598,63 @@ __global__ void k_fill_u32(uint32_t *p, uint32_t v, size_t n)
 }  // namespace
 
 // ---------------------------------------------------------------------------
-hipError_t launch_make_yref(const uint8_t *frame0, uint16_t *yref, int W, int H, int rs, hipStream_t s)
-{
-    const int rows = (H + rs - 1) / rs;
-    const int n = rows * (W / 4);
-    const int grid = min((n + 255) / 256, 4096);
-    k_make_yref<<<grid, 256, 0, s>>>(frame0, yref, W, H, rs);
-    return hipGetLastError();
-}
-
 hipError_t launch_gain(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t, hipStream_t s,
-                       StageEvents ev, const CallPatch *patch)
+                       StageEvents ev)
 {
     if (total_tiles <= 0)
         return hipSuccess;
     const int grid = min(total_tiles, n_cu * t.grid_per_cu);
-    CallPatch p{};
-    if (patch)
-        p = *patch;
-    FIZI_LAUNCH(k_gain, grid, 256, 0, s, ev, const_cast<Table *>(d_tab), p);
+    FIZI_LAUNCH(k_gain, grid, 256, 0, s, ev, const_cast<Table *>(d_tab));
     return hipGetLastError();
+}
+
+namespace {
+
+template <int MODE>
+hipError_t launch_gain_span_mode(Table *tab, const SpanJobs &S, hipStream_t s, StageEvents ev)
+{
+    const bool wide = reinterpret_cast<uintptr_t>(S.frame) % 16 == 0;
+    // waves per frame: one item per lane, but no more than about eight waves
+    // per SIMD over the launch; in parts of four waves, more (up to 16) where
+    // 32 parts would not hold them, and as many rounds as remain, the same
+    // for every part. Over 50 frames of 1920x1080 (learning) parts of 4 / 8 /
+    // 16 waves take 19 / 23 / 27 us, half the waves 22.
+    const long long items = (long long)((S.H + S.rs - 1) / S.rs) * (S.W / (wide ? 16 : 4));
+    const int full = (int)((items + kWave - 1) / kWave), waves_f = std::min(full, std::max(32, 8192 / S.n));
+    const int parts = std::max(1, std::min(kGainSlots, (waves_f + 3) / 4));
+    const int most = std::min(16, (waves_f + parts - 1) / parts), rounds = (full + parts * most - 1) / (parts * most);
+    const int threads = kWave * ((full + parts * rounds - 1) / (parts * rounds));
+    const dim3 grid((unsigned)parts, (unsigned)S.n + 1);
+    if (S.make_yref) {
+        if (wide)
+            FIZI_LAUNCH((k_gain_span<MODE, true, true>), grid, threads, 0, s, ev, tab, S);
+        else
+            FIZI_LAUNCH((k_gain_span<MODE, true, false>), grid, threads, 0, s, ev, tab, S);
+    } else {
+        if (wide)
+            FIZI_LAUNCH((k_gain_span<MODE, false, true>), grid, threads, 0, s, ev, tab, S);
+        else
+            FIZI_LAUNCH((k_gain_span<MODE, false, false>), grid, threads, 0, s, ev, tab, S);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_put_job(Job *d_job, const Job &J, hipStream_t s)
+{
+    k_put_job<<<1, 64, 0, s>>>(d_job, J);
+    return hipGetLastError();
+}
+
+hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, StageEvents ev)
+{
+    switch (S.hue.mode) {
+    case 0: return launch_gain_span_mode<0>(d_tab, S, s, ev);
+    case 1: return launch_gain_span_mode<1>(d_tab, S, s, ev);
+    case 2: return launch_gain_span_mode<2>(d_tab, S, s, ev);
+    default: return launch_gain_span_mode<3>(d_tab, S, s, ev);
+    }
 }
 
 hipError_t launch_minmax(const Table *d_tab, int njobs, uint8_t *bgmin, uint8_t *bgmax, int npx,
@@ -2420,8 +2692,25 @@ hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const 
 // round (seven 256-thread workgroups per CU): then 8, or 4. Measured for 64
 // frames of 1920x1080 with 4 / 8 / 16 / 32 / 64 frames: 124 / 98 / 92 / 98 /
 // 118 us; for 16 frames of 1280x720 (900 tiles) with 8 / 16: 17 / 21 us.
-hipError_t launch_classify_span(const Table *d_tab, const FrameSpan &F, int n_cu, hipStream_t s, StageEvents ev)
+hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &J, int n_cu, hipStream_t s,
+                                StageEvents ev)
 {
+    FrameSpan F{};
+    F.frames = S.frame;
+    F.frame_stride = S.frame_bytes;
+    F.raw = S.raw;
+    F.raw_words = S.raw_bytes / sizeof(uint64_t);
+    F.bgmin = J.bgmin;
+    F.bgmax = J.bgmax;
+    F.npx = (uint32_t)J.W * (uint32_t)J.H;
+    F.n = S.n;
+    F.delta = J.delta;
+    F.S1 = J.S1;
+    F.S0 = J.S0;
+    F.scaled = J.scaled;
+    F.lum2 = J.lum2;
+    F.S_q16 = J.S_q16;
+    F.hue = hue_form(J.hue);
     if (F.n <= 0)
         return hipSuccess;
     const int tiles = (int)((F.npx + 1023u) / 1024u);
@@ -2459,19 +2748,18 @@ hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max
     return hipGetLastError();
 }
 
-hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev, bool serial, bool small,
-                          bool clear_acc)
+hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev, bool serial, bool small)
 {
     if (njobs <= 0)
         return hipSuccess;
     // consecutive tracked frames of one stream: every frame's forest and
     // largest component at once, then the tracking chain in frame order
     Table *tab = const_cast<Table *>(d_tab);
-    const int defer = serial ? 1 : 0, clear = clear_acc ? 1 : 0;
+    const int defer = serial ? 1 : 0;
     if (small)
-        FIZI_LAUNCH(k_resolve<kResolveThreadsSmall>, njobs, kResolveThreadsSmall, 0, s, ev, tab, defer, clear);
+        FIZI_LAUNCH(k_resolve<kResolveThreadsSmall>, njobs, kResolveThreadsSmall, 0, s, ev, tab, defer);
     else
-        FIZI_LAUNCH(k_resolve<kResolveThreads>, njobs, kResolveThreads, 0, s, ev, tab, defer, clear);
+        FIZI_LAUNCH(k_resolve<kResolveThreads>, njobs, kResolveThreads, 0, s, ev, tab, defer);
     if (serial) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
