@@ -386,7 +386,7 @@ int fizi_batch_learn(fizi_batch *b, int32_t stream_id, const uint8_t *d_frames, 
     FIZI_TRY(order_after_previous(b, s));
     int slot;
     FIZI_TRY(b->ring.take(&slot));
-    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, b->n_cu, d_frames, n_frames, reset, s, &b->clk));
+    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, d_frames, n_frames, reset, s, &b->clk));
     FIZI_TRY(b->ring.finish(slot, s));
     return mark_last(b, s);
 }
@@ -410,7 +410,7 @@ int fizi_batch_relearn(fizi_batch *b, int32_t stream_id, const uint8_t *d_frames
     FIZI_TRY(order_after_previous(b, s));
     int slot;
     FIZI_TRY(b->ring.take(&slot));
-    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, b->n_cu, d_frames, n_frames, 0, s, &b->clk, d_fizi_bits));
+    FIZI_TRY(learn_model(m, b->ring.d[slot], b->arrived, b->tune, d_frames, n_frames, 0, s, &b->clk, d_fizi_bits));
     FIZI_TRY(b->ring.finish(slot, s));
     return mark_last(b, s);
 }

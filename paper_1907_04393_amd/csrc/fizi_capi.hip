@@ -271,7 +271,7 @@ int learn_background(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     FIZI_TRY(order_after_previous(c, s));
     FIZI_TRY(join_pending(c, s));
-    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, c->n_cu, d_frames, n_frames, reset, s, &c->clk));
+    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, d_frames, n_frames, reset, s, &c->clk));
     return mark_last(c, s);
 }
 
@@ -290,7 +290,7 @@ int relearn_background(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, c
     FIZI_TRY(order_after_previous(c, s));
     // the masks may come from a call whose back half is still pending
     FIZI_TRY(join_pending(c, s));
-    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, c->n_cu, d_frames, n_frames, 0, s, &c->clk, d_fizi_bits));
+    FIZI_TRY(learn_model(c->m, take_table(c), reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune, d_frames, n_frames, 0, s, &c->clk, d_fizi_bits));
     return mark_last(c, s);
 }
 

@@ -134,7 +134,7 @@ int device_cu_count(int *device, int *n_cu);
 // I_FIZI bit masks whose set bits keep a frame's pixels out of the model).
 // d_tab: a table in device memory that no enqueued work on another stream
 // than s still reads; arrived: kArrivedWords words, 0 between launches.
-int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, int n_cu, const uint8_t *frames, int n, int reset,
+int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, const uint8_t *frames, int n, int reset,
                 hipStream_t s, StageClock *clk, const uint64_t *masks = nullptr);
 
 // Enqueues gain, classify, morphology and components for the jobs of the

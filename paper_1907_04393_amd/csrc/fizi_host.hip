@@ -457,7 +457,7 @@ int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &
     return FIZI_OK;
 }
 
-int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, int n_cu, const uint8_t *frames, int n, int reset,
+int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, const uint8_t *frames, int n, int reset,
                 hipStream_t s, StageClock *clk, const uint64_t *masks)
 {
     const size_t px = (size_t)m.g.width * m.g.height;
@@ -466,15 +466,12 @@ int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, int 
         Job J;
         fill_job(m, t.morph_rows, J);
         J.frame = frames + (size_t)f0 * px * 3;
-        if (masks)
-            J.fizi = const_cast<uint64_t *>(masks) + (size_t)f0 * (px / 64);
         SpanJobs S = span_jobs(J, k, arrived, t);
-        if (!masks)
-            S.fizi_words = 0;
         S.make_yref = reset && f0 == 0;
         FIZI_HIP(launch_gain_span(d_tab, S, s));
-        FIZI_HIP(launch_minmax(d_tab, k, m.bgmin, m.bgmax, (int)px, (reset && f0 == 0) ? 1 : 0, masks != nullptr,
-                               n_cu, s, clk ? clk->next(FIZI_STAGE_LEARN) : StageEvents{}));
+        const LearnSpan L{J.frame, px * 3, masks ? masks + (size_t)f0 * (px / 64) : nullptr, m.bgmin, m.bgmax,
+                          (uint32_t)px, k, (reset && f0 == 0) ? 1 : 0};
+        FIZI_HIP(launch_minmax(d_tab, L, s, clk ? clk->next(FIZI_STAGE_LEARN) : StageEvents{}));
     }
     m.learned = true;
     return FIZI_OK;

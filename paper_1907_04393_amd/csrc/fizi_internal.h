@@ -199,7 +199,7 @@ struct StageEvents {
 // lines cost 6 us over 64 frames)
 constexpr int kArrivedStride = 32;
 struct SpanJobs {
-    const Job *base;                    // null when learning: no kernel but minmax follows
+    const Job *base;                    // null when learning: no table is written
     const uint8_t *frame;
     size_t frame_bytes;
     uint64_t *raw, *fizi, *hand;        // hand null: none
@@ -218,14 +218,24 @@ struct SpanJobs {
     HueTest hue;
 };
 
+// Consecutive frames that widen a model; their inverse gains lie in a table
+// (k_gain_span). masks: null, or each frame's pixels to keep out.
+struct LearnSpan {
+    const uint8_t *frames;
+    size_t frame_bytes;
+    const uint64_t *masks;
+    uint8_t *bgmin, *bgmax;
+    uint32_t npx;
+    int32_t n, reset;
+};
+
 // Kernel launchers (fizi_kernels.hip). Each returns the hipError_t of its launch.
 hipError_t launch_gain(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                        hipStream_t s, StageEvents ev = {});
 hipError_t launch_put_job(Job *d_job, const Job &J, hipStream_t s);
 // Gain of a span's frames; builds its table.
 hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, StageEvents ev = {});
-hipError_t launch_minmax(const Table *d_tab, int njobs, uint8_t *bgmin, uint8_t *bgmax,
-                         int npx, int reset, bool masked, int n_cu, hipStream_t s, StageEvents ev = {});
+hipError_t launch_minmax(const Table *d_tab, const LearnSpan &S, hipStream_t s, StageEvents ev = {});
 hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                            hipStream_t s, StageEvents ev = {});
 hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s,

@@ -35,6 +35,7 @@ constexpr int kWave = 64;
 
 #define GLOBAL __attribute__((address_space(1)))
 
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Pointers in the job table are generic; casting them to the global address
@@ -43,6 +44,16 @@ template <typename T>
 __device__ __forceinline__ GLOBAL T *G(T *p)
 {
     return (GLOBAL T *)p;
+}
+
+// A byte offset within a frame's arrays (3 p < 2^28: frames are at most 8192 x
+// 8192) is added to each array's wave-uniform base as an unsigned 32-bit
+// value, so that the loads take the scalar-base, vector-offset form and no
+// 64-bit address is formed per lane.
+template <typename T>
+__device__ __forceinline__ const GLOBAL T *at_byte(const GLOBAL T *base, uint32_t off)
+{
+    return reinterpret_cast<const GLOBAL T *>(reinterpret_cast<const GLOBAL uint8_t *>(base) + off);
 }
 
 // A frame's union-find forest is only touched by one workgroup per kernel,
@@ -117,11 +128,13 @@ __device__ __forceinline__ int find_job(const int32_t *pre, int nj, int t)
 // Brightness correction of one channel value (Q16 inverse gain, half up,
 // saturated). v < 2^8 and inv <= 2^20 both fit 24 bits, so the full-rate
 // 24-bit multiply gives the exact product (< 2^28).
-__device__ __forceinline__ uint32_t corr(uint32_t v, uint32_t inv)
+__device__ __forceinline__ uint32_t corrected(uint32_t product)
 {
-    uint32_t t = (__umul24(v, inv) + 32768u) >> 16;
+    const uint32_t t = (product + 32768u) >> 16;
     return t < 255u ? t : 255u;
 }
+
+__device__ __forceinline__ uint32_t corr(uint32_t v, uint32_t inv) { return corrected(__umul24(v, inv)); }
 
 // Q16 inverse gain from the sums of reference and frame luminance: rounded
 // half up and clamped; 1.0 when no sampled pixel was usable.
@@ -194,12 +207,11 @@ __device__ __forceinline__ uint32_t frame_gain(const Job *J)
     return g & kGainKnown ? g & ~kGainKnown : wave_job_gain(J);
 }
 
-// Inverse gains of jobs [j0, j0 + n) of a span into s_inv (the whole
-// workgroup; it synchronises afterwards).
-__device__ __forceinline__ void span_gains(const Table *T, int j0, int n, uint32_t *s_inv)
+// The inverse gain of a span's job j0 + threadIdx.x (n of them, at most one
+// per thread), loaded ahead of the frames so that it waits for none of them.
+__device__ __forceinline__ uint32_t span_gain(const Table *T, int j0, int n)
 {
-    for (int j = threadIdx.x; j < n; j += blockDim.x)
-        s_inv[j] = T->jobs[j0 + j].ginv & ~kGainKnown;
+    return G(&T->jobs[j0 + min((int)threadIdx.x, n - 1)].ginv)[0] & ~kGainKnown;
 }
 
 // Skin-hue membership without division; see HueTest. Chroma > 0 is checked
@@ -512,15 +524,6 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
 {
     Job *J = &T->jobs[i];
     const Job *B = S.base;
-    const uint8_t *frame = S.frame + (size_t)i * S.frame_bytes;
-    uint64_t *fizi = S.fizi + (size_t)i * S.fizi_words;
-    if (!B) {
-        J->frame = frame;
-        J->fizi = fizi;
-        J->glo = S.glo;
-        J->ghi = S.ghi;
-        return;
-    }
     // every field but the gain sums, which other workgroups are writing
     const uint64_t *src = reinterpret_cast<const uint64_t *>(B);
     uint64_t *dst = reinterpret_cast<uint64_t *>(J);
@@ -536,9 +539,9 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     auto moved = [&](auto *p, size_t bytes) {
         return reinterpret_cast<decltype(p)>(reinterpret_cast<uint8_t *>(p) + bytes);
     };
-    head.frame = frame;
+    head.frame = S.frame + (size_t)i * S.frame_bytes;
     head.raw = moved(S.raw, (size_t)i * S.raw_bytes);
-    head.fizi = fizi;
+    head.fizi = S.fizi + (size_t)i * S.fizi_words;
     head.hand = S.hand ? S.hand + (size_t)i * S.hand_words : nullptr;
     head.parent = moved(head.parent, so);
     head.area = moved(head.area, so);
@@ -666,64 +669,110 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
 }
 
 // ---------------------------------------------------------------------------
-// MASKED: partial re-learning, each job's I_FIZI bits keep its pixels out.
+// Learning: every frame widens the model. The correction is monotone, so the
+// least and greatest corrected value of a channel are the corrections of the
+// least and greatest v inv: per frame and channel only the product is taken
+// (its byte selected by the multiply itself) and half a three-way minimum and
+// maximum (frames in pairs); rounding, shift and saturation come once at the
+// end. 2 instructions per channel and frame where correcting first took 6.
+// MASKED: partial re-learning, each frame's I_FIZI bits keep its pixels out;
+// waves without such pixels take the plain code.
+// Bound by HBM: 50 frames of 1920x1080 (323 MB) in 51 us, 6.3 TB/s (64 us
+// with every value corrected); 8 frames with masks on top of a model 12-15 us
+// (20).
+constexpr int kLearnAhead = 4;         // frames in flight per lane (two pairs)
+
 template <bool MASKED>
-__global__ __launch_bounds__(256) void k_minmax(Table *__restrict__ T, int nj,
-                                                uint8_t *__restrict__ bgmin,
-                                                uint8_t *__restrict__ bgmax, int npx, int reset)
+__global__ __launch_bounds__(256) void k_minmax(const Table *__restrict__ T, const LearnSpan S)
 {
     __shared__ uint32_t s_inv[kMaxJobs];
-    span_gains(T, 0, nj, s_inv);
+    const GLOBAL uint8_t *frames = G(S.frames), *masks = G(reinterpret_cast<const uint8_t *>(S.masks));
+    const int last = S.n - 1;
+    static_assert(kMaxJobs <= 256, "one inverse gain per thread");
+    const uint32_t gain = span_gain(T, 0, S.n);
+    // lanes past the end repeat the last group and store nothing
+    const uint32_t ngroups = S.npx / 4u, g = min(blockIdx.x * blockDim.x + threadIdx.x, ngroups - 1u);
+    auto load = [&](int f) __attribute__((always_inline)) {
+        return __builtin_nontemporal_load(
+            at_byte(reinterpret_cast<const GLOBAL u32x3 *>(frames + (size_t)f * S.frame_bytes), 12u * g));
+    };
+    // the lane's 4 mask bits of a frame
+    auto skip_of = [&](int f) __attribute__((always_inline)) {
+        return MASKED ? ((uint32_t)(masks + (size_t)f * (S.npx / 8u))[g >> 1] >> ((g & 1u) * 4u)) & 0xFu : 0u;
+    };
+    u32x3 ring[kLearnAhead];
+    uint32_t skip[kLearnAhead];
+#pragma unroll
+    for (int q = 0; q < kLearnAhead; ++q) {
+        ring[q] = load(min(q, last));
+        skip[q] = skip_of(min(q, last));
+    }
+    if ((int)threadIdx.x < S.n)
+        s_inv[threadIdx.x] = gain;
     __syncthreads();
-    const int ngroups = npx / 4;
-    for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ngroups; g += gridDim.x * blockDim.x) {
-        GLOBAL uint32_t *pmin = G(reinterpret_cast<uint32_t *>(bgmin)) + 3 * g;
-        GLOBAL uint32_t *pmax = G(reinterpret_cast<uint32_t *>(bgmax)) + 3 * g;
-        uint32_t lo[12], hi[12];
-        if (reset) {
+    uint32_t lo[12], hi[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        lo[i] = 0x0FFFFFFFu;        // corrects to 255
+        hi[i] = 0u;
+    }
+    // a pair of frames: f and the next one, or f twice when it is the last
+    auto widen = [&](int f, const u32x3 w0, const u32x3 w1, uint32_t skip0, uint32_t skip1)
+                     __attribute__((always_inline)) {
+        const uint32_t i0 = s_inv[f], i1 = s_inv[min(f + 1, last)];
+        if (MASKED && __builtin_amdgcn_ballot_w64((skip0 | skip1) != 0u)) {
 #pragma unroll
             for (int i = 0; i < 12; ++i) {
-                lo[i] = 255u;
-                hi[i] = 0u;
+                const uint32_t x0 = __umul24(byte_of(w0.x, w0.y, w0.z, i), i0),
+                               x1 = __umul24(byte_of(w1.x, w1.y, w1.z, i), i1);
+                const bool u0 = !((skip0 >> (i / 3)) & 1u), u1 = !((skip1 >> (i / 3)) & 1u);
+                lo[i] = min(min(lo[i], u0 ? x0 : ~0u), u1 ? x1 : ~0u);
+                hi[i] = max(max(hi[i], u0 ? x0 : 0u), u1 ? x1 : 0u);
             }
         } else {
-            const uint32_t a0 = pmin[0], a1 = pmin[1], a2 = pmin[2];
-            const uint32_t b0 = pmax[0], b1 = pmax[1], b2 = pmax[2];
 #pragma unroll
             for (int i = 0; i < 12; ++i) {
-                lo[i] = byte_of(a0, a1, a2, i);
-                hi[i] = byte_of(b0, b1, b2, i);
+                const uint32_t x0 = __umul24(byte_of(w0.x, w0.y, w0.z, i), i0),
+                               x1 = __umul24(byte_of(w1.x, w1.y, w1.z, i), i1);
+                lo[i] = min(min(lo[i], x0), x1);
+                hi[i] = max(max(hi[i], x0), x1);
             }
         }
-        for (int j = 0; j < nj; ++j) {
-            const GLOBAL uint32_t *f = G(reinterpret_cast<const uint32_t *>(T->jobs[j].frame)) + 3 * g;
-            const uint32_t inv = s_inv[j];
-            const uint32_t w0 = __builtin_nontemporal_load(f), w1 = __builtin_nontemporal_load(f + 1),
-                           w2 = __builtin_nontemporal_load(f + 2);
-            // partial re-learning: the frame's I_FIZI (bit set = not background)
-            // excludes its pixels; plain learning has no mask
-            const uint32_t skip =
-                MASKED ? (uint32_t)(G(T->jobs[j].fizi)[g >> 4] >> ((g & 15) << 2)) & 0xFu : 0u;
+    };
+    // the loads of the loop are unconditional (past the end the last frame
+    // again): a branch around them would make every wait one for all of them
+    int f = 0;
+    for (; f + kLearnAhead < S.n; f += kLearnAhead) {
 #pragma unroll
-            for (int i = 0; i < 12; ++i) {
-                const uint32_t v = corr(byte_of(w0, w1, w2, i), inv);
-                const bool use = !MASKED || !((skip >> (i / 3)) & 1u);
-                lo[i] = use ? min(lo[i], v) : lo[i];
-                hi[i] = use ? max(hi[i], v) : hi[i];
+        for (int q = 0; q < kLearnAhead; q += 2) {
+            widen(f + q, ring[q], ring[q + 1], skip[q], skip[q + 1]);
+#pragma unroll
+            for (int r = q; r < q + 2; ++r) {
+                ring[r] = load(min(f + r + kLearnAhead, last));
+                skip[r] = skip_of(min(f + r + kLearnAhead, last));
             }
         }
-        uint32_t a[3] = {0, 0, 0}, b[3] = {0, 0, 0};
+    }
 #pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            a[i >> 2] |= lo[i] << (8 * (i & 3));
-            b[i >> 2] |= hi[i] << (8 * (i & 3));
-        }
-        pmin[0] = a[0];
-        pmin[1] = a[1];
-        pmin[2] = a[2];
-        pmax[0] = b[0];
-        pmax[1] = b[1];
-        pmax[2] = b[2];
+    for (int q = 0; q < kLearnAhead; q += 2)
+        if (f + q < S.n)
+            widen(f + q, ring[q], ring[q + 1], skip[q], skip[q + 1]);
+    GLOBAL u32x3 *pmin = reinterpret_cast<GLOBAL u32x3 *>(G(S.bgmin) + 12u * (size_t)g);
+    GLOBAL u32x3 *pmax = reinterpret_cast<GLOBAL u32x3 *>(G(S.bgmax) + 12u * (size_t)g);
+    u32x3 a = {~0u, ~0u, ~0u}, b = {0u, 0u, 0u};
+    if (!S.reset) {
+        a = *pmin;
+        b = *pmax;
+    }
+    uint32_t ra[3] = {0, 0, 0}, rb[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        ra[i >> 2] |= min(byte_of(a.x, a.y, a.z, i), corrected(lo[i])) << (8 * (i & 3));
+        rb[i >> 2] |= max(byte_of(b.x, b.y, b.z, i), corrected(hi[i])) << (8 * (i & 3));
+    }
+    if (blockIdx.x * blockDim.x + threadIdx.x < ngroups) {
+        *pmin = u32x3{ra[0], ra[1], ra[2]};
+        *pmax = u32x3{rb[0], rb[1], rb[2]};
     }
 }
 
@@ -795,18 +844,6 @@ __device__ __forceinline__ bool not_gray(const C &c, int mx, int mn)
 struct Px4 {
     uint32_t f[3], l[3], u[3];
 };
-
-// The byte offset (3 p < 2^28: frames are at most 8192 x 8192) is
-// added to each array's wave-uniform base as an unsigned 32-bit value, so
-// that the loads take the scalar-base, vector-offset form and no 64-bit
-// address is formed per lane.
-template <typename T>
-__device__ __forceinline__ const GLOBAL T *at_byte(const GLOBAL T *base, uint32_t off)
-{
-    return reinterpret_cast<const GLOBAL T *>(reinterpret_cast<const GLOBAL uint8_t *>(base) + off);
-}
-
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 
 __device__ __forceinline__ void load_px4(const ClsJob &c, uint32_t p, uint32_t pend, Px4 &x)
 {
@@ -997,9 +1034,8 @@ __global__ __launch_bounds__(256) void k_classify(Table *__restrict__ T)
 // against Hi - Lo per channel. A frame on its own (k_classify) also takes the
 // whole unpacking of the model: 29 instructions per pixel in all, against 9
 // here plus the box (170 per lane) and the pixels outside it.
-// Bound by HBM and the VALU together: 64 frames of 1920x1080 (398 MB) take 92
-// us (174 us frame by frame), moving 4.9 TB/s with the VALU two thirds busy;
-// without the pixels outside the box it would take 78 us.
+// Bound by HBM and the VALU together: 64 frames of 1920x1080 (398 MB) take 78
+// us (174 us frame by frame), moving 5.6 TB/s with the VALU two thirds busy.
 struct Box4 {
     uint32_t a[12];            // (32768 or 0) - Lo, wrapping
     uint32_t r[12];            // Hi - Lo
@@ -1077,6 +1113,7 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int f0 = (int)blockIdx.y * per, nf = min(per, F.n - f0);
+    const uint32_t gain = span_gain(T, f0, nf);
     const uint32_t base = blockIdx.x * 1024u + (uint32_t)wave * 256u;
     const uint32_t p = base + 4u * (uint32_t)lane;
     // lanes past the frame's end read its last pixels and never test as outside
@@ -1094,28 +1131,36 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
 #pragma unroll
     for (int q = 0; q < kSpanAhead; ++q)
         ring[q] = load(min(q, nf - 1));
-    span_gains(T, f0, nf, s_inv);
+    if ((int)threadIdx.x < nf)
+        s_inv[threadIdx.x] = gain;
     __syncthreads();
     Box4 box;
     box_of<KIND>(F, l, u, p < F.npx, box);
     const uint32_t word = (base >> 6) + (uint32_t)(lane >> 4);
     const bool store = (lane & 15) == 0 && word < (F.npx >> 6);
     GLOBAL uint64_t *raw = G(F.raw) + (size_t)f0 * F.raw_words;
-    for (int f = 0; f < nf; f += kSpanAhead) {
+    auto test = [&](int f, const u32x3 w) __attribute__((always_inline)) {
+        const uint32_t bits = span_bits<KIND>(F, box, w, s_inv[f]);
+        uint64_t m = 0;
+        if (__builtin_amdgcn_ballot_w64(bits != 0u))
+            m = row_word(bits);
+        if (store)
+            (raw + (size_t)f * F.raw_words)[word] = m;
+    };
+    // the loads of the loop are unconditional (past the end the last frame
+    // again): a branch around them would make every wait one for all of them
+    int f = 0;
+    for (; f + kSpanAhead < nf; f += kSpanAhead) {
 #pragma unroll
         for (int q = 0; q < kSpanAhead; ++q) {
-            if (f + q < nf) {
-                const uint32_t bits = span_bits<KIND>(F, box, ring[q], s_inv[f + q]);
-                if (f + q + kSpanAhead < nf)
-                    ring[q] = load(f + q + kSpanAhead);
-                uint64_t w = 0;
-                if (__builtin_amdgcn_ballot_w64(bits != 0u))
-                    w = row_word(bits);
-                if (store)
-                    (raw + (size_t)(f + q) * F.raw_words)[word] = w;
-            }
+            test(f + q, ring[q]);
+            ring[q] = load(min(f + q + kSpanAhead, nf - 1));
         }
     }
+#pragma unroll
+    for (int q = 0; q < kSpanAhead; ++q)
+        if (f + q < nf)
+            test(f + q, ring[q]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2624,7 +2669,7 @@ hipError_t launch_gain_span_mode(Table *tab, const SpanJobs &S, hipStream_t s, S
     const int parts = std::max(1, std::min(kGainSlots, (waves_f + 3) / 4));
     const int most = std::min(16, (waves_f + parts - 1) / parts), rounds = (full + parts * most - 1) / (parts * most);
     const int threads = kWave * ((full + parts * rounds - 1) / (parts * rounds));
-    const dim3 grid((unsigned)parts, (unsigned)S.n + 1);
+    const dim3 grid((unsigned)parts, (unsigned)S.n + (S.base ? 1u : 0u));
     if (S.make_yref) {
         if (wide)
             FIZI_LAUNCH((k_gain_span<MODE, true, true>), grid, threads, 0, s, ev, tab, S);
@@ -2657,17 +2702,13 @@ hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, Stag
     }
 }
 
-hipError_t launch_minmax(const Table *d_tab, int njobs, uint8_t *bgmin, uint8_t *bgmax, int npx,
-                         int reset, bool masked, int n_cu, hipStream_t s, StageEvents ev)
+hipError_t launch_minmax(const Table *d_tab, const LearnSpan &S, hipStream_t s, StageEvents ev)
 {
-    const int groups = npx / 4;
-    const int grid = min((groups + 255) / 256, n_cu * 8);
-    if (masked)
-        FIZI_LAUNCH(k_minmax<true>, grid, 256, 0, s, ev, const_cast<Table *>(d_tab), njobs, bgmin, bgmax, npx,
-                    reset);
+    const int grid = (int)((S.npx / 4u + 255u) / 256u);
+    if (S.masks)
+        FIZI_LAUNCH(k_minmax<true>, grid, 256, 0, s, ev, d_tab, S);
     else
-        FIZI_LAUNCH(k_minmax<false>, grid, 256, 0, s, ev, const_cast<Table *>(d_tab), njobs, bgmin, bgmax, npx,
-                    reset);
+        FIZI_LAUNCH(k_minmax<false>, grid, 256, 0, s, ev, d_tab, S);
     return hipGetLastError();
 }
 
@@ -2689,9 +2730,9 @@ hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const 
 
 // Frames of one span workgroup: 16, so that a pixel's box is unpacked once
 // for 16 frames, unless that leaves fewer workgroups than about one resident
-// round (seven 256-thread workgroups per CU): then 8, or 4. Measured for 64
-// frames of 1920x1080 with 4 / 8 / 16 / 32 / 64 frames: 124 / 98 / 92 / 98 /
-// 118 us; for 16 frames of 1280x720 (900 tiles) with 8 / 16: 17 / 21 us.
+// round (seven 256-thread workgroups per CU): then 8, or 4. Measured (when
+// 16 took 92 us) for 64 frames of 1920x1080 with 4 / 8 / 16 / 32 / 64 frames:
+// 124 / 98 / 92 / 98 / 118 us; for 16 frames of 1280x720 (900 tiles) with 8 / 16: 17 / 21 us.
 hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &J, int n_cu, hipStream_t s,
                                 StageEvents ev)
 {
