@@ -237,7 +237,7 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
         if (e == hipSuccess) {
             // what every job of this context has in common
             Job J;
-            fill_job(c->m, c->tune.morph_rows, J);
+            fill_job(c->m, c->tune.morph_rows, J, false);
             set_scratch(J, slot_at(*geom, c->d + L.slots));
             e = launch_put_job(reinterpret_cast<Job *>(c->d + L.base), J, static_cast<hipStream_t>(stream));
             if (e == hipSuccess)
@@ -327,10 +327,8 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
             c->tune.short_bands && (size_t)k * ((H + kShortBand - 1) / kShortBand) <= (size_t)c->n_cu * 4;
         // the launch's first job, and the strides to the next ones
         Job J;
-        if (short_chain)
-            fill_job(c->m, kShortBand, J, false);
-        else
-            fill_job(c->m, c->tune.morph_rows, J);
+        fill_job(c->m, short_chain ? kShortBand : c->tune.morph_rows, J,
+                 !short_chain && morph_in_regs(c->tune.morph_rows, (int)(W / 64), morph_ops(c->m.p)));
         set_scratch(J, slot_at(c->m.g, c->d + c->L.slots));
         if (pipelined && par)
             J.raw = reinterpret_cast<uint64_t *>(c->d + c->L.raw2);

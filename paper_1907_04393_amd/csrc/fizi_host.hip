@@ -223,10 +223,9 @@ void fill_job(const Model &m, int band, Job &J, bool pack)
     J.Wd = m.g.width / 64;
     J.rs = m.p.gain_row_stride;
     J.band = band;
-    // narrow frames under the default opening and closing share a wave
-    // between bands: 4 bands of at most 16 words, or 2 of at most 32
-    const bool packable = pack && m.p.open_iters == 1 && m.p.close_iters == 1;
-    J.mgroup = !packable ? 64 : (J.Wd <= 16 ? 16 : (J.Wd <= 32 ? 32 : 64));
+    // narrow frames share a wave between bands: 4 bands of at most 16 words,
+    // or 2 of at most 32
+    J.mgroup = !pack ? 64 : (J.Wd <= 16 ? 16 : (J.Wd <= 32 ? 32 : 64));
     J.delta = m.p.bg_delta;
     J.S1 = std::max(m.p.gray_S, 1);
     J.open_it = m.p.open_iters;
@@ -464,7 +463,7 @@ int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, cons
     for (int f0 = 0; f0 < n; f0 += kMaxJobs) {
         const int k = std::min(kMaxJobs, n - f0);
         Job J;
-        fill_job(m, t.morph_rows, J);
+        fill_job(m, t.morph_rows, J, false);
         J.frame = frames + (size_t)f0 * px * 3;
         SpanJobs S = span_jobs(J, k, arrived, t);
         S.make_yref = reset && f0 == 0;

@@ -27,6 +27,7 @@ constexpr uint16_t kYrefClipped = 0xFFFFu;
 constexpr int kMaxMorphIters = 3;      // open_iters, close_iters <= 3
 constexpr int kGainSlots = 32;         // gain sums are spread over 32 accumulators
 constexpr int kGainRows = 4;           // sampled rows per gain tile
+constexpr int kShortBand = 4;          // morphology band height of launches too small to fill the device
 
 // Skin-hue test on one RGB triple, without division (Section 3.1 (iii)).
 // For a hue a, let d_a be an RGB colour of hue a. The determinant
@@ -159,6 +160,17 @@ struct Tuning {
     int grid_per_cu;    // resident blocks per CU for the streaming kernels
     int short_bands = 1;   // launches too small to fill the device take short morphology bands
 };
+
+// Whether the morphology of a launch (tuned band height, widest frame in
+// words, most stages of a job) holds its bands in registers with their halo:
+// bands of 8 or 16 rows, and of the short height in such a launch, but frames
+// of more than 64 words only with the default four stages. Other launches
+// stream their bands. Only bands in registers share a wave on narrow frames.
+inline bool morph_in_regs(int morph_rows, int max_wd, int max_ops)
+{
+    const bool wide = max_wd > 64, deep = max_ops > 4;
+    return (morph_rows == 8 || morph_rows == 16) && !(wide && deep);
+}
 
 inline int cls_tile_px(const Tuning &t) { return 1024 * t.cls_iters; }
 

@@ -1332,6 +1332,10 @@ struct WaveLds {
     uint32_t start[kSegRuns];              // first pixel of segment run k
     uint32_t end[kSegRuns];                // its last pixel, | kLinkUp if flagged
     uint32_t par[kSegRuns];                // union-find parent (segment index)
+    // touching pairs still to unite, run | run << 16: at most one per run of
+    // the segment (each belongs to the start of a run of the upper row)
+    uint32_t pairs[kSegRuns];
+    uint32_t npairs;
 };
 
 __device__ __forceinline__ void wave_sync()
@@ -1367,22 +1371,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
     return v;
 }
 
-// Lanes per row: LG lanes hold one row (LG = 64: the whole wave; LG = 16 or
-// 32 pack 64 / LG bands of a narrow frame into one wave, lane group g holding
-// band g's row). The word a lane holds, and its group:
-template <int LG>
-__device__ __forceinline__ int lane_word() { return (int)(threadIdx.x & (uint32_t)(LG - 1)); }
-template <int LG>
-__device__ __forceinline__ int lane_group() { return LG == kWave ? 0 : (int)((threadIdx.x & (kWave - 1)) / LG); }
+// Lanes per row: lg lanes hold one row (64: the whole wave; 16 or 32 pack 64 /
+// lg bands of a narrow frame into one wave, lane group g holding band g's
+// row). The word a lane holds, and its group:
+__device__ __forceinline__ int lane_word(int lg) { return (int)(threadIdx.x & (uint32_t)(lg - 1)); }
+__device__ __forceinline__ int lane_group(int lg) { return (int)((threadIdx.x & (kWave - 1)) >> (31 - __builtin_clz(lg))); }
 
 // Edge bits of the neighbouring words of this lane's NC words (word
 // w + 64 q of the lane group's row): bit 63 of the word on the left (lc) and
 // bit 0 of the word on the right (rc); words outside [0, Wd) give `edge`.
-template <int NC, int LG = kWave>
-__device__ __forceinline__ void row_carries(const uint64_t *v, int Wd, uint32_t edge, uint32_t *lc, uint32_t *rc)
+template <int NC>
+__device__ __forceinline__ void row_carries(const uint64_t *v, int Wd, uint32_t edge, uint32_t *lc, uint32_t *rc,
+                                            int lg = kWave)
 {
-    static_assert(NC == 1 || LG == kWave, "lane groups hold one word per lane");
-    const int lane = lane_word<LG>();
+    const int lane = lane_word(lg);            // lane groups (lg < 64) hold one word per lane
     const uint32_t hi0 = (uint32_t)(v[0] >> 63), lo0 = (uint32_t)v[0] & 1u;
     const uint32_t up0 = from_left(hi0), dn0 = from_right(lo0);
     lc[0] = lane == 0 ? edge : up0;
@@ -1400,7 +1402,7 @@ __device__ __forceinline__ void row_carries(const uint64_t *v, int Wd, uint32_t 
 }
 
 // One erosion (ero) or dilation of row b given the rows above (a) and below (c).
-template <int NC, int LG = kWave>
+template <int NC>
 __device__ __forceinline__ void morph_row(bool ero, const uint64_t *a, const uint64_t *b, const uint64_t *c, int Wd,
                                           uint64_t *out)
 {
@@ -1409,7 +1411,7 @@ __device__ __forceinline__ void morph_row(bool ero, const uint64_t *a, const uin
     for (int q = 0; q < NC; ++q)
         v[q] = ero ? (a[q] & b[q] & c[q]) : (a[q] | b[q] | c[q]);
     uint32_t lc[NC], rc[NC];
-    row_carries<NC, LG>(v, Wd, ero ? 1u : 0u, lc, rc);
+    row_carries<NC>(v, Wd, ero ? 1u : 0u, lc, rc);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
         const uint64_t left = (v[q] << 1) | lc[q];
@@ -1492,11 +1494,11 @@ struct RowBits {
 // Fills r from the row x; en receives the run ends. Returns the row's runs
 // (of every lane group: runs are numbered across the wave). r.last holds
 // wave positions 64 lane + bit, which grow across the groups.
-template <int NC, int LG = kWave>
-__device__ __forceinline__ uint32_t row_bits(RowBits<NC> &r, const uint64_t *x, int Wd, uint64_t *en)
+template <int NC>
+__device__ __forceinline__ uint32_t row_bits(RowBits<NC> &r, const uint64_t *x, int Wd, uint64_t *en, int lg)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    row_carries<NC, LG>(x, Wd, 0u, r.lc, r.rc);
+    row_carries<NC>(x, Wd, 0u, r.lc, r.rc, lg);
     uint32_t total = 0;
     int before = -1;
 #pragma unroll
@@ -1519,11 +1521,11 @@ __device__ __forceinline__ uint32_t row_bits(RowBits<NC> &r, const uint64_t *x, 
 // x of the first pixel of the run that contains bit t (set, t in [-1, 64])
 // around word c of the row. A run never crosses a lane group (its edges are
 // out-of-image), so a start before the word lies in the same group.
-template <int NC, int LG = kWave>
-__device__ __forceinline__ int start_at(const RowBits<NC> &r, int c, int t)
+template <int NC>
+__device__ __forceinline__ int start_at(const RowBits<NC> &r, int c, int t, int lg)
 {
-    const int wb = 64 * (lane_word<LG>() + kWave * c);
-    const int gofs = 64 * LG * lane_group<LG>();
+    const int wb = 64 * (lane_word(lg) + kWave * c);
+    const int gofs = 64 * lg * lane_group(lg);
     if (t < 0)
         return r.last[c] - gofs;
     uint64_t m;
@@ -1537,64 +1539,51 @@ __device__ __forceinline__ int start_at(const RowBits<NC> &r, int c, int t)
     return m ? wb + 63 - __builtin_clzll(m) : r.last[c] - gofs;
 }
 
-// Every touching pair of runs of two consecutive rows U (above) and D
-// (below), each once, from the lanes' words. Under 8-connectivity a U run
-// [us, ue] and a D run [ds, de] touch when us <= de + 1 and ue >= ds - 1.
-// When us <= ds + 1, U has a pixel in columns ds - 1 .. ds + 1, and D's start
-// meets it there (the pixel at ds, else those beside it). Otherwise
-// us >= ds + 2, so D holds columns us - 2 and us - 1, and U's start meets the
-// D run there. f(c, from_d, b, t): the run starting at bit b of word c of D
-// (from_d) or U touches the run of the other row that contains bit t.
-// ONCE = false: U's starts look at the one to three pixels below them as D's
-// do above, so most pairs come twice (the band-border joins keep that form:
-// the component stage unites them concurrently, and the second meeting of a
-// pair shortens the chains the first one built).
-template <int NC, bool ONCE, typename F>
+// Touching pairs of runs of two consecutive rows U (above) and D (below), from
+// the lanes' words. Under 8-connectivity a U run [us, ue] and a D run [ds, de]
+// touch when us <= de + 1 and ue >= ds - 1. When us <= ds + 1, U has a pixel
+// in columns ds - 1 .. ds + 1, and D's start meets it there (the pixel at ds,
+// else those beside it). Otherwise us >= ds + 2, so D holds columns us - 2 and
+// us - 1, and U's start meets the D run there: each pair is met once.
+// Whether D holds the two columns left of bit b of word c (for b = 0: its run
+// through the word's left edge started at least two columns before it).
+template <int NC>
+__device__ __forceinline__ bool holds_left2(const RowBits<NC> &D, int c, int b)
+{
+    if (b >= 2)
+        return ((D.w[c] >> (b - 2)) & 3ull) == 3ull;
+    if (b == 1)
+        return (D.lc[c] & (uint32_t)D.w[c] & 1u) != 0u;
+    return D.lc[c] != 0u && D.last[c] < 64 * ((int)(threadIdx.x & (kWave - 1)) + kWave * c) - 1;
+}
+
+// The same pairs with U's starts looking at the one to three pixels below
+// them as D's do above, so that most come twice: f(c, from_d, b, t), the run
+// starting at bit b of word c of D (from_d) or U touches the run of the other
+// row that contains bit t. The band-border joins keep this form: the component
+// stage unites them concurrently, and the second meeting of a pair shortens
+// the chains the first one built.
+template <int NC, typename F>
 __device__ __forceinline__ void touching_runs(const RowBits<NC> &U, const RowBits<NC> &D, F f)
 {
-    const int lane = threadIdx.x & (kWave - 1);
+    auto look = [&](int c, bool from_d, uint64_t starts, const RowBits<NC> &O) {
+        while (starts) {
+            const int b = __builtin_ctzll(starts);
+            starts &= starts - 1;
+            if (bit_at(b, O.w[c], O.lc[c], O.rc[c])) {
+                f(c, from_d, b, b);
+            } else {
+                if (bit_at(b - 1, O.w[c], O.lc[c], O.rc[c]))
+                    f(c, from_d, b, b - 1);
+                if (bit_at(b + 1, O.w[c], O.lc[c], O.rc[c]))
+                    f(c, from_d, b, b + 1);
+            }
+        }
+    };
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        uint64_t m = D.st[c];
-        while (m) {
-            const int b = __builtin_ctzll(m);
-            m &= m - 1;
-            if (bit_at(b, U.w[c], U.lc[c], U.rc[c])) {
-                f(c, true, b, b);
-            } else {
-                if (bit_at(b - 1, U.w[c], U.lc[c], U.rc[c]))
-                    f(c, true, b, b - 1);
-                if (bit_at(b + 1, U.w[c], U.lc[c], U.rc[c]))
-                    f(c, true, b, b + 1);
-            }
-        }
-        m = U.st[c];
-        while (m) {
-            const int b = __builtin_ctzll(m);
-            m &= m - 1;
-            if (!ONCE) {
-                if (bit_at(b, D.w[c], D.lc[c], D.rc[c])) {
-                    f(c, false, b, b);
-                } else {
-                    if (bit_at(b - 1, D.w[c], D.lc[c], D.rc[c]))
-                        f(c, false, b, b - 1);
-                    if (bit_at(b + 1, D.w[c], D.lc[c], D.rc[c]))
-                        f(c, false, b, b + 1);
-                }
-                continue;
-            }
-            // D holds columns b - 2 and b - 1 (for b = 0: its run through
-            // the word's left edge started at least two columns before it)
-            bool left2;
-            if (b >= 2)
-                left2 = ((D.w[c] >> (b - 2)) & 3ull) == 3ull;
-            else if (b == 1)
-                left2 = (D.lc[c] & (uint32_t)D.w[c] & 1u) != 0u;
-            else
-                left2 = D.lc[c] != 0u && D.last[c] < 64 * (lane + kWave * c) - 1;
-            if (left2)
-                f(c, false, b, b - 1);
-        }
+        look(c, true, D.st[c], U);
+        look(c, false, U.st[c], D);
     }
 }
 
@@ -1622,6 +1611,12 @@ __device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GL
     if (n == 0)
         return;
     const uint32_t base = reserve_runs(J, n, cap);
+    const uint32_t np = L.npairs;
+    for (uint32_t i = lane; i < np; i += kWave)
+        unite_lds(L.par, L.pairs[i] & 0xFFFFu, L.pairs[i] >> 16);
+    wave_sync();
+    if (lane == 0)
+        L.npairs = 0u;
     for (uint32_t k = lane; k < n; k += kWave) {
         const uint32_t st = L.start[k];
         const uint32_t r = find_lds(L.par, k);
@@ -1634,17 +1629,16 @@ __device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GL
     wave_sync();
 }
 
-// Rows r0 .. r0 + kRawChunk - 1 of the raw mask (r0 per lane group),
-// addresses clamped to rows 0 .. H - 1 and words below Wd. Values of clamped
+// Rows r0 .. r0 + kRawChunk - 1 of the raw mask, addresses clamped to rows 0 .. H - 1 and words below Wd. Values of clamped
 // rows and words are never used (rows outside the image enter the pipeline as
 // its neutral value, words from Wd on never reach a valid word), so the loads
 // need no condition: they stay in flight while the previous chunk is
 // processed.
-template <int NC, int LG = kWave>
+template <int NC>
 __device__ __forceinline__ void load_rows(uint64_t (&dst)[kRawChunk][NC], const GLOBAL uint64_t *raw, int r0, int H,
                                           int Wd)
 {
-    const int lane = lane_word<LG>();
+    const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
     for (int qq = 0; qq < kRawChunk; ++qq) {
         const size_t ro = (size_t)min(max(r0 + qq, 0), H - 1) * Wd;
@@ -1654,31 +1648,221 @@ __device__ __forceinline__ void load_rows(uint64_t (&dst)[kRawChunk][NC], const 
     }
 }
 
-// KMAX: most opening/closing stages a job may have; NC: words per lane; FLOW:
-// inside the persistent step (stores other workgroups read in the launch);
-// OI, CI: the opening and closing iterations when fixed at compile time (the
-// stages' kinds then need no selects), -1 to read them from the job; LG:
-// lanes per row (bands band, band + 1, ... of the frame on the wave's lane
-// groups; every group steps through the same band-relative rows, so control
-// stays uniform, and rows outside the image are neutral or dropped per group).
-template <int KMAX, int NC, bool FLOW, int OI = -1, int CI = -1, int LG = kWave>
+// A band's final rows, one after the other: what a row needs of its job, and
+// the row above.
+struct BandOut {
+    Job *J;
+    int W, Wd, lg, word;
+    GLOBAL uint64_t *runs;
+    GLOBAL uint32_t *parent, *area, *linkw;
+    uint32_t cap, link_cap;
+};
+
+__device__ __forceinline__ BandOut band_out(Job *J, int lg)
+{
+    BandOut B;
+    B.J = J;
+    B.W = J->W;
+    B.Wd = J->Wd;
+    B.lg = lg;
+    B.word = lane_word(lg);
+    B.runs = G(reinterpret_cast<uint64_t *>(J->runs));
+    B.parent = G(J->parent);
+    B.area = G(J->area);
+    B.linkw = G(reinterpret_cast<uint32_t *>(J->links));
+    B.cap = J->run_cap;
+    B.link_cap = J->link_cap;
+    return B;
+}
+
+template <int NC>
+struct RunState {
+    uint32_t nseg = 0, prev_first = 0;
+    bool prev_valid = false;    // P holds the previous row and it has runs
+    bool prev_in_seg = false;   // ... in the open segment
+    RowBits<NC> P;
+
+    __device__ __forceinline__ RunState()
+    {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            P.w[c] = P.st[c] = 0ull;
+            P.lc[c] = P.rc[c] = P.ex[c] = 0u;
+            P.last[c] = -1;
+        }
+    }
+};
+
+// The last row of the band above, only to join with.
+template <int NC>
+__device__ __forceinline__ void halo_row(const BandOut &B, RunState<NC> &S, const uint64_t *x)
+{
+    uint64_t en[NC];
+    (void)row_bits<NC>(S.P, x, B.Wd, en, B.lg);
+    S.prev_valid = true;
+    S.prev_in_seg = false;
+}
+
+// A final I_FIZI row with pixels (jrow per lane group): its runs and their
+// joins with the row above.
+template <int NC, bool FLOW>
+__device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveLds &L, const uint64_t *x, int jrow)
+{
+    Job *J = B.J;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int W = B.W, Wd = B.Wd, word = B.word;
+    GLOBAL uint64_t *runs = B.runs;
+    GLOBAL uint32_t *parent = B.parent, *area = B.area, *linkw = B.linkw;
+    const uint32_t cap = B.cap, link_cap = B.link_cap;
+    RowBits<NC> &P = S.P;
+    uint32_t &nseg = S.nseg, &prev_first = S.prev_first;
+    bool &prev_valid = S.prev_valid, &prev_in_seg = S.prev_in_seg;
+    RowBits<NC> D;
+    uint64_t en[NC];
+    const uint32_t total = row_bits<NC>(D, x, Wd, en, B.lg);
+    if (nseg + total > (uint32_t)kSegRuns) {
+        // the open segment is full: close it, this row opens the next
+        flush_segment<FLOW>(J, L, nseg, runs, parent, area, cap);
+        nseg = 0;
+        prev_in_seg = false;
+    }
+    const bool direct = total > (uint32_t)kSegRuns;
+    const uint32_t rowpx = (uint32_t)max(jrow, 0) * (uint32_t)W;
+    // joins with a row above whose runs are not in the open segment (the
+    // band above, a closed segment, or a row written directly) go to the
+    // frame's link list as pairs of run starts
+    uint32_t flag = 0u;
+    if (prev_valid && (!prev_in_seg || direct)) {
+        uint32_t cnt = 0;
+        touching_runs<NC>(P, D, [&](int, bool, int, int) { ++cnt; });
+        const uint32_t inc = wave_incl_scan(cnt);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        uint32_t base = 0;
+        if (lane == 0)
+            base = atomicAdd(&J->nlinks, n);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        uint32_t k = base + inc - cnt;
+        const uint32_t upx = rowpx - (uint32_t)W;
+        touching_runs<NC>(P, D, [&](int c, bool from_d, int b, int t) {
+            const uint32_t wb = 64u * (uint32_t)(word + kWave * c);
+            const uint32_t a = from_d ? rowpx + wb + (uint32_t)b : upx + wb + (uint32_t)b;
+            const uint32_t o = from_d ? upx + (uint32_t)start_at<NC>(P, c, t, B.lg)
+                                      : rowpx + (uint32_t)start_at<NC>(D, c, t, B.lg);
+            if (k < link_cap) {
+                put<FLOW>(linkw + 2 * (size_t)k, a);
+                put<FLOW>(linkw + 2 * (size_t)k + 1, o);
+            }
+            ++k;
+        });
+        if (base + n > link_cap) {
+            // the list is full: the component stage joins this row to
+            // the row above by reading I_FIZI
+            flag = kLinkUp;
+            if (lane == 0)
+                atomicAdd(&J->nflag, 1u);
+        }
+    }
+    const uint32_t rbase = direct ? reserve_runs(J, total, cap) : 0u;
+    GLOBAL uint32_t *runw = reinterpret_cast<GLOBAL uint32_t *>(runs);
+    // record the row's runs: the lane holding a run's first pixel writes
+    // its start, the lane holding its last pixel its end
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const uint32_t wpx = rowpx + 64u * (uint32_t)(word + kWave * c);
+        uint64_t m = D.st[c];
+        while (m) {
+            const int b = __builtin_ctzll(m);
+            const uint32_t k = D.ex[c] + (uint32_t)__popcll(D.st[c] & ((1ull << b) - 1ull));
+            m &= m - 1;
+            const uint32_t start = wpx + (uint32_t)b;
+            if (!direct) {
+                L.start[nseg + k] = start;
+                L.par[nseg + k] = nseg + k;
+            } else if (rbase + k < cap) {
+                put<FLOW>(runw + 2 * (size_t)(rbase + k), start);
+                put_parent<FLOW>(parent + start, start);
+                put<FLOW>(area + start, 0u);
+            }
+        }
+        m = en[c];
+        while (m) {
+            const int e = __builtin_ctzll(m);
+            const uint32_t k = D.ex[c] + (uint32_t)__popcll(D.st[c] & (~0ull >> (63 - e))) - 1u;
+            m &= m - 1;
+            const uint32_t end = (wpx + (uint32_t)e) | flag;
+            if (!direct)
+                L.end[nseg + k] = end;
+            else if (rbase + k < cap)
+                put<FLOW>(runw + 2 * (size_t)(rbase + k) + 1, end);
+        }
+    }
+    wave_sync();
+    // joins with the row above in the open segment: each touching pair once
+    // (see touching_runs). The first run that a run's start meets above gives
+    // it its parent, that run's own parent, so that without further pairs
+    // every run points at its root; the others are united when the segment
+    // closes, all lanes at once, instead of one row's few at a time
+    if (prev_valid && prev_in_seg && !direct) {
+        auto later = [&](uint32_t u, uint32_t d) { L.pairs[atomicAdd(&L.npairs, 1u)] = u | (d << 16); };
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            uint64_t m = D.st[c];
+            while (m) {
+                const int b = __builtin_ctzll(m);
+                m &= m - 1;
+                const uint32_t k = nseg + D.ex[c] + (uint32_t)__popcll(D.st[c] & ((1ull << b) - 1ull));
+                auto above = [&](int t) { return prev_first + run_at(t, P.ex[c], P.st[c], P.w[c], P.rc[c]); };
+                if (bit_at(b, P.w[c], P.lc[c], P.rc[c])) {
+                    L.par[k] = L.par[above(b)];
+                } else {
+                    const bool l = bit_at(b - 1, P.w[c], P.lc[c], P.rc[c]) != 0u,
+                               r = bit_at(b + 1, P.w[c], P.lc[c], P.rc[c]) != 0u;
+                    if (l | r)
+                        L.par[k] = L.par[above(l ? b - 1 : b + 1)];
+                    if (l & r)
+                        later(above(b + 1), k);
+                }
+            }
+            m = P.st[c];
+            while (m) {
+                const int b = __builtin_ctzll(m);
+                m &= m - 1;
+                if (holds_left2<NC>(D, c, b))
+                    later(prev_first + P.ex[c] + (uint32_t)__popcll(P.st[c] & ((1ull << b) - 1ull)),
+                          nseg + run_at(b - 1, D.ex[c], D.st[c], D.w[c], D.rc[c]));
+            }
+        }
+        wave_sync();
+    }
+    // this row becomes the row above
+    P = D;
+    prev_valid = true;
+    prev_in_seg = !direct;
+    if (!direct) {
+        prev_first = nseg;
+        nseg += total;
+    }
+}
+
+// A band streamed through the register pipeline: bands of any height, in the
+// persistent step and for the heights that morph_regs does not take. KMAX:
+// most opening/closing stages a job may have; NC: words per lane; FLOW: inside
+// the persistent step (stores other workgroups read in the launch); OI, CI:
+// the opening and closing iterations when fixed at compile time (the stages'
+// kinds then need no selects), -1 to read them from the job.
+template <int KMAX, int NC, bool FLOW, int OI = -1, int CI = -1>
 __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int word = lane_word<LG>();
-    const int W = J->W, H = J->H, Wd = J->Wd, R = J->band;
+    const int word = threadIdx.x & (kWave - 1);
+    const int H = J->H, Wd = J->Wd, R = J->band;
     const int oi = OI >= 0 ? OI : J->open_it, ci = CI >= 0 ? CI : J->close_it;
     const int K = 2 * (oi + ci);
-    const int y0 = (band + lane_group<LG>()) * R;
+    const int y0 = band * R;
     // one more halo row above: row y0 - 1 is computed exactly, to join the
     // band's first row to it without reading the band above
     const int ya = y0 - K - 1;
     const GLOBAL uint64_t *raw = G(J->raw);
     GLOBAL uint64_t *fz = G(J->fizi);
-    GLOBAL uint32_t *parent = G(J->parent);
-    GLOBAL uint32_t *area = G(J->area);
-    GLOBAL uint64_t *runs = G(reinterpret_cast<uint64_t *>(J->runs));
-    const uint32_t cap = J->run_cap;
     bool valid_w[NC];
 #pragma unroll
     for (int q = 0; q < NC; ++q)
@@ -1691,18 +1875,10 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
 #pragma unroll
         for (int q = 0; q < NC; ++q)
             p2[k][q] = p1[k][q] = stage_erodes(k, oi, ci) ? ~0ull : 0ull;
-    uint32_t nseg = 0, prev_first = 0;
-    bool prev_valid = false;    // P holds the previous row and it has runs
-    bool prev_in_seg = false;   // ... in the open segment
-    RowBits<NC> P;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        P.w[c] = P.st[c] = 0ull;
-        P.lc[c] = P.rc[c] = P.ex[c] = 0u;
-        P.last[c] = -1;
-    }
-    GLOBAL uint32_t *linkw = G(reinterpret_cast<uint32_t *>(J->links));
-    const uint32_t link_cap = J->link_cap;
+    const BandOut B = band_out(J, kWave);
+    RunState<NC> S;
+    L.npairs = 0u;
+    wave_sync();
     const int nsteps = R + 2 * K + 1;
     // one input row through the stages, then the band's final row it yields
     auto step = [&](int s, int q, const uint64_t (&ch)[kRawChunk][NC]) __attribute__((always_inline)) {
@@ -1725,7 +1901,7 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
                         x[c] = ero ? ~0ull : 0ull;
                 }
                 uint64_t o[NC];
-                morph_row<NC, LG>(ero, p2[k], p1[k], x, Wd, o);
+                morph_row<NC>(ero, p2[k], p1[k], x, Wd, o);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     p2[k][c] = p1[k][c];
@@ -1755,13 +1931,8 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
         }
         const bool nonempty = __ballot(orw != 0ull) != 0ull;
         if (jrel == -1) {
-            // the last row of the band above, only to join with
-            if (nonempty) {
-                uint64_t en[NC];
-                (void)row_bits<NC, LG>(P, x, Wd, en);
-            }
-            prev_valid = nonempty;
-            prev_in_seg = false;
+            if (nonempty)
+                halo_row<NC>(B, S, x);
             return;
         }
         // a final I_FIZI row
@@ -1770,128 +1941,233 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
         for (int c = 0; c < NC; ++c)
             if (valid_w[c] && row_ok)
                 put<FLOW>(frow + word + kWave * c, x[c]);
-        if (!nonempty) {
-            prev_valid = false;
-            return;
-        }
-        RowBits<NC> D;
-        uint64_t en[NC];
-        const uint32_t total = row_bits<NC, LG>(D, x, Wd, en);
-        if (nseg + total > (uint32_t)kSegRuns) {
-            // the open segment is full: close it, this row opens the next
-            flush_segment<FLOW>(J, L, nseg, runs, parent, area, cap);
-            nseg = 0;
-            prev_in_seg = false;
-        }
-        const bool direct = total > (uint32_t)kSegRuns;
-        const uint32_t rowpx = (uint32_t)max(jrow, 0) * (uint32_t)W;
-        // joins with a row above whose runs are not in the open segment (the
-        // band above, a closed segment, or a row written directly) go to the
-        // frame's link list as pairs of run starts
-        uint32_t flag = 0u;
-        if (prev_valid && (!prev_in_seg || direct)) {
-            uint32_t cnt = 0;
-            touching_runs<NC, false>(P, D, [&](int, bool, int, int) { ++cnt; });
-            const uint32_t inc = wave_incl_scan(cnt);
-            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-            uint32_t base = 0;
-            if (lane == 0)
-                base = atomicAdd(&J->nlinks, n);
-            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-            uint32_t k = base + inc - cnt;
-            const uint32_t upx = rowpx - (uint32_t)W;
-            touching_runs<NC, false>(P, D, [&](int c, bool from_d, int b, int t) {
-                const uint32_t wb = 64u * (uint32_t)(word + kWave * c);
-                const uint32_t a = from_d ? rowpx + wb + (uint32_t)b : upx + wb + (uint32_t)b;
-                const uint32_t o = from_d ? upx + (uint32_t)start_at<NC, LG>(P, c, t)
-                                          : rowpx + (uint32_t)start_at<NC, LG>(D, c, t);
-                if (k < link_cap) {
-                    put<FLOW>(linkw + 2 * (size_t)k, a);
-                    put<FLOW>(linkw + 2 * (size_t)k + 1, o);
-                }
-                ++k;
-            });
-            if (base + n > link_cap) {
-                // the list is full: the component stage joins this row to
-                // the row above by reading I_FIZI
-                flag = kLinkUp;
-                if (lane == 0)
-                    atomicAdd(&J->nflag, 1u);
-            }
-        }
-        const uint32_t rbase = direct ? reserve_runs(J, total, cap) : 0u;
-        GLOBAL uint32_t *runw = reinterpret_cast<GLOBAL uint32_t *>(runs);
-        // record the row's runs: the lane holding a run's first pixel writes
-        // its start, the lane holding its last pixel its end
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const uint32_t wpx = rowpx + 64u * (uint32_t)(word + kWave * c);
-            uint64_t m = D.st[c];
-            while (m) {
-                const int b = __builtin_ctzll(m);
-                const uint32_t k = D.ex[c] + (uint32_t)__popcll(D.st[c] & ((1ull << b) - 1ull));
-                m &= m - 1;
-                const uint32_t start = wpx + (uint32_t)b;
-                if (!direct) {
-                    L.start[nseg + k] = start;
-                    L.par[nseg + k] = nseg + k;
-                } else if (rbase + k < cap) {
-                    put<FLOW>(runw + 2 * (size_t)(rbase + k), start);
-                    put_parent<FLOW>(parent + start, start);
-                    put<FLOW>(area + start, 0u);
-                }
-            }
-            m = en[c];
-            while (m) {
-                const int e = __builtin_ctzll(m);
-                const uint32_t k = D.ex[c] + (uint32_t)__popcll(D.st[c] & (~0ull >> (63 - e))) - 1u;
-                m &= m - 1;
-                const uint32_t end = (wpx + (uint32_t)e) | flag;
-                if (!direct)
-                    L.end[nseg + k] = end;
-                else if (rbase + k < cap)
-                    put<FLOW>(runw + 2 * (size_t)(rbase + k) + 1, end);
-            }
-        }
-        wave_sync();
-        // joins with the row above in the open segment, in the LDS union-find
-        if (prev_valid && prev_in_seg && !direct) {
-            touching_runs<NC, true>(P, D, [&](int c, bool from_d, int b, int t) {
-                const uint64_t below = (1ull << b) - 1ull;
-                if (from_d)
-                    unite_lds(L.par, nseg + D.ex[c] + (uint32_t)__popcll(D.st[c] & below),
-                              prev_first + run_at(t, P.ex[c], P.st[c], P.w[c], P.rc[c]));
-                else
-                    unite_lds(L.par, prev_first + P.ex[c] + (uint32_t)__popcll(P.st[c] & below),
-                              nseg + run_at(t, D.ex[c], D.st[c], D.w[c], D.rc[c]));
-            });
-            wave_sync();
-        }
-        // this row becomes the row above
-        P = D;
-        prev_valid = true;
-        prev_in_seg = !direct;
-        if (!direct) {
-            prev_first = nseg;
-            nseg += total;
-        }
+        if (nonempty)
+            run_row<NC, FLOW>(B, S, L, x, jrow);
+        else
+            S.prev_valid = false;
     };
     // input chunks alternate between two register buffers: each is loaded a
     // chunk ahead of its use, straight into the registers that use it
     uint64_t ca[kRawChunk][NC], cb[kRawChunk][NC];
-    load_rows<NC, LG>(ca, raw, ya, H, Wd);
+    load_rows<NC>(ca, raw, ya, H, Wd);
 #pragma unroll 1
     for (int s0 = 0; s0 < nsteps; s0 += 2 * kRawChunk) {
-        load_rows<NC, LG>(cb, raw, ya + s0 + kRawChunk, H, Wd);
+        load_rows<NC>(cb, raw, ya + s0 + kRawChunk, H, Wd);
 #pragma unroll 1
         for (int q = 0; q < kRawChunk && s0 + q < nsteps; ++q)
             step(s0 + q, q, ca);
-        load_rows<NC, LG>(ca, raw, ya + s0 + 2 * kRawChunk, H, Wd);
+        load_rows<NC>(ca, raw, ya + s0 + 2 * kRawChunk, H, Wd);
 #pragma unroll 1
         for (int q = 0; q < kRawChunk && s0 + kRawChunk + q < nsteps; ++q)
             step(s0 + kRawChunk + q, q, cb);
     }
-    flush_segment<FLOW>(J, L, nseg, runs, parent, area, cap);
+    flush_segment<FLOW>(J, L, S.nseg, B.runs, B.parent, B.area, B.cap);
+}
+
+// A band of at most 16 rows, all of it in registers: the rows with their halo
+// are loaded at once and go through the stages one stage at a time, so that
+// the rows of a stage are independent of each other (the streamed form is one
+// chain of dependent steps, with selects for the image's borders in each).
+// Waves whose rows hold no three pixels above one another anywhere - the first
+// erosion leaves nothing then, and the closing nothing to close - store empty
+// rows and are done: background with noise, most bands of a frame.
+// Bound by the latency of the bands that hold the hand: 64 frames of 1920x1080
+// in 8-row bands take 25 us (35 streamed), the 64-stream batch in 16-row bands
+// 67 us (89), 16 frames of 1344x757 with two openings and closings 24 us (52),
+// a frame of 320x240 4 us (8). R: band height; KT: stages the halo has rows
+// for; NC: words per lane.
+// One stage on rows from .. to of the N in registers. edge: the band's rows
+// reach outside the image, where a stage reads its neutral value (1 for
+// erosion, 0 for dilation).
+template <bool ERO, int N, int NC>
+__device__ __forceinline__ void regs_stage(uint64_t (&x)[N][NC], int from, int to, int Wd, int lg, bool edge,
+                                           int ytop, int H)
+{
+    constexpr uint64_t neutral = ERO ? ~0ull : 0ull;
+    if (edge) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const bool out = (uint32_t)(ytop + r) >= (uint32_t)H;
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                x[r][q] = out ? neutral : x[r][q];
+        }
+    }
+    const int lane = lane_word(lg);
+    const bool first = lane == 0, last = lane + 1 >= Wd, last1 = lane + kWave + 1 >= Wd;
+    uint64_t prev[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        prev[q] = x[from - 1][q];
+#pragma unroll
+    for (int r = 1; r < N - 1; ++r) {
+        if (r < from || r > to)
+            continue;
+        uint32_t lo[NC], hi[NC], lw[NC], rw[NC];
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            const uint64_t v = ERO ? (prev[q] & x[r][q] & x[r + 1][q]) : (prev[q] | x[r][q] | x[r + 1][q]);
+            prev[q] = x[r][q];
+            lo[q] = (uint32_t)v;
+            hi[q] = (uint32_t)(v >> 32);
+        }
+        // the nearest half of the words on both sides, neutral past the row's ends
+        const uint32_t edge32 = (uint32_t)neutral;
+        const uint32_t l0 = from_left(hi[0]), r0 = from_right(lo[0]);
+        lw[0] = first ? edge32 : l0;
+        rw[0] = last ? edge32 : r0;
+        if constexpr (NC == 2) {
+            const uint32_t end0 = (uint32_t)__builtin_amdgcn_readlane((int)hi[0], kWave - 1);
+            const uint32_t beg1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo[1]);
+            const uint32_t l1 = from_left(hi[1]), r1 = from_right(lo[1]);
+            lw[1] = first ? end0 : l1;
+            rw[1] = last1 ? edge32 : r1;
+            if (lane == kWave - 1 && !last)
+                rw[0] = beg1;
+        }
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            const uint32_t ll = __builtin_amdgcn_alignbit(lo[q], lw[q], 31), lh = __builtin_amdgcn_alignbit(hi[q], lo[q], 31);
+            const uint32_t rl = __builtin_amdgcn_alignbit(hi[q], lo[q], 1), rh = __builtin_amdgcn_alignbit(rw[q], hi[q], 1);
+            const uint32_t ol = ERO ? (lo[q] & ll & rl) : (lo[q] | ll | rl), oh = ERO ? (hi[q] & lh & rh) : (hi[q] | lh | rh);
+            x[r][q] = ((uint64_t)oh << 32) | ol;
+        }
+    }
+}
+
+template <int R, int KT, int NC>
+__device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
+{
+    constexpr int N = R + 2 * KT + 1;          // rows y0 - 1 - KT .. y0 + R + KT - 1
+    const int lg = NC == 1 ? J->mgroup : kWave;
+    const int word = lane_word(lg);
+    const int H = J->H, Wd = J->Wd, oi = J->open_it, K = 2 * (oi + J->close_it);
+    const int y0 = (item * (kWave / lg) + lane_group(lg)) * R;
+    const int ytop = y0 - 1 - KT;
+    const GLOBAL uint64_t *raw = G(J->raw);
+    uint64_t x[N][NC];
+    const bool edge = __ballot(ytop < 0 || ytop + N > H) != 0ull;
+    uint32_t col[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        col[q] = (uint32_t)min(word + kWave * q, Wd - 1);
+    if (edge) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const uint32_t row = (uint32_t)min(max(ytop + r, 0), H - 1) * (uint32_t)Wd;
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                x[r][q] = *at_byte(raw, 8u * (row + col[q]));
+        }
+    } else {
+        const uint32_t row = (uint32_t)ytop * (uint32_t)Wd;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            const uint32_t off = 8u * (row + col[q]);
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                x[r][q] = *at_byte(raw + (size_t)r * Wd, off);
+        }
+    }
+    bool valid_w[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        valid_w[q] = word + kWave * q < Wd;
+    // anything left after the first stage?
+    uint64_t any = 0ull;
+    if (oi > 0) {
+#pragma unroll
+        for (int r = 1; r < N - 1; ++r) {
+            // rows outside the image are no obstacle to an erosion
+            const bool above = !edge || (uint32_t)(ytop + r - 1) < (uint32_t)H,
+                       below = !edge || (uint32_t)(ytop + r + 1) < (uint32_t)H,
+                       here = !edge || (uint32_t)(ytop + r) < (uint32_t)H;
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {
+                uint64_t v = x[r][q] & (above ? x[r - 1][q] : ~0ull) & (below ? x[r + 1][q] : ~0ull);
+                any |= valid_w[q] && here ? v : 0ull;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                any |= valid_w[q] && (uint32_t)(ytop + r) < (uint32_t)H ? x[r][q] : 0ull;
+    }
+    GLOBAL uint64_t *fz = G(J->fizi);
+    if (__ballot(any != 0ull) == 0ull) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                if (valid_w[q] && y0 + j < H)
+                    fz[j * Wd + y0 * Wd + word + kWave * q] = 0ull;
+        return;
+    }
+    if (KT == 4 && oi == 1 && K == 4) {          // the default opening and closing
+        regs_stage<true, N, NC>(x, 1, N - 2, Wd, lg, edge, ytop, H);
+        regs_stage<false, N, NC>(x, 2, N - 3, Wd, lg, edge, ytop, H);
+        regs_stage<false, N, NC>(x, 3, N - 4, Wd, lg, edge, ytop, H);
+        regs_stage<true, N, NC>(x, 4, N - 5, Wd, lg, edge, ytop, H);
+    } else {
+#pragma unroll 1
+        for (int k = 0; k < K; ++k) {
+            if (stage_erodes(k, oi, J->close_it))
+                regs_stage<true, N, NC>(x, 1, N - 2, Wd, lg, edge, ytop, H);
+            else
+                regs_stage<false, N, NC>(x, 1, N - 2, Wd, lg, edge, ytop, H);
+        }
+    }
+    // the final rows: stored, and those with pixels gathered for the run pass
+    typedef uint32_t rows_t __attribute__((ext_vector_type(R)));
+    rows_t lo[NC], hi[NC];
+    uint32_t full = 0;                          // bit j: row j has pixels
+#pragma unroll
+    for (int j = -1; j < R; ++j) {
+        uint64_t orw = 0ull;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            uint64_t &v = x[KT + 1 + j][q];
+            const bool in = valid_w[q] && (uint32_t)(y0 + j) < (uint32_t)H;
+            v = in ? v : 0ull;
+            orw |= v;
+            if (j >= 0) {
+                if (in)
+                    fz[j * Wd + y0 * Wd + word + kWave * q] = v;
+                lo[q][j < 0 ? 0 : j] = (uint32_t)v;
+                hi[q][j < 0 ? 0 : j] = (uint32_t)(v >> 32);
+            }
+        }
+        if (j >= 0 && __ballot(orw != 0ull) != 0ull)
+            full |= 1u << j;
+    }
+    if (!full)
+        return;
+    const BandOut B = band_out(J, lg);
+    RunState<NC> S;
+    L.npairs = 0u;
+    wave_sync();
+    uint64_t orw = 0ull;
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        orw |= x[KT][q];
+    if ((full & 1u) && __ballot(orw != 0ull) != 0ull)
+        halo_row<NC>(B, S, x[KT]);
+    int before = -1;                            // last row with runs
+#pragma unroll 1
+    for (uint32_t m = full; m; m &= m - 1u) {
+        const int j = __builtin_ctz(m);
+        uint64_t v[NC];
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+            v[q] = ((uint64_t)hi[q][j] << 32) | lo[q][j];
+        if (j != before + 1)
+            S.prev_valid = false;
+        before = j;
+        run_row<NC, false>(B, S, L, v, y0 + j);
+    }
+    flush_segment<false>(J, L, S.nseg, B.runs, B.parent, B.area, B.cap);
 }
 
 template <int KMAX, int NC>
@@ -1908,15 +2184,35 @@ __global__ __launch_bounds__(256) void k_morph(Table *__restrict__ T)
         const int j = find_job(T->h.mor_pre, nj, t);
         Job *J = &T->jobs[j];
         const int item = t - T->h.mor_pre[j];
-        if (KMAX >= 4 && J->open_it == 1 && J->close_it == 1) {   // the default opening and closing
-            if (J->mgroup == 16)
-                morph_band<KMAX, 1, false, 1, 1, 16>(J, 4 * item, s_wl[wave]);
-            else if (J->mgroup == 32)
-                morph_band<KMAX, 1, false, 1, 1, 32>(J, 2 * item, s_wl[wave]);
-            else
-                morph_band<KMAX, NC, false, 1, 1>(J, item, s_wl[wave]);
-        } else {
+        if (KMAX >= 4 && J->open_it == 1 && J->close_it == 1)     // the default opening and closing
+            morph_band<KMAX, NC, false, 1, 1>(J, item, s_wl[wave]);
+        else
             morph_band<KMAX, NC, false>(J, item, s_wl[wave]);
+    }
+}
+
+// Bands of R rows, or of the short height (the height is the job's: a graph
+// replays one kernel for steps of either).
+template <int R, int KT, int NC>
+__global__ __launch_bounds__(256) void k_morph_regs(Table *__restrict__ T)
+{
+    __shared__ WaveLds s_wl[256 / kWave];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int nj = T->h.njobs;
+    const int total = T->h.mor_pre[nj];
+    for (int t = blockIdx.x * (256 / kWave) + wave; t < total; t += gridDim.x * (256 / kWave)) {
+        const int j = find_job(T->h.mor_pre, nj, t);
+        Job *J = &T->jobs[j];
+        const int item = t - T->h.mor_pre[j];
+        if (NC == 2 && J->Wd > kWave) {
+            if (J->band == kShortBand)
+                morph_regs<kShortBand, KT, 2>(J, item, s_wl[wave]);
+            else
+                morph_regs<R, KT, 2>(J, item, s_wl[wave]);
+        } else if (J->band == kShortBand) {
+            morph_regs<kShortBand, KT, 1>(J, item, s_wl[wave]);
+        } else {
+            morph_regs<R, KT, 1>(J, item, s_wl[wave]);
         }
     }
 }
@@ -2389,8 +2685,9 @@ constexpr int kChainMax = kMaxJobs;
 __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restrict__ T)
 {
     __shared__ fizi_pointer s_ptr[kChainMax];
-    __shared__ uint32_t s_cover[kChainMax];
-    __shared__ int32_t s_gx[kChainMax], s_gy[kChainMax];   // guessed previous centroid, -1: no hand
+    __shared__ uint32_t s_cover[kChainMax], s_largest[kChainMax];
+    // guessed previous centroid of frame j, -1: no hand (j = nj: of the next call)
+    __shared__ int32_t s_gx[kChainMax + 1], s_gy[kChainMax + 1];
     __shared__ int32_t s_ax, s_ay;                          // actual previous centroid, -1: no hand
     __shared__ int s_next;                                  // frame the workgroup works on, or nj
     __shared__ uint32_t s_pick;
@@ -2400,12 +2697,16 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
     if (nj == 0)
         return;
     TrackState *ts = T->jobs[0].track;
-    for (int j = threadIdx.x; j < nj; j += blockDim.x)
+    for (int j = threadIdx.x; j < nj; j += blockDim.x) {
         s_ptr[j] = *T->jobs[j].out;
+        s_largest[j] = T->jobs[j].pick;
+    }
+    // one stream: its thresholds are the same in every job
+    const uint32_t amin = (uint32_t)max(T->jobs[0].min_area, 0), r2 = T->jobs[0].track_r2;
+    const int debounce = T->jobs[0].debounce;
     __syncthreads();
     // 1: the covering tests on the guess
-    for (int j = threadIdx.x; j < nj; j += blockDim.x) {
-        const Job *J = &T->jobs[j];
+    for (int j = threadIdx.x; j <= nj; j += blockDim.x) {
         int gx = -1, gy = -1;
         if (j == 0) {
             if (ts->valid) {
@@ -2418,7 +2719,8 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         }
         s_gx[j] = gx;
         s_gy[j] = gy;
-        s_cover[j] = gx >= 0 ? covering_root(J, gx, gy, (uint32_t)max(J->min_area, 0)) : kNoRoot;
+        if (j < nj)
+            s_cover[j] = gx >= 0 ? covering_root(&T->jobs[j], gx, gy, amin) : kNoRoot;
     }
     if (threadIdx.x == 0) {
         s_ax = ts->valid ? ts->x : -1;
@@ -2430,25 +2732,28 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
     int j0 = 0;
     for (;;) {
         if (threadIdx.x == 0) {
-            int j = j0;
+            int j = j0, ax = s_ax, ay = s_ay;
+            uint32_t state = s_state;
             for (; j < nj; ++j) {
-                const Job *J = &T->jobs[j];
-                const int ax = s_ax, ay = s_ay;
                 uint32_t c = s_cover[j];
                 if (ax != s_gx[j] || ay != s_gy[j])
-                    c = ax >= 0 ? covering_root(J, ax, ay, (uint32_t)max(J->min_area, 0)) : kNoRoot;
-                const bool near = ax >= 0 && c == kNoRoot && J->track_r2 > 0;
-                if (near || (c != kNoRoot && c != J->pick)) {
+                    c = ax >= 0 ? covering_root(&T->jobs[j], ax, ay, amin) : kNoRoot;
+                const bool near = ax >= 0 && c == kNoRoot && r2 > 0;
+                if (near || (c != kNoRoot && c != s_largest[j])) {
                     s_pick = c;
                     s_zone = !near;
                     break;
                 }
-                // the largest component keeps the hand: only the click changes
+                // the largest component keeps the hand: only the click
+                // changes, and the centroid is the one guessed
                 fizi_pointer &o = s_ptr[j];
-                o.click = debounce_click(&s_state, o.present != 0, o.click, J->debounce);
-                s_ax = o.present ? (int32_t)(o.sum_x / o.area) : -1;
-                s_ay = o.present ? (int32_t)(o.sum_y / o.area) : -1;
+                o.click = debounce_click(&state, o.present != 0, o.click, debounce);
+                ax = s_gx[j + 1];
+                ay = s_gy[j + 1];
             }
+            s_ax = ax;
+            s_ay = ay;
+            s_state = state;
             s_next = j;
         }
         __syncthreads();
@@ -2456,11 +2761,10 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         if (j >= nj)
             break;
         Job *J = &T->jobs[j];
-        const uint32_t amin = (uint32_t)max(J->min_area, 0);
         uint32_t pick = s_pick;
         if (!s_zone)
-            pick = nearest_root(J, s_ax, s_ay, amin, J->track_r2);
-        if (pick != kNoRoot && pick != J->pick) {
+            pick = nearest_root(J, s_ax, s_ay, amin, r2);
+        if (pick != kNoRoot && pick != s_largest[j]) {
             // the tracked zone is not the largest: its own sums, box, hand bits
             GLOBAL uint64_t *hand = J->hand ? G(J->hand) : nullptr;
             if (hand) {
@@ -2475,7 +2779,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         }
         if (threadIdx.x == 0) {
             fizi_pointer &o = s_ptr[j];
-            o.click = debounce_click(&s_state, o.present != 0, o.click, J->debounce);
+            o.click = debounce_click(&s_state, o.present != 0, o.click, debounce);
             s_ax = o.present ? (int32_t)(o.sum_x / o.area) : -1;
             s_ay = o.present ? (int32_t)(o.sum_y / o.area) : -1;
         }
@@ -2778,6 +3082,27 @@ hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max
     const int grid = min((total_tiles + waves - 1) / waves, n_cu * t.grid_per_cu);
     Table *tab = const_cast<Table *>(d_tab);
     const bool wide = max_wd > kWave, deep = max_ops > 4;
+    if (morph_in_regs(t.morph_rows, max_wd, max_ops)) {
+        if (t.morph_rows == 16) {
+            if (wide)
+                FIZI_LAUNCH((k_morph_regs<16, 4, 2>), grid, 256, 0, s, ev, tab);
+            else if (!deep)
+                FIZI_LAUNCH((k_morph_regs<16, 4, 1>), grid, 256, 0, s, ev, tab);
+            else if (max_ops <= 8)
+                FIZI_LAUNCH((k_morph_regs<16, 8, 1>), grid, 256, 0, s, ev, tab);
+            else
+                FIZI_LAUNCH((k_morph_regs<16, 12, 1>), grid, 256, 0, s, ev, tab);
+        } else if (wide) {
+            FIZI_LAUNCH((k_morph_regs<8, 4, 2>), grid, 256, 0, s, ev, tab);
+        } else if (!deep) {
+            FIZI_LAUNCH((k_morph_regs<8, 4, 1>), grid, 256, 0, s, ev, tab);
+        } else if (max_ops <= 8) {
+            FIZI_LAUNCH((k_morph_regs<8, 8, 1>), grid, 256, 0, s, ev, tab);
+        } else {
+            FIZI_LAUNCH((k_morph_regs<8, 12, 1>), grid, 256, 0, s, ev, tab);
+        }
+        return hipGetLastError();
+    }
     if (!wide && !deep)
         FIZI_LAUNCH((k_morph<4, 1>), grid, 256, 0, s, ev, tab);
     else if (!wide)
