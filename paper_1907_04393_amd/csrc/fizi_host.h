@@ -66,7 +66,7 @@ struct Slot {
     uint64_t *raw = nullptr;
     uint64_t *fz = nullptr;
     uint32_t *parent = nullptr;
-    uint32_t *area = nullptr;
+    uint32_t *index = nullptr;
     uint2 *runs = nullptr;
     uint2 *links = nullptr;
     uint32_t *bflag = nullptr;           // persistent step: per band epoch

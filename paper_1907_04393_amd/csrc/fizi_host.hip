@@ -197,7 +197,7 @@ Slot slot_at(const fizi_geom &g, uint8_t *base)
     o += align256(words * 8);
     s.parent = reinterpret_cast<uint32_t *>(base + o);
     o += align256(px * 4);
-    s.area = reinterpret_cast<uint32_t *>(base + o);
+    s.index = reinterpret_cast<uint32_t *>(base + o);
     o += align256(px * 4);
     s.runs = reinterpret_cast<uint2 *>(base + o);
     s.run_cap = (uint32_t)(px / 2);      // the most runs a mask can have
@@ -249,7 +249,7 @@ void set_scratch(Job &J, const Slot &s)
     J.raw = s.raw;
     J.fizi = s.fz;
     J.parent = s.parent;
-    J.area = s.area;
+    J.index = s.index;
     J.runs = s.runs;
     J.run_cap = s.run_cap;
     J.links = s.links;

@@ -76,9 +76,9 @@ struct Job {
     uint64_t *raw;             // H*Wd words: AND of the three masks
     uint64_t *fizi;            // H*Wd words: after opening and closing
     uint64_t *hand;            // H*Wd words or null
-    uint32_t *parent;          // W*H: union-find parent, valid at run starts
+    uint32_t *parent;          // W*H: union-find parents by run (run_cap), then component areas by root run
     uint32_t *bflag;           // per row band of the persistent step: epoch when classified
-    uint32_t *area;            // W*H: component area, valid at roots
+    uint32_t *index;           // W*H: run of a run's first pixel (valid there)
     uint2 *runs;               // run_cap runs (first pixel, last pixel | link flag)
     uint2 *links;              // link_cap pairs of run starts to join
     fizi_pointer *out;         // one pointer
@@ -109,7 +109,7 @@ struct Job {
     uint32_t nruns, flags, nlinks, nflag;
     uint32_t gain_done, morph_done;   // persistent step: finished gain tiles, morphology bands
     uint32_t ginv;                    // persistent step and spans: 0x80000000 | inverse gain, once known
-    uint32_t pick;                    // deferred tracking: root of the largest component (or none)
+    uint32_t pick;                    // deferred tracking: root run of the largest component (or none)
 };
 
 // The persistent step's queue: segments of work items, in order

@@ -544,7 +544,7 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     head.fizi = S.fizi + (size_t)i * S.fizi_words;
     head.hand = S.hand ? S.hand + (size_t)i * S.hand_words : nullptr;
     head.parent = moved(head.parent, so);
-    head.area = moved(head.area, so);
+    head.index = moved(head.index, so);
     head.runs = moved(head.runs, so);
     head.links = moved(head.links, so);
     head.out = S.out + i;
@@ -1168,13 +1168,6 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
 // flag kLinkUp (bit 63): the run must still be joined to the row above.
 constexpr uint32_t kLinkUp = 0x80000000u;
 
-// (first pixel, length) of a run list entry
-__device__ __forceinline__ uint2 unpack_run(uint64_t v)
-{
-    const uint32_t a = (uint32_t)v, e = (uint32_t)(v >> 32) & ~kLinkUp;
-    return make_uint2(a, e - a + 1u);
-}
-
 // Bit scans of one mask row (W = 64 * Wd pixels).
 // First x in [pos, limit] whose bit is 1, or -1.
 template <typename P>
@@ -1225,26 +1218,29 @@ __device__ __forceinline__ int next_zero(P row, int Wd, int pos)
     return (w << 6) + __builtin_ctzll(m);
 }
 
-// Union-find over run starts (pixel indices). A parent never exceeds its
-// child, so following parents always ends, and the root of a finished
-// component is its smallest run start: its first pixel in raster order.
+// Union-find over the runs of a frame's list. A root is linked under the root
+// whose run starts earlier in raster order, so following parents always ends,
+// and the root of a finished component is its first run: its first pixel is
+// the component's. A forest gives a run's parent (par), first pixel (start)
+// and link (an atomic that replaces a root's parent, returning what it found).
+//
 // Root of x with path halving: each visited node is pointed at its
 // grandparent. Safe beside concurrent finds and unions of the same workgroup:
-// parents only ever move to ancestors of the same set (a linked root's new
-// parent is smaller, a halved node's grandparent is one of its ancestors), so
-// a store that overwrites another still leaves the node in its set. Without
-// it, the border joins of a tall component chain one band's root under the
-// next, and every find walks that chain one dependent load at a time.
-__device__ __forceinline__ uint32_t find_root(GLOBAL uint32_t *parent, uint32_t x)
+// parents only ever move to ancestors of the same set, so a store that
+// overwrites another still leaves the node in its set. Without it, the border
+// joins of a tall component chain one band's root under the next, and every
+// find walks that chain one dependent load at a time.
+template <typename F>
+__device__ __forceinline__ uint32_t find_root(const F &f, uint32_t x)
 {
     for (;;) {
-        const uint32_t p = ld_wg(parent + x);
+        const uint32_t p = f.par(x);
         if (p == x)
             return x;
-        const uint32_t g = ld_wg(parent + p);
+        const uint32_t g = f.par(p);
         if (g == p)
             return p;
-        st_wg(parent + x, g);
+        f.set_par(x, g);
         x = g;
     }
 }
@@ -1253,41 +1249,95 @@ __device__ __forceinline__ uint32_t find_root(GLOBAL uint32_t *parent, uint32_t 
 // over, a node's parent need not be its root (a halving store of one thread
 // can land after another thread pointed the node at its root, and leave it at
 // an older ancestor), so a membership test walks to the root.
-__device__ __forceinline__ uint32_t root_of(GLOBAL uint32_t *parent, uint32_t x)
+template <typename F>
+__device__ __forceinline__ uint32_t root_of(const F &f, uint32_t x)
 {
     for (;;) {
-        const uint32_t p = ld_wg(parent + x);
+        const uint32_t p = f.par(x);
         if (p == x)
             return x;
         x = p;
     }
 }
 
-__device__ __forceinline__ void unite(GLOBAL uint32_t *parent, uint32_t a, uint32_t b)
+template <typename F>
+__device__ __forceinline__ void unite(const F &f, uint32_t a, uint32_t b)
 {
     for (;;) {
-        a = find_root(parent, a);
-        b = find_root(parent, b);
+        a = find_root(f, a);
+        b = find_root(f, b);
         if (a == b)
             return;
-        if (a > b) {
+        if (f.start(a) > f.start(b)) {
             const uint32_t t = a;
             a = b;
             b = t;
         }
-        const uint32_t old = __hip_atomic_fetch_min(parent + b, a, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t old = f.link(b, a);
         if (old == b)
             return;
         b = old;
     }
 }
 
-// Joins run (y, xs..xe), whose start pixel is `start`, with every run of the
-// row above that it touches under 8-connectivity (columns xs-1 .. xe+1).
-template <typename P>
-__device__ __forceinline__ void link_up(GLOBAL uint32_t *parent, P above, int Wd, int W, int y,
-                                        int xs, int xe, uint32_t start)
+// (first pixel, length) of a run list entry
+__device__ __forceinline__ uint2 unpack_run(uint64_t v)
+{
+    const uint32_t a = (uint32_t)v, e = (uint32_t)(v >> 32) & ~kLinkUp;
+    return make_uint2(a, e - a + 1u);
+}
+
+// A frame's forest in global memory: parents and areas by run, the run list.
+struct GlobalForest {
+    GLOBAL uint32_t *parent, *areas;
+    const GLOBAL uint64_t *runs;
+
+    __device__ __forceinline__ explicit GlobalForest(const Job *J)
+        : parent(G(J->parent)), areas(G(J->parent) + J->run_cap), runs(G(reinterpret_cast<const uint64_t *>(J->runs)))
+    {
+    }
+    __device__ __forceinline__ uint32_t par(uint32_t i) const { return ld_wg(parent + i); }
+    __device__ __forceinline__ void set_par(uint32_t i, uint32_t v) const { st_wg(parent + i, v); }
+    __device__ __forceinline__ uint32_t start(uint32_t i) const { return (uint32_t)runs[i]; }
+    __device__ __forceinline__ uint32_t link(uint32_t root, uint32_t to) const
+    {
+        uint32_t expect = root;
+        __hip_atomic_compare_exchange_strong(parent + root, &expect, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        return expect;
+    }
+    __device__ __forceinline__ uint32_t area(uint32_t root) const { return ld_wg(areas + root); }
+    __device__ __forceinline__ uint2 run(uint32_t i) const { return unpack_run(runs[i]); }
+};
+
+// The same in LDS, for frames of at most C runs.
+template <int C>
+struct LdsRuns {
+    uint32_t par[C], start[C], len[C], area[C];
+};
+
+template <int C>
+struct LdsForest {
+    LdsRuns<C> &t;
+    __device__ __forceinline__ uint32_t par(uint32_t i) const
+    {
+        return __hip_atomic_load(&t.par[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void set_par(uint32_t i, uint32_t v) const
+    {
+        __hip_atomic_store(&t.par[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t start(uint32_t i) const { return t.start[i]; }
+    __device__ __forceinline__ uint32_t link(uint32_t root, uint32_t to) const { return atomicCAS(&t.par[root], root, to); }
+    __device__ __forceinline__ uint32_t area(uint32_t root) const { return t.area[root]; }
+    __device__ __forceinline__ uint2 run(uint32_t i) const { return make_uint2(t.start[i], t.len[i]); }
+};
+
+// Joins run i (y, xs..xe) with every run of the row above that it touches
+// under 8-connectivity (columns xs-1 .. xe+1).
+template <typename F, typename P>
+__device__ __forceinline__ void link_up(const F &f, const GLOBAL uint32_t *index, P above, int Wd, int W, int y,
+                                        int xs, int xe, uint32_t i)
 {
     const int hi = min(xe + 1, W - 1);
     int pos = max(xs - 1, 0);
@@ -1296,7 +1346,7 @@ __device__ __forceinline__ void link_up(GLOBAL uint32_t *parent, P above, int Wd
         if (xb < 0)
             break;
         const int bs = prev_zero(above, xb) + 1;
-        unite(parent, start, (uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs);
+        unite(f, i, index[(uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs]);
         pos = next_zero(above, Wd, xb) + 1;
     }
 }
@@ -1605,7 +1655,7 @@ __device__ __forceinline__ uint32_t reserve_runs(Job *J, uint32_t n, uint32_t ca
 // Closes a segment: its n runs join the run list, each pointing at its root.
 template <bool FLOW>
 __device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GLOBAL uint64_t *runs,
-                                              GLOBAL uint32_t *parent, GLOBAL uint32_t *area, uint32_t cap)
+                                              GLOBAL uint32_t *parent, GLOBAL uint32_t *index, uint32_t cap)
 {
     const int lane = threadIdx.x & (kWave - 1);
     if (n == 0)
@@ -1622,8 +1672,8 @@ __device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GL
         const uint32_t r = find_lds(L.par, k);
         if (base + k < cap) {
             put<FLOW>(runs + base + k, ((uint64_t)L.end[k] << 32) | st);
-            put_parent<FLOW>(parent + st, L.start[r]);
-            put<FLOW>(area + st, 0u);
+            put_parent<FLOW>(parent + base + k, base + r);
+            put<FLOW>(index + st, base + k);
         }
     }
     wave_sync();
@@ -1654,7 +1704,7 @@ struct BandOut {
     Job *J;
     int W, Wd, lg, word;
     GLOBAL uint64_t *runs;
-    GLOBAL uint32_t *parent, *area, *linkw;
+    GLOBAL uint32_t *parent, *index, *linkw;
     uint32_t cap, link_cap;
 };
 
@@ -1668,7 +1718,7 @@ __device__ __forceinline__ BandOut band_out(Job *J, int lg)
     B.word = lane_word(lg);
     B.runs = G(reinterpret_cast<uint64_t *>(J->runs));
     B.parent = G(J->parent);
-    B.area = G(J->area);
+    B.index = G(J->index);
     B.linkw = G(reinterpret_cast<uint32_t *>(J->links));
     B.cap = J->run_cap;
     B.link_cap = J->link_cap;
@@ -1712,7 +1762,7 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
     const int lane = threadIdx.x & (kWave - 1);
     const int W = B.W, Wd = B.Wd, word = B.word;
     GLOBAL uint64_t *runs = B.runs;
-    GLOBAL uint32_t *parent = B.parent, *area = B.area, *linkw = B.linkw;
+    GLOBAL uint32_t *parent = B.parent, *index = B.index, *linkw = B.linkw;
     const uint32_t cap = B.cap, link_cap = B.link_cap;
     RowBits<NC> &P = S.P;
     uint32_t &nseg = S.nseg, &prev_first = S.prev_first;
@@ -1722,7 +1772,7 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
     const uint32_t total = row_bits<NC>(D, x, Wd, en, B.lg);
     if (nseg + total > (uint32_t)kSegRuns) {
         // the open segment is full: close it, this row opens the next
-        flush_segment<FLOW>(J, L, nseg, runs, parent, area, cap);
+        flush_segment<FLOW>(J, L, nseg, runs, parent, index, cap);
         nseg = 0;
         prev_in_seg = false;
     }
@@ -1780,8 +1830,8 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
                 L.par[nseg + k] = nseg + k;
             } else if (rbase + k < cap) {
                 put<FLOW>(runw + 2 * (size_t)(rbase + k), start);
-                put_parent<FLOW>(parent + start, start);
-                put<FLOW>(area + start, 0u);
+                put_parent<FLOW>(parent + rbase + k, rbase + k);
+                put<FLOW>(index + start, rbase + k);
             }
         }
         m = en[c];
@@ -1961,7 +2011,7 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
         for (int q = 0; q < kRawChunk && s0 + kRawChunk + q < nsteps; ++q)
             step(s0 + kRawChunk + q, q, cb);
     }
-    flush_segment<FLOW>(J, L, S.nseg, B.runs, B.parent, B.area, B.cap);
+    flush_segment<FLOW>(J, L, S.nseg, B.runs, B.parent, B.index, B.cap);
 }
 
 // A band of at most 16 rows, all of it in registers: the rows with their halo
@@ -2167,7 +2217,7 @@ __device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
         before = j;
         run_row<NC, false>(B, S, L, v, y0 + j);
     }
-    flush_segment<false>(J, L, S.nseg, B.runs, B.parent, B.area, B.cap);
+    flush_segment<false>(J, L, S.nseg, B.runs, B.parent, B.index, B.cap);
 }
 
 template <int KMAX, int NC>
@@ -2240,8 +2290,18 @@ struct AreaTable {
     uint32_t val[kAreaSlots];
     uint32_t overflow;
 };
-// the persistent step lends its four waves' morphology tables to it
-static_assert(sizeof(AreaTable) <= 4 * sizeof(WaveLds), "area table fits the morphology LDS");
+
+// A frame's components in LDS where its runs fit: 3072 (48 KiB) in the
+// component stage, 2048 in the persistent step, which lends its four waves'
+// morphology tables (16 bytes a run). A frame with more runs is resolved in global memory, with
+// the table of areas in the same place.
+constexpr int kForestRuns = 3072, kForestRunsFlow = 2048;
+template <int C>
+union ResolveLds {
+    LdsRuns<C> runs;
+    AreaTable areas;
+};
+static_assert(sizeof(ResolveLds<kForestRunsFlow>) <= 4 * sizeof(WaveLds), "the forest fits the morphology LDS");
 
 __device__ __forceinline__ void area_add(AreaTable &t, GLOBAL uint32_t *area, uint32_t root, uint32_t len)
 {
@@ -2297,23 +2357,128 @@ __device__ __forceinline__ unsigned long long wg_max_u64(unsigned long long v, u
 
 constexpr uint32_t kNoRoot = 0xFFFFFFFFu;
 
-// Phases A-C of the component stage for one frame (one workgroup): the joins
-// across band and segment borders (and runs flagged when the pair list was
-// full, joined by reading I_FIZI), every run's root and each component's
-// area, and the largest component (ties to the smallest first index) as a
-// key area << 32 | ~root. Afterwards area[] holds every root's area and
-// each non-root run start's parent is one of its ancestors (see root_of).
-__device__ __forceinline__ void resolve_forest(Job *J, AreaTable &tab, uint32_t *ncomp_out,
-                                               unsigned long long *best_out)
+// A frame's components after its unions: their number, the largest one's
+// area and root run (ties to the smallest first pixel).
+struct Components {
+    uint32_t count, area, root;
+};
+
+// The components of a forest whose areas are known, from each thread's own
+// best key (area << 32 | ~first pixel) and root run, and its count of roots
+// (whole workgroup).
+__device__ __forceinline__ Components largest_of(unsigned long long best, uint32_t root, uint32_t count)
 {
     __shared__ unsigned long long s_u64[kMaxWaves];
-    __shared__ uint32_t s_u32[kMaxWaves];
+    __shared__ uint32_t s_u32[kMaxWaves], s_root;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    const int W = J->W, Wd = J->Wd;
-    const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
+    unsigned long long all = best;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const unsigned long long ob = __shfl_xor(all, o, kWave);
+        all = ob > all ? ob : all;
+        count += (uint32_t)__shfl_xor((int)count, o, kWave);
+    }
+    if (lane == 0) {
+        s_u64[wave] = all;
+        s_u32[wave] = count;
+    }
+    if (threadIdx.x == 0)
+        s_root = kNoRoot;
+    __syncthreads();
+    all = s_u64[0];
+    count = s_u32[0];
+    for (int w = 1; w < nw; ++w) {
+        all = s_u64[w] > all ? s_u64[w] : all;
+        count += s_u32[w];
+    }
+    // a key belongs to one component
+    if (best == all && best != 0ull)
+        s_root = root;
+    __syncthreads();
+    return Components{count, (uint32_t)(all >> 32), s_root};
+}
+
+__device__ __forceinline__ unsigned long long size_key(uint32_t area, uint32_t first)
+{
+    return ((unsigned long long)area << 32) | (0xFFFFFFFFull - first);
+}
+
+// The components of one frame (one workgroup): the joins across band and
+// segment borders, every run's root and each component's area, and the
+// largest component. In LDS: the run list, parents and joins are each read
+// once, all loads at once, and what follows waits for LDS only (in global
+// memory each step of a find and each union was a dependent access of 0.6 us:
+// one frame of 1920x1080 15.7 us against 12 here, 16 of 1280x720 12.5 against
+// 9.8, the 64-stream batch beside classify 134 against 43).
+template <int C>
+__device__ __forceinline__ Components resolve_lds(Job *J, LdsRuns<C> &t, uint32_t nr, uint32_t nl)
+{
     const GLOBAL uint64_t *runs = G(reinterpret_cast<const uint64_t *>(J->runs));
-    GLOBAL uint32_t *parent = G(J->parent);
-    GLOBAL uint32_t *area = G(J->area);
+    const GLOBAL uint64_t *links = G(reinterpret_cast<const uint64_t *>(J->links));
+    const GLOBAL uint32_t *index = G(J->index), *parent = G(J->parent);
+    const LdsForest<C> f{t};
+    // the thread's first join, its runs looked up beside the run list
+    uint32_t la = 0, lb = 0;
+    const bool joins = threadIdx.x < nl;
+    if (joins) {
+        const uint64_t l = links[threadIdx.x];
+        la = index[(uint32_t)l];
+        lb = index[(uint32_t)(l >> 32)];
+    }
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
+        const uint2 rn = unpack_run(runs[i]);
+        t.par[i] = parent[i];
+        t.start[i] = rn.x;
+        t.len[i] = rn.y;
+        t.area[i] = rn.y;
+    }
+    __syncthreads();
+    if (joins)
+        unite(f, la, lb);
+    for (uint32_t i = threadIdx.x + blockDim.x; i < nl; i += blockDim.x) {
+        const uint64_t l = links[i];
+        unite(f, index[(uint32_t)l], index[(uint32_t)(l >> 32)]);
+    }
+    __syncthreads();
+    // shorten the paths, then point every run at its root
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
+        (void)find_root(f, i);
+    __syncthreads();
+    uint32_t count = 0;
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
+        const uint32_t r = root_of(f, i);
+        if (r == i) {
+            ++count;
+        } else {
+            f.set_par(i, r);
+            atomicAdd(&t.area[r], t.len[i]);
+        }
+    }
+    __syncthreads();
+    unsigned long long best = 0ull;
+    uint32_t root = 0;
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
+        if (t.par[i] == i) {
+            const unsigned long long key = size_key(t.area[i], t.start[i]);
+            if (key > best) {
+                best = key;
+                root = i;
+            }
+        }
+    }
+    return largest_of(best, root, count);
+}
+
+// The same in global memory, for frames with more runs or an overflown join
+// list (its flagged runs are joined by reading I_FIZI). Afterwards the areas
+// hold every root's area and each other run's parent is one of its ancestors
+// (see root_of).
+__device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uint32_t nr, uint32_t nl)
+{
+    const int W = J->W, Wd = J->Wd;
+    const GlobalForest f(J);
+    const GLOBAL uint64_t *links = G(reinterpret_cast<const uint64_t *>(J->links));
+    const GLOBAL uint32_t *index = G(J->index);
     const GLOBAL uint64_t *fz = G(J->fizi);
     if (threadIdx.x == 0)
         tab.overflow = 0;
@@ -2321,16 +2486,16 @@ __device__ __forceinline__ void resolve_forest(Job *J, AreaTable &tab, uint32_t 
         tab.key[i] = kAreaEmpty;
         tab.val[i] = 0;
     }
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
+        st_wg(f.areas + i, 0u);
     __syncthreads();
-    const uint32_t nl = min(ld_dev(&J->nlinks), J->link_cap);
-    const GLOBAL uint64_t *links = G(reinterpret_cast<const uint64_t *>(J->links));
     for (uint32_t i = threadIdx.x; i < nl; i += blockDim.x) {
         const uint64_t l = links[i];
-        unite(parent, (uint32_t)l, (uint32_t)(l >> 32));
+        unite(f, index[(uint32_t)l], index[(uint32_t)(l >> 32)]);
     }
     if (ld_dev(&J->nflag))
         for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-            const uint64_t rv = runs[i];
+            const uint64_t rv = f.runs[i];
             if (!((uint32_t)(rv >> 32) & kLinkUp))
                 continue;
             const uint2 rn = unpack_run(rv);
@@ -2338,73 +2503,55 @@ __device__ __forceinline__ void resolve_forest(Job *J, AreaTable &tab, uint32_t 
             if (y == 0)
                 continue;
             const int xs = (int)(rn.x - (uint32_t)y * W), xe = xs + (int)rn.y - 1;
-            link_up(parent, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xe, rn.x);
+            link_up(f, index, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xe, i);
         }
     __syncthreads();
-    // B: roots and areas
-    uint32_t ncomp = 0;
+    // roots and areas
+    uint32_t count = 0;
     for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        const uint2 rn = unpack_run(runs[i]);
-        const uint32_t root = find_root(parent, rn.x);
-        if (root == rn.x)
-            ++ncomp;
+        const uint32_t r = find_root(f, i);
+        if (r == i)
+            ++count;
         else
-            st_wg(parent + rn.x, root);
-        area_add(tab, area, root, rn.y);
+            f.set_par(i, r);
+        area_add(tab, f.areas, r, f.run(i).y);
     }
     __syncthreads();
-    // the table's areas go to the global array (tracking and the chain read it)
-    for (int i = threadIdx.x; i < kAreaSlots; i += blockDim.x) {
-        const uint32_t k = tab.key[i];
-        if (k != kAreaEmpty)
-            st_wg(area + k, tab.val[i]);
-    }
-    // C: the largest component: from the table, or from every run when some
+    // the table's areas go to the global array (tracking and the chain read
+    // it); the largest component from the table, or from every run when some
     // root did not fit it
     unsigned long long best = 0ull;
-    if (!tab.overflow) {
-        for (int i = threadIdx.x; i < kAreaSlots; i += blockDim.x) {
-            const uint32_t k = tab.key[i];
-            if (k != kAreaEmpty) {
-                const unsigned long long key = ((unsigned long long)tab.val[i] << 32) | (0xFFFFFFFFull - k);
-                best = key > best ? key : best;
+    uint32_t root = 0;
+    for (int i = threadIdx.x; i < kAreaSlots; i += blockDim.x) {
+        const uint32_t k = tab.key[i];
+        if (k != kAreaEmpty) {
+            st_wg(f.areas + k, tab.val[i]);
+            const unsigned long long key = size_key(tab.val[i], f.start(k));
+            if (key > best) {
+                best = key;
+                root = k;
             }
         }
-    } else {
+    }
+    if (tab.overflow) {
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-            const uint32_t s = (uint32_t)runs[i];
-            if (ld_wg(parent + s) == s) {
-                const unsigned long long key = ((unsigned long long)ld_wg(area + s) << 32) | (0xFFFFFFFFull - s);
-                best = key > best ? key : best;
+            if (f.par(i) == i) {
+                const unsigned long long key = size_key(f.area(i), f.start(i));
+                if (key > best) {
+                    best = key;
+                    root = i;
+                }
             }
         }
     }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const unsigned long long ob = __shfl_xor(best, o, kWave);
-        best = ob > best ? ob : best;
-        ncomp += (uint32_t)__shfl_xor((int)ncomp, o, kWave);
-    }
-    __syncthreads();
-    if (lane == 0) {
-        s_u64[wave] = best;
-        s_u32[wave] = ncomp;
-    }
-    __syncthreads();
-    best = s_u64[0];
-    ncomp = s_u32[0];
-    for (int w = 1; w < nw; ++w) {
-        best = s_u64[w] > best ? s_u64[w] : best;
-        ncomp += s_u32[w];
-    }
-    *ncomp_out = ncomp;
-    *best_out = best;
+    return largest_of(best, root, count);
 }
 
-// Root of the component of area >= amin covering pixel (tx, ty), or kNoRoot
-// (one thread; the forest is final).
-__device__ __forceinline__ uint32_t covering_root(const Job *J, int tx, int ty, uint32_t amin)
+// Root run of the component of area >= amin covering pixel (tx, ty), or
+// kNoRoot (one thread; the forest is final).
+template <typename F>
+__device__ __forceinline__ uint32_t covering_root(const Job *J, const F &f, int tx, int ty, uint32_t amin)
 {
     if (tx < 0 || tx >= J->W || ty < 0 || ty >= J->H)
         return kNoRoot;
@@ -2412,25 +2559,23 @@ __device__ __forceinline__ uint32_t covering_root(const Job *J, int tx, int ty, 
     if (!((row[tx >> 6] >> (tx & 63)) & 1ull))
         return kNoRoot;
     const uint32_t start = (uint32_t)ty * (uint32_t)J->W + (uint32_t)(prev_zero(row, tx) + 1);
-    const uint32_t r = root_of(G(J->parent), start);
-    return ld_wg(G(J->area) + r) >= amin ? r : kNoRoot;
+    const uint32_t r = root_of(f, G(J->index)[start]);
+    return f.area(r) >= amin ? r : kNoRoot;
 }
 
 // The component of area >= amin nearest to (tx, ty) within sqrt(r2) pixels:
 // the smallest squared distance from the point to a pixel of it, ties to the
-// larger area, then the smaller first index; kNoRoot when none (whole
+// larger area, then the smaller first pixel; kNoRoot when none (whole
 // workgroup; the forest is final). A run's pixel nearest to the point is
 // its own clamp of tx, so two passes over the runs decide it: the least
 // distance, then the best key among the runs at that distance.
-__device__ __forceinline__ uint32_t nearest_root(const Job *J, int tx, int ty, uint32_t amin, uint32_t r2)
+template <typename F>
+__device__ __forceinline__ uint32_t nearest_root(const Job *J, const F &f, int tx, int ty, uint32_t amin, uint32_t r2)
 {
     __shared__ uint32_t s_min[kMaxWaves];
     __shared__ unsigned long long s_key[kMaxWaves];
     const int W = J->W;
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
-    const GLOBAL uint64_t *runs = G(reinterpret_cast<const uint64_t *>(J->runs));
-    GLOBAL uint32_t *parent = G(J->parent);
-    GLOBAL uint32_t *area = G(J->area);
     auto dist2 = [&](uint2 rn) -> uint32_t {
         const int y = (int)(rn.x / (uint32_t)W), xs = (int)(rn.x - (uint32_t)y * W), xe = xs + (int)rn.y - 1;
         const int dx = tx < xs ? xs - tx : (tx > xe ? tx - xe : 0), dy = y - ty;
@@ -2438,45 +2583,42 @@ __device__ __forceinline__ uint32_t nearest_root(const Job *J, int tx, int ty, u
         return d2 > 0xFFFFFFFEull ? 0xFFFFFFFEu : (uint32_t)d2;
     };
     uint32_t dmin = 0xFFFFFFFFu;
-    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        const uint2 rn = unpack_run(runs[i]);
-        const uint32_t r = root_of(parent, rn.x);
-        if (ld_wg(area + r) >= amin)
-            dmin = min(dmin, dist2(rn));
-    }
+    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
+        if (f.area(root_of(f, i)) >= amin)
+            dmin = min(dmin, dist2(f.run(i)));
     dmin = wg_min_u32(dmin, s_min);
     if (dmin > r2)
         return kNoRoot;
     unsigned long long key = 0ull;
     for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        const uint2 rn = unpack_run(runs[i]);
-        if (dist2(rn) != dmin)
+        if (dist2(f.run(i)) != dmin)
             continue;
-        const uint32_t r = root_of(parent, rn.x);
-        const uint32_t a = ld_wg(area + r);
+        const uint32_t r = root_of(f, i);
+        const uint32_t a = f.area(r);
         if (a >= amin) {
-            const unsigned long long k = ((unsigned long long)a << 32) | (0xFFFFFFFFull - r);
+            const unsigned long long k = size_key(a, f.start(r));
             key = k > key ? k : key;
         }
     }
     key = wg_max_u64(key, s_key);
-    return key ? 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull) : kNoRoot;
+    return key ? G(J->index)[0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull)] : kNoRoot;
 }
 
 // The tracked pick given the previous frame's centroid pixel (valid: it had
 // a hand): the covering component, else the nearest within the radius;
 // kNoRoot for the largest (whole workgroup).
-__device__ __forceinline__ uint32_t tracked_pick(const Job *J, bool valid, int tx, int ty)
+template <typename F>
+__device__ __forceinline__ uint32_t tracked_pick(const Job *J, const F &f, bool valid, int tx, int ty)
 {
     __shared__ uint32_t s_pick;
     const uint32_t amin = (uint32_t)max(J->min_area, 0);
     if (threadIdx.x == 0)
-        s_pick = valid ? covering_root(J, tx, ty, amin) : kNoRoot;
+        s_pick = valid ? covering_root(J, f, tx, ty, amin) : kNoRoot;
     __syncthreads();
     uint32_t pick = s_pick;
     __syncthreads();
     if (valid && pick == kNoRoot && J->track_r2 > 0)
-        pick = nearest_root(J, tx, ty, amin, J->track_r2);
+        pick = nearest_root(J, f, tx, ty, amin, J->track_r2);
     return pick;
 }
 
@@ -2488,20 +2630,19 @@ struct ZoneStats {
 // Pass D: coordinate sums and box of component kstar, and its hand bits
 // (whole workgroup; thread 0 gets the totals). Membership walks each run to
 // its root without writing.
-__device__ __forceinline__ ZoneStats zone_stats(const Job *J, uint32_t kstar, GLOBAL uint64_t *hand)
+template <typename F>
+__device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32_t kstar, GLOBAL uint64_t *hand)
 {
     __shared__ unsigned long long s_u64[2][kMaxWaves];
     __shared__ uint32_t s_u32[4][kMaxWaves];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
     const int W = J->W, Wd = J->Wd;
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
-    const GLOBAL uint64_t *runs = G(reinterpret_cast<const uint64_t *>(J->runs));
-    GLOBAL uint32_t *parent = G(J->parent);
     ZoneStats z{0, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, 0};
     for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        const uint2 rn = unpack_run(runs[i]);
-        if (root_of(parent, rn.x) != kstar)
+        if (root_of(f, i) != kstar)
             continue;
+        const uint2 rn = f.run(i);
         const uint32_t y = rn.x / (uint32_t)W, xs = rn.x - y * (uint32_t)W;
         const uint32_t xe = xs + rn.y - 1;
         z.sx += (unsigned long long)rn.y * xs + (unsigned long long)rn.y * (rn.y - 1) / 2;
@@ -2601,41 +2742,31 @@ __device__ __forceinline__ uint8_t debounce_click(uint32_t *state, bool present,
     return (uint8_t)shown;
 }
 
-// One workgroup per frame: the forest, the hand zone, its sums and box, and
-// the pointer. A tracked frame picks its zone from the previous centroid
+// The hand zone of a frame whose components are known, and its pointer (whole
+// workgroup). A tracked frame picks its zone from the previous centroid
 // (tracked_pick) and debounces its click - unless `defer`: then the frame's
-// pointer is the largest component's, its root goes to J->pick, and the
+// pointer is the largest component's, its root run goes to J->pick, and the
 // tracking chain (k_track_chain) settles the tracked frames of the launch in
 // order afterwards.
-__device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool same_launch, AreaTable &tab,
-                                            bool defer = false)
+template <typename F>
+__device__ __forceinline__ void resolve_zone(Job *J, const F &f, const Components &c, uint32_t inv, bool defer)
 {
-    Job *J = &T->jobs[j];
-    const int H = J->H, Wd = J->Wd;
-    GLOBAL uint32_t *area = G(J->area);
     GLOBAL uint64_t *hand = J->hand ? G(J->hand) : nullptr;
-    const uint32_t inv = same_launch ? job_gain(J, true) : frame_gain(J);
-    if (hand)
-        for (int i = threadIdx.x; i < H * Wd; i += blockDim.x)
-            hand[i] = 0ull;
-    uint32_t ncomp;
-    unsigned long long best;
-    resolve_forest(J, tab, &ncomp, &best);
     TrackState *ts = J->track;
     uint32_t pick = kNoRoot;
     if (ts && !defer)
-        pick = tracked_pick(J, ts->valid != 0, ts->x, ts->y);
+        pick = tracked_pick(J, f, ts->valid != 0, ts->x, ts->y);
     const bool tracked = pick != kNoRoot;
-    const uint32_t A = tracked ? ld_wg(area + pick) : (uint32_t)(best >> 32);
-    const uint32_t kstar = tracked ? pick : 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
-    const bool present = ncomp > 0 && (long long)A >= (long long)J->min_area;
+    const uint32_t A = tracked ? f.area(pick) : c.area;
+    const uint32_t kstar = tracked ? pick : c.root;
+    const bool present = c.count > 0 && (long long)A >= (long long)J->min_area;
     ZoneStats z{0, 0, 0, 0, 0, 0};
     if (present)
-        z = zone_stats(J, kstar, hand);
+        z = zone_stats(J, f, kstar, hand);
     if (threadIdx.x == 0) {
-        fizi_pointer o = make_pointer(J, present, A, z, ncomp, inv);
+        fizi_pointer o = make_pointer(J, present, A, z, c.count, inv);
         if (defer) {
-            J->pick = ncomp > 0 ? kstar : kNoRoot;
+            J->pick = c.count > 0 ? kstar : kNoRoot;
         } else if (ts) {
             o.click = debounce_click(&ts->click, present, o.click, J->debounce);
             ts->valid = present ? 1 : 0;
@@ -2650,16 +2781,48 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
         if (J->hout && !defer)
             *J->hout = o;
     }
+}
+
+// One workgroup per frame: its components, the hand zone, and the pointer.
+template <int C>
+__device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool same_launch, ResolveLds<C> &lds,
+                                            bool defer = false)
+{
+    Job *J = &T->jobs[j];
+    const uint32_t inv = same_launch ? job_gain(J, true) : frame_gain(J);
+    const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap), nl = min(ld_dev(&J->nlinks), J->link_cap);
+    if (J->hand) {
+        GLOBAL uint64_t *hand = G(J->hand);
+        for (int i = threadIdx.x; i < J->H * J->Wd; i += blockDim.x)
+            hand[i] = 0ull;
+    }
+    if (nr <= (uint32_t)C && ld_dev(&J->nflag) == 0u) {
+        const LdsForest<C> f{lds.runs};
+        const Components c = resolve_lds(J, lds.runs, nr, nl);
+        if (defer) {
+            // the chain reads the forest
+            const GlobalForest g(J);
+            for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
+                st_wg(g.parent + i, lds.runs.par[i]);
+                st_wg(g.areas + i, lds.runs.area[i]);
+            }
+        }
+        resolve_zone(J, f, c, inv, defer);
+    } else {
+        const GlobalForest f(J);
+        const Components c = resolve_global(J, lds.areas, nr, nl);
+        resolve_zone(J, f, c, inv, defer);
+    }
     __syncthreads();
 }
 
 template <int NT>
 __global__ __launch_bounds__(NT) void k_resolve(Table *__restrict__ T, int defer)
 {
-    __shared__ AreaTable s_tab;
+    __shared__ ResolveLds<kForestRuns> s_lds;
     const int nj = T->h.njobs;
     for (int j = blockIdx.x; j < nj; j += gridDim.x)
-        resolve_job(T, j, false, s_tab, defer != 0);
+        resolve_job(T, j, false, s_lds, defer != 0);
 }
 
 // Tracking of consecutive frames of one stream after a deferred component
@@ -2720,7 +2883,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         s_gx[j] = gx;
         s_gy[j] = gy;
         if (j < nj)
-            s_cover[j] = gx >= 0 ? covering_root(&T->jobs[j], gx, gy, amin) : kNoRoot;
+            s_cover[j] = gx >= 0 ? covering_root(&T->jobs[j], GlobalForest(&T->jobs[j]), gx, gy, amin) : kNoRoot;
     }
     if (threadIdx.x == 0) {
         s_ax = ts->valid ? ts->x : -1;
@@ -2737,7 +2900,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
             for (; j < nj; ++j) {
                 uint32_t c = s_cover[j];
                 if (ax != s_gx[j] || ay != s_gy[j])
-                    c = ax >= 0 ? covering_root(&T->jobs[j], ax, ay, amin) : kNoRoot;
+                    c = ax >= 0 ? covering_root(&T->jobs[j], GlobalForest(&T->jobs[j]), ax, ay, amin) : kNoRoot;
                 const bool near = ax >= 0 && c == kNoRoot && r2 > 0;
                 if (near || (c != kNoRoot && c != s_largest[j])) {
                     s_pick = c;
@@ -2761,9 +2924,10 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         if (j >= nj)
             break;
         Job *J = &T->jobs[j];
+        const GlobalForest f(J);
         uint32_t pick = s_pick;
         if (!s_zone)
-            pick = nearest_root(J, s_ax, s_ay, amin, r2);
+            pick = nearest_root(J, f, s_ax, s_ay, amin, r2);
         if (pick != kNoRoot && pick != s_largest[j]) {
             // the tracked zone is not the largest: its own sums, box, hand bits
             GLOBAL uint64_t *hand = J->hand ? G(J->hand) : nullptr;
@@ -2772,8 +2936,8 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
                     hand[i] = 0ull;
                 __syncthreads();
             }
-            const uint32_t A = ld_wg(G(J->area) + pick);
-            const ZoneStats z = zone_stats(J, pick, hand);
+            const uint32_t A = f.area(pick);
+            const ZoneStats z = zone_stats(J, f, pick, hand);
             if (threadIdx.x == 0)
                 s_ptr[j] = make_pointer(J, true, A, z, s_ptr[j].n_components, s_ptr[j].inv_gain_q16);
         }
@@ -2922,9 +3086,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX == 4 &
             if (publish_add(&J->morph_done, cnt, &s_u) + cnt == (uint32_t)nsub) {
                 // the frame's last band: its components
                 acquire_for_block();
-                // the waves' morphology tables are free again: the area table
-                // takes their place
-                resolve_job(T, j, true, *reinterpret_cast<AreaTable *>(&s_wl[0]));
+                // the waves' morphology tables are free again: the components
+                // take their place
+                resolve_job(T, j, true, *reinterpret_cast<ResolveLds<kForestRunsFlow> *>(&s_wl[0]));
             }
         }
     }
