@@ -450,7 +450,7 @@ int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &
               StageClock *clk, bool beside)
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
-    FIZI_HIP(launch_morph(d_tab, S.n * S.mor_items, S.W / 64, max_ops, n_cu, t, s, ev(FIZI_STAGE_MORPH)));
+    FIZI_HIP(launch_morph(d_tab, S.n * S.mor_items, S.mor_items, S.W / 64, max_ops, n_cu, t, s, ev(FIZI_STAGE_MORPH)));
     // tracked consecutive frames are resolved in order
     FIZI_HIP(launch_resolve(d_tab, S.n, s, ev(FIZI_STAGE_RESOLVE), S.n > 1 && S.track != nullptr, beside));
     return FIZI_OK;
@@ -492,7 +492,7 @@ int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int ma
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
     const int big = INT_MAX / 2;
-    FIZI_HIP(launch_morph(d_tab, fixed_grid ? big : h.h.mor_pre[njobs], max_wd, max_ops, n_cu, t, s,
+    FIZI_HIP(launch_morph(d_tab, fixed_grid ? big : h.h.mor_pre[njobs], 0, max_wd, max_ops, n_cu, t, s,
                           ev(FIZI_STAGE_MORPH)));
     FIZI_HIP(launch_resolve(d_tab, fixed_grid ? max_jobs : njobs, s, ev(FIZI_STAGE_RESOLVE), false, beside));
     return FIZI_OK;

@@ -106,7 +106,8 @@ struct Job {
     // most 1020, 2.1e9)
     alignas(8) uint32_t num[kGainSlots];
     uint32_t den[kGainSlots];
-    uint32_t nruns, flags, nlinks, nflag;
+    uint32_t nruns, nlinks;           // reserved together by one 64-bit add where both are known
+    uint32_t flags, nflag;
     uint32_t gain_done, morph_done;   // persistent step: finished gain tiles, morphology bands
     uint32_t ginv;                    // persistent step and spans: 0x80000000 | inverse gain, once known
     uint32_t pick;                    // deferred tracking: root run of the largest component (or none)
@@ -252,7 +253,9 @@ hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const 
                            hipStream_t s, StageEvents ev = {});
 hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s,
                                 StageEvents ev = {});
-hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max_ops, int n_cu,
+// items: morphology items of each job when they are all the same (a span), 0
+// to look a band's job up in the table.
+hipError_t launch_morph(const Table *d_tab, int total_tiles, int items, int max_wd, int max_ops, int n_cu,
                         const Tuning &t, hipStream_t s, StageEvents ev = {});
 // serial: one workgroup takes the jobs in table order (consecutive frames of
 // one tracked stream); small: 256-thread workgroups, for a launch that runs

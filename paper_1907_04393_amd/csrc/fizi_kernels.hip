@@ -1652,22 +1652,25 @@ __device__ __forceinline__ uint32_t reserve_runs(Job *J, uint32_t n, uint32_t ca
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
 }
 
-// Closes a segment: its n runs join the run list, each pointing at its root.
-template <bool FLOW>
-__device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GLOBAL uint64_t *runs,
-                                              GLOBAL uint32_t *parent, GLOBAL uint32_t *index, uint32_t cap)
+// Unites the pairs a segment put off.
+__device__ __forceinline__ void unite_pairs(WaveLds &L)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    if (n == 0)
-        return;
-    const uint32_t base = reserve_runs(J, n, cap);
     const uint32_t np = L.npairs;
     for (uint32_t i = lane; i < np; i += kWave)
         unite_lds(L.par, L.pairs[i] & 0xFFFFu, L.pairs[i] >> 16);
     wave_sync();
     if (lane == 0)
         L.npairs = 0u;
-    for (uint32_t k = lane; k < n; k += kWave) {
+}
+
+// A segment's n runs join the run list from entry base on, each pointing at
+// its root.
+template <bool FLOW>
+__device__ __forceinline__ void store_segment(WaveLds &L, uint32_t n, uint32_t base, GLOBAL uint64_t *runs,
+                                              GLOBAL uint32_t *parent, GLOBAL uint32_t *index, uint32_t cap)
+{
+    for (uint32_t k = threadIdx.x & (kWave - 1); k < n; k += kWave) {
         const uint32_t st = L.start[k];
         const uint32_t r = find_lds(L.par, k);
         if (base + k < cap) {
@@ -1677,6 +1680,18 @@ __device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GL
         }
     }
     wave_sync();
+}
+
+// Closes a segment.
+template <bool FLOW>
+__device__ __forceinline__ void flush_segment(Job *J, WaveLds &L, uint32_t n, GLOBAL uint64_t *runs,
+                                              GLOBAL uint32_t *parent, GLOBAL uint32_t *index, uint32_t cap)
+{
+    if (n == 0)
+        return;
+    const uint32_t base = reserve_runs(J, n, cap);
+    unite_pairs(L);
+    store_segment<FLOW>(L, n, base, runs, parent, index, cap);
 }
 
 // Rows r0 .. r0 + kRawChunk - 1 of the raw mask, addresses clamped to rows 0 .. H - 1 and words below Wd. Values of clamped
@@ -1753,16 +1768,37 @@ __device__ __forceinline__ void halo_row(const BandOut &B, RunState<NC> &S, cons
     S.prev_in_seg = false;
 }
 
-// A final I_FIZI row with pixels (jrow per lane group): its runs and their
-// joins with the row above.
+// The joins of a row D (first pixel rowpx, per lane group) with the row P above
+// as pairs of run starts, from entry k of the frame's link list on (per lane).
 template <int NC, bool FLOW>
+__device__ __forceinline__ void band_links(const BandOut &B, const RowBits<NC> &P, const RowBits<NC> &D,
+                                           uint32_t rowpx, uint32_t k)
+{
+    const uint32_t upx = rowpx - (uint32_t)B.W;
+    touching_runs<NC>(P, D, [&](int c, bool from_d, int b, int t) {
+        const uint32_t wb = 64u * (uint32_t)(B.word + kWave * c);
+        const uint32_t a = from_d ? rowpx + wb + (uint32_t)b : upx + wb + (uint32_t)b;
+        const uint32_t o = from_d ? upx + (uint32_t)start_at<NC>(P, c, t, B.lg)
+                                  : rowpx + (uint32_t)start_at<NC>(D, c, t, B.lg);
+        if (k < B.link_cap) {
+            put<FLOW>(B.linkw + 2 * (size_t)k, a);
+            put<FLOW>(B.linkw + 2 * (size_t)k + 1, o);
+        }
+        ++k;
+    });
+}
+
+// A final I_FIZI row with pixels (jrow per lane group): its runs and their
+// joins with the row above. ONE: the band's runs are known to fit one segment
+// and its joins with the band above are written at the end (band_links).
+template <int NC, bool FLOW, bool ONE = false>
 __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveLds &L, const uint64_t *x, int jrow)
 {
     Job *J = B.J;
     const int lane = threadIdx.x & (kWave - 1);
     const int W = B.W, Wd = B.Wd, word = B.word;
     GLOBAL uint64_t *runs = B.runs;
-    GLOBAL uint32_t *parent = B.parent, *index = B.index, *linkw = B.linkw;
+    GLOBAL uint32_t *parent = B.parent, *index = B.index;
     const uint32_t cap = B.cap, link_cap = B.link_cap;
     RowBits<NC> &P = S.P;
     uint32_t &nseg = S.nseg, &prev_first = S.prev_first;
@@ -1770,19 +1806,19 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
     RowBits<NC> D;
     uint64_t en[NC];
     const uint32_t total = row_bits<NC>(D, x, Wd, en, B.lg);
-    if (nseg + total > (uint32_t)kSegRuns) {
+    if (!ONE && nseg + total > (uint32_t)kSegRuns) {
         // the open segment is full: close it, this row opens the next
         flush_segment<FLOW>(J, L, nseg, runs, parent, index, cap);
         nseg = 0;
         prev_in_seg = false;
     }
-    const bool direct = total > (uint32_t)kSegRuns;
+    const bool direct = !ONE && total > (uint32_t)kSegRuns;
     const uint32_t rowpx = (uint32_t)max(jrow, 0) * (uint32_t)W;
     // joins with a row above whose runs are not in the open segment (the
     // band above, a closed segment, or a row written directly) go to the
     // frame's link list as pairs of run starts
     uint32_t flag = 0u;
-    if (prev_valid && (!prev_in_seg || direct)) {
+    if (!ONE && prev_valid && (!prev_in_seg || direct)) {
         uint32_t cnt = 0;
         touching_runs<NC>(P, D, [&](int, bool, int, int) { ++cnt; });
         const uint32_t inc = wave_incl_scan(cnt);
@@ -1791,19 +1827,8 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
         if (lane == 0)
             base = atomicAdd(&J->nlinks, n);
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-        uint32_t k = base + inc - cnt;
-        const uint32_t upx = rowpx - (uint32_t)W;
-        touching_runs<NC>(P, D, [&](int c, bool from_d, int b, int t) {
-            const uint32_t wb = 64u * (uint32_t)(word + kWave * c);
-            const uint32_t a = from_d ? rowpx + wb + (uint32_t)b : upx + wb + (uint32_t)b;
-            const uint32_t o = from_d ? upx + (uint32_t)start_at<NC>(P, c, t, B.lg)
-                                      : rowpx + (uint32_t)start_at<NC>(D, c, t, B.lg);
-            if (k < link_cap) {
-                put<FLOW>(linkw + 2 * (size_t)k, a);
-                put<FLOW>(linkw + 2 * (size_t)k + 1, o);
-            }
-            ++k;
-        });
+        const uint32_t k = base + inc - cnt;
+        band_links<NC, FLOW>(B, P, D, rowpx, k);
         if (base + n > link_cap) {
             // the list is full: the component stage joins this row to
             // the row above by reading I_FIZI
@@ -2022,8 +2047,8 @@ __device__ __forceinline__ void morph_band(Job *J, int band, WaveLds &L)
 // erosion leaves nothing then, and the closing nothing to close - store empty
 // rows and are done: background with noise, most bands of a frame.
 // Bound by the latency of the bands that hold the hand: 64 frames of 1920x1080
-// in 8-row bands take 25 us (35 streamed), the 64-stream batch in 16-row bands
-// 67 us (89), 16 frames of 1344x757 with two openings and closings 24 us (52),
+// in 8-row bands take 22 us (35 streamed), the 64-stream batch in 16-row bands
+// 67 us (89), 16 frames of 1344x757 with two openings and closings 21 us (52),
 // a frame of 320x240 4 us (8). R: band height; KT: stages the halo has rows
 // for; NC: words per lane.
 // One stage on rows from .. to of the N in registers. edge: the band's rows
@@ -2173,6 +2198,7 @@ __device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
     typedef uint32_t rows_t __attribute__((ext_vector_type(R)));
     rows_t lo[NC], hi[NC];
     uint32_t full = 0;                          // bit j: row j has pixels
+    uint32_t nstart = 0;                        // run starts in the lane's words
 #pragma unroll
     for (int j = -1; j < R; ++j) {
         uint64_t orw = 0ull;
@@ -2189,8 +2215,15 @@ __device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
                 hi[q][j < 0 ? 0 : j] = (uint32_t)(v >> 32);
             }
         }
-        if (j >= 0 && __ballot(orw != 0ull) != 0ull)
-            full |= 1u << j;
+        if (j >= 0) {
+            if (__ballot(orw != 0ull) != 0ull)
+                full |= 1u << j;
+            uint32_t lc[NC], rc[NC];
+            row_carries<NC>(x[KT + 1 + j], Wd, 0u, lc, rc, lg);
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                nstart += (uint32_t)__popcll(x[KT + 1 + j][q] & ~((x[KT + 1 + j][q] << 1) | lc[q]));
+        }
     }
     if (!full)
         return;
@@ -2202,16 +2235,73 @@ __device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
 #pragma unroll
     for (int q = 0; q < NC; ++q)
         orw |= x[KT][q];
-    if ((full & 1u) && __ballot(orw != 0ull) != 0ull)
+    const bool halo = (full & 1u) && __ballot(orw != 0ull) != 0ull;
+    auto row_of = [&](int j, uint64_t (&v)[NC]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+            v[q] = ((uint64_t)hi[q][j] << 32) | lo[q][j];
+    };
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(nstart), kWave - 1);
+    if (total <= (uint32_t)kSegRuns) {
+        // one segment holds the band's runs: their places in the run list and
+        // those of the joins with the band above are reserved at once, ahead
+        // of the rows, so that the 2 us the device-scope atomic takes pass
+        // beside them
+        uint64_t v0[NC], en[NC];
+        row_of(0, v0);
+        uint32_t cnt = 0, inc = 0;
+        RowBits<NC> D0;
+        if (halo) {
+            (void)row_bits<NC>(S.P, x[KT], Wd, en, lg);
+            (void)row_bits<NC>(D0, v0, Wd, en, lg);
+            touching_runs<NC>(S.P, D0, [&](int, bool, int, int) { ++cnt; });
+            inc = wave_incl_scan(cnt);
+        }
+        const uint32_t nlink = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        unsigned long long at = 0;
+        if ((threadIdx.x & (kWave - 1)) == 0)
+            at = atomicAdd(reinterpret_cast<unsigned long long *>(&J->nruns),
+                           (unsigned long long)total | ((unsigned long long)nlink << 32));
+        int before = -2;                        // last row with runs
+#pragma unroll 1
+        for (uint32_t m = full; m; m &= m - 1u) {
+            const int j = __builtin_ctz(m);
+            uint64_t v[NC];
+            row_of(j, v);
+            if (j != before + 1)
+                S.prev_valid = false;
+            before = j;
+            run_row<NC, false, true>(B, S, L, v, y0 + j);
+        }
+        unite_pairs(L);
+        const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at),
+                       lbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+        if (nlink) {
+            row_of(0, v0);
+            (void)row_bits<NC>(S.P, x[KT], Wd, en, lg);
+            const uint32_t first = row_bits<NC>(D0, v0, Wd, en, lg);
+            band_links<NC, false>(B, S.P, D0, (uint32_t)max(y0, 0) * (uint32_t)B.W, lbase + inc - cnt);
+            if (lbase + nlink > B.link_cap) {
+                // the list is full: the component stage joins the row's runs
+                // to the row above by reading I_FIZI
+                for (uint32_t k = threadIdx.x & (kWave - 1); k < first; k += kWave)
+                    L.end[k] |= kLinkUp;
+                wave_sync();
+                if ((threadIdx.x & (kWave - 1)) == 0)
+                    atomicAdd(&J->nflag, 1u);
+            }
+        }
+        store_segment<false>(L, S.nseg, base, B.runs, B.parent, B.index, B.cap);
+        return;
+    }
+    if (halo)
         halo_row<NC>(B, S, x[KT]);
     int before = -1;                            // last row with runs
 #pragma unroll 1
     for (uint32_t m = full; m; m &= m - 1u) {
         const int j = __builtin_ctz(m);
         uint64_t v[NC];
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-            v[q] = ((uint64_t)hi[q][j] << 32) | lo[q][j];
+        row_of(j, v);
         if (j != before + 1)
             S.prev_valid = false;
         before = j;
@@ -2242,18 +2332,20 @@ __global__ __launch_bounds__(256) void k_morph(Table *__restrict__ T)
 }
 
 // Bands of R rows, or of the short height (the height is the job's: a graph
-// replays one kernel for steps of either).
+// replays one kernel for steps of either). A span's jobs have `items` each and
+// `total` in all; otherwise (items 0) both come from the table.
 template <int R, int KT, int NC>
-__global__ __launch_bounds__(256) void k_morph_regs(Table *__restrict__ T)
+__global__ __launch_bounds__(256) void k_morph_regs(Table *__restrict__ T, int total, int items)
 {
     __shared__ WaveLds s_wl[256 / kWave];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int nj = T->h.njobs;
-    const int total = T->h.mor_pre[nj];
+    const int nj = items ? 0 : T->h.njobs;
+    if (!items)
+        total = T->h.mor_pre[nj];
     for (int t = blockIdx.x * (256 / kWave) + wave; t < total; t += gridDim.x * (256 / kWave)) {
-        const int j = find_job(T->h.mor_pre, nj, t);
+        const int j = items ? t / items : find_job(T->h.mor_pre, nj, t);
         Job *J = &T->jobs[j];
-        const int item = t - T->h.mor_pre[j];
+        const int item = t - (items ? j * items : T->h.mor_pre[j]);
         if (NC == 2 && J->Wd > kWave) {
             if (J->band == kShortBand)
                 morph_regs<kShortBand, KT, 2>(J, item, s_wl[wave]);
@@ -2268,11 +2360,12 @@ __global__ __launch_bounds__(256) void k_morph_regs(Table *__restrict__ T)
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup of the component stage: 1024 threads when it runs on its own;
-// 256 when it runs beside a streaming kernel (pipelined steps), where a
-// 1024-thread workgroup, four waves on every SIMD of a CU, finds no room
-// until the streaming kernel drains.
-constexpr int kResolveThreads = 1024;
+// Workgroup of the component stage: 512 threads when it runs on its own (one
+// frame of 1920x1080 in 1024 / 512 / 256 threads: 9.9 / 8.9 / 8.0 us, eight of
+// 3840x2160 10.0 / 9.3 / 9.6, eight of 1920x1080 10.4 / 10.1 / 11.3); 256
+// beside a streaming kernel (pipelined steps), where a large workgroup finds
+// no room until the streaming kernel drains.
+constexpr int kResolveThreads = 512;
 constexpr int kResolveThreadsSmall = 256;
 constexpr int kMaxWaves = 16;
 
@@ -2320,39 +2413,83 @@ __device__ __forceinline__ void area_add(AreaTable &t, GLOBAL uint32_t *area, ui
     __hip_atomic_fetch_add(area + root, len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Workgroup reductions (thread 0 and then every thread see the result).
-__device__ __forceinline__ uint32_t wg_min_u32(uint32_t v, uint32_t *s_tmp)
+// Reductions by DPP: within rows of 16 lanes (shifts of 1, 2, 4, 8: lane 15 of a
+// row has its total), then across the rows (lane 63 has the wave's). Lanes a
+// move does not write contribute `none`. A step is a few instructions; as
+// shuffles through LDS, and with one thread walking the waves' results, the
+// largest component and the zone's sums took 6 of a component stage's 12 us.
+template <int CTRL, int ROWS, typename V, typename OP>
+__device__ __forceinline__ V dpp_step(V v, V none, OP op)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1)
-        v = min(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-    __syncthreads();
-    if (lane == 0)
-        s_tmp[wave] = v;
-    __syncthreads();
-    v = s_tmp[0];
-    for (int w = 1; w < nw; ++w)
-        v = min(v, s_tmp[w]);
-    return v;
+    if constexpr (sizeof(V) == 8) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)none, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(none >> 32), (int)(uint32_t)(v >> 32), CTRL,
+                                                                  ROWS, 0xF, false);
+        return op(v, ((unsigned long long)hi << 32) | lo);
+    } else {
+        return op(v, (V)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false));
+    }
 }
 
-__device__ __forceinline__ unsigned long long wg_max_u64(unsigned long long v, unsigned long long *s_tmp)
+template <typename V, typename OP>
+__device__ __forceinline__ V row_reduce(V v, V none, OP op)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const unsigned long long ov = __shfl_xor(v, o, kWave);
-        v = ov > v ? ov : v;
-    }
+    v = dpp_step<0x111, 0xF>(v, none, op);
+    v = dpp_step<0x112, 0xF>(v, none, op);
+    v = dpp_step<0x114, 0xF>(v, none, op);
+    return dpp_step<0x118, 0xF>(v, none, op);
+}
+
+template <typename V>
+__device__ __forceinline__ V from_lane(V v, int lane)
+{
+    if constexpr (sizeof(V) == 8)
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    else
+        return (V)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+template <typename V, typename OP>
+__device__ __forceinline__ V wave_reduce(V v, V none, OP op)
+{
+    v = row_reduce(v, none, op);
+    v = dpp_step<0x142, 0xA>(v, none, op);
+    v = dpp_step<0x143, 0xC>(v, none, op);
+    return from_lane(v, kWave - 1);
+}
+
+// Second half of a workgroup reduction: the at most 16 waves' results in s.
+template <typename V, typename OP>
+__device__ __forceinline__ V waves_reduce(const V *s, V none, OP op)
+{
+    const int lane = threadIdx.x & (kWave - 1), nw = blockDim.x / kWave;
+    return from_lane(row_reduce(lane < nw ? s[lane] : none, none, op), 15);
+}
+
+struct OpMin {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return b < a ? b : a; }
+};
+struct OpMax {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return b > a ? b : a; }
+};
+struct OpSum {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return a + b; }
+};
+
+// Workgroup reductions (every thread gets the result).
+template <typename V, typename OP>
+__device__ __forceinline__ V wg_reduce(V v, V none, OP op, V *s_tmp)
+{
+    v = wave_reduce(v, none, op);
     __syncthreads();
-    if (lane == 0)
-        s_tmp[wave] = v;
+    if ((threadIdx.x & (kWave - 1)) == 0)
+        s_tmp[threadIdx.x / kWave] = v;
     __syncthreads();
-    v = s_tmp[0];
-    for (int w = 1; w < nw; ++w)
-        v = s_tmp[w] > v ? s_tmp[w] : v;
-    return v;
+    return waves_reduce(s_tmp, none, op);
 }
 
 constexpr uint32_t kNoRoot = 0xFFFFFFFFu;
@@ -2370,27 +2507,17 @@ __device__ __forceinline__ Components largest_of(unsigned long long best, uint32
 {
     __shared__ unsigned long long s_u64[kMaxWaves];
     __shared__ uint32_t s_u32[kMaxWaves], s_root;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    unsigned long long all = best;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const unsigned long long ob = __shfl_xor(all, o, kWave);
-        all = ob > all ? ob : all;
-        count += (uint32_t)__shfl_xor((int)count, o, kWave);
-    }
-    if (lane == 0) {
-        s_u64[wave] = all;
-        s_u32[wave] = count;
+    unsigned long long all = wave_reduce(best, 0ull, OpMax());
+    count = wave_reduce(count, 0u, OpSum());
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_u64[threadIdx.x / kWave] = all;
+        s_u32[threadIdx.x / kWave] = count;
     }
     if (threadIdx.x == 0)
         s_root = kNoRoot;
     __syncthreads();
-    all = s_u64[0];
-    count = s_u32[0];
-    for (int w = 1; w < nw; ++w) {
-        all = s_u64[w] > all ? s_u64[w] : all;
-        count += s_u32[w];
-    }
+    all = waves_reduce(s_u64, 0ull, OpMax());
+    count = waves_reduce(s_u32, 0u, OpSum());
     // a key belongs to one component
     if (best == all && best != 0ull)
         s_root = root;
@@ -2408,8 +2535,8 @@ __device__ __forceinline__ unsigned long long size_key(uint32_t area, uint32_t f
 // largest component. In LDS: the run list, parents and joins are each read
 // once, all loads at once, and what follows waits for LDS only (in global
 // memory each step of a find and each union was a dependent access of 0.6 us:
-// one frame of 1920x1080 15.7 us against 12 here, 16 of 1280x720 12.5 against
-// 9.8, the 64-stream batch beside classify 134 against 43).
+// one frame of 1920x1080 15.7 us against 8.9 here, 16 of 1280x720 12.5 against
+// 9.5, the 64-stream batch beside classify 134 against 43).
 template <int C>
 __device__ __forceinline__ Components resolve_lds(Job *J, LdsRuns<C> &t, uint32_t nr, uint32_t nl)
 {
@@ -2473,7 +2600,7 @@ __device__ __forceinline__ Components resolve_lds(Job *J, LdsRuns<C> &t, uint32_
 // list (its flagged runs are joined by reading I_FIZI). Afterwards the areas
 // hold every root's area and each other run's parent is one of its ancestors
 // (see root_of).
-__device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uint32_t nr, uint32_t nl)
+__device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uint32_t nr, uint32_t nl, uint32_t nflag)
 {
     const int W = J->W, Wd = J->Wd;
     const GlobalForest f(J);
@@ -2493,7 +2620,7 @@ __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uin
         const uint64_t l = links[i];
         unite(f, index[(uint32_t)l], index[(uint32_t)(l >> 32)]);
     }
-    if (ld_dev(&J->nflag))
+    if (nflag)
         for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
             const uint64_t rv = f.runs[i];
             if (!((uint32_t)(rv >> 32) & kLinkUp))
@@ -2548,18 +2675,26 @@ __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uin
     return largest_of(best, root, count);
 }
 
-// Root run of the component of area >= amin covering pixel (tx, ty), or
-// kNoRoot (one thread; the forest is final).
-template <typename F>
-__device__ __forceinline__ uint32_t covering_root(const Job *J, const F &f, int tx, int ty, uint32_t amin)
+// The run covering pixel (tx, ty), or kNoRoot (one thread; it needs no forest).
+__device__ __forceinline__ uint32_t covering_run(const Job *J, int tx, int ty)
 {
     if (tx < 0 || tx >= J->W || ty < 0 || ty >= J->H)
         return kNoRoot;
     const GLOBAL uint64_t *row = G(J->fizi) + (size_t)ty * J->Wd;
     if (!((row[tx >> 6] >> (tx & 63)) & 1ull))
         return kNoRoot;
-    const uint32_t start = (uint32_t)ty * (uint32_t)J->W + (uint32_t)(prev_zero(row, tx) + 1);
-    const uint32_t r = root_of(f, G(J->index)[start]);
+    return G(J->index)[(uint32_t)ty * (uint32_t)J->W + (uint32_t)(prev_zero(row, tx) + 1)];
+}
+
+// Root run of the component of area >= amin covering pixel (tx, ty), or
+// kNoRoot (one thread; the forest is final).
+template <typename F>
+__device__ __forceinline__ uint32_t covering_root(const Job *J, const F &f, int tx, int ty, uint32_t amin)
+{
+    const uint32_t i = covering_run(J, tx, ty);
+    if (i == kNoRoot)
+        return kNoRoot;
+    const uint32_t r = root_of(f, i);
     return f.area(r) >= amin ? r : kNoRoot;
 }
 
@@ -2586,7 +2721,7 @@ __device__ __forceinline__ uint32_t nearest_root(const Job *J, const F &f, int t
     for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
         if (f.area(root_of(f, i)) >= amin)
             dmin = min(dmin, dist2(f.run(i)));
-    dmin = wg_min_u32(dmin, s_min);
+    dmin = wg_reduce(dmin, 0xFFFFFFFFu, OpMin(), s_min);
     if (dmin > r2)
         return kNoRoot;
     unsigned long long key = 0ull;
@@ -2600,25 +2735,26 @@ __device__ __forceinline__ uint32_t nearest_root(const Job *J, const F &f, int t
             key = k > key ? k : key;
         }
     }
-    key = wg_max_u64(key, s_key);
+    key = wg_reduce(key, 0ull, OpMax(), s_key);
     return key ? G(J->index)[0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull)] : kNoRoot;
 }
 
 // The tracked pick given the previous frame's centroid pixel (valid: it had
 // a hand): the covering component, else the nearest within the radius;
 // kNoRoot for the largest (whole workgroup).
+// cover: the run covering that pixel, or kNoRoot.
 template <typename F>
-__device__ __forceinline__ uint32_t tracked_pick(const Job *J, const F &f, bool valid, int tx, int ty)
+__device__ __forceinline__ uint32_t tracked_pick(const Job *J, const F &f, const TrackState &ts, uint32_t cover)
 {
-    __shared__ uint32_t s_pick;
     const uint32_t amin = (uint32_t)max(J->min_area, 0);
-    if (threadIdx.x == 0)
-        s_pick = valid ? covering_root(J, f, tx, ty, amin) : kNoRoot;
-    __syncthreads();
-    uint32_t pick = s_pick;
-    __syncthreads();
-    if (valid && pick == kNoRoot && J->track_r2 > 0)
-        pick = nearest_root(J, f, tx, ty, amin, J->track_r2);
+    uint32_t pick = kNoRoot;
+    if (cover != kNoRoot) {
+        const uint32_t r = root_of(f, cover);
+        if (f.area(r) >= amin)
+            pick = r;
+    }
+    if (ts.valid && pick == kNoRoot && J->track_r2 > 0)
+        pick = nearest_root(J, f, ts.x, ts.y, amin, J->track_r2);
     return pick;
 }
 
@@ -2635,7 +2771,7 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
 {
     __shared__ unsigned long long s_u64[2][kMaxWaves];
     __shared__ uint32_t s_u32[4][kMaxWaves];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int W = J->W, Wd = J->Wd;
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
     ZoneStats z{0, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, 0};
@@ -2662,15 +2798,12 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
             }
         }
     }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        z.sx += __shfl_xor(z.sx, o, kWave);
-        z.sy += __shfl_xor(z.sy, o, kWave);
-        z.x0 = min(z.x0, (uint32_t)__shfl_xor((int)z.x0, o, kWave));
-        z.y0 = min(z.y0, (uint32_t)__shfl_xor((int)z.y0, o, kWave));
-        z.x1 = max(z.x1, (uint32_t)__shfl_xor((int)z.x1, o, kWave));
-        z.y1 = max(z.y1, (uint32_t)__shfl_xor((int)z.y1, o, kWave));
-    }
+    z.sx = wave_reduce(z.sx, 0ull, OpSum());
+    z.sy = wave_reduce(z.sy, 0ull, OpSum());
+    z.x0 = wave_reduce(z.x0, 0xFFFFFFFFu, OpMin());
+    z.y0 = wave_reduce(z.y0, 0xFFFFFFFFu, OpMin());
+    z.x1 = wave_reduce(z.x1, 0u, OpMax());
+    z.y1 = wave_reduce(z.y1, 0u, OpMax());
     __syncthreads();
     if (lane == 0) {
         s_u64[0][wave] = z.sx;
@@ -2681,15 +2814,14 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
         s_u32[3][wave] = z.y1;
     }
     __syncthreads();
-    if (threadIdx.x == 0)
-        for (int w = 1; w < nw; ++w) {
-            z.sx += s_u64[0][w];
-            z.sy += s_u64[1][w];
-            z.x0 = min(z.x0, s_u32[0][w]);
-            z.y0 = min(z.y0, s_u32[1][w]);
-            z.x1 = max(z.x1, s_u32[2][w]);
-            z.y1 = max(z.y1, s_u32[3][w]);
-        }
+    if (wave == 0) {
+        z.sx = waves_reduce(s_u64[0], 0ull, OpSum());
+        z.sy = waves_reduce(s_u64[1], 0ull, OpSum());
+        z.x0 = waves_reduce(s_u32[0], 0xFFFFFFFFu, OpMin());
+        z.y0 = waves_reduce(s_u32[1], 0xFFFFFFFFu, OpMin());
+        z.x1 = waves_reduce(s_u32[2], 0u, OpMax());
+        z.y1 = waves_reduce(s_u32[3], 0u, OpMax());
+    }
     return z;
 }
 
@@ -2749,13 +2881,14 @@ __device__ __forceinline__ uint8_t debounce_click(uint32_t *state, bool present,
 // tracking chain (k_track_chain) settles the tracked frames of the launch in
 // order afterwards.
 template <typename F>
-__device__ __forceinline__ void resolve_zone(Job *J, const F &f, const Components &c, uint32_t inv, bool defer)
+__device__ __forceinline__ void resolve_zone(Job *J, const F &f, const Components &c, uint32_t inv, bool defer,
+                                             const TrackState &was, uint32_t cover)
 {
     GLOBAL uint64_t *hand = J->hand ? G(J->hand) : nullptr;
     TrackState *ts = J->track;
     uint32_t pick = kNoRoot;
     if (ts && !defer)
-        pick = tracked_pick(J, f, ts->valid != 0, ts->x, ts->y);
+        pick = tracked_pick(J, f, was, cover);
     const bool tracked = pick != kNoRoot;
     const uint32_t A = tracked ? f.area(pick) : c.area;
     const uint32_t kstar = tracked ? pick : c.root;
@@ -2790,13 +2923,23 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
 {
     Job *J = &T->jobs[j];
     const uint32_t inv = same_launch ? job_gain(J, true) : frame_gain(J);
-    const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap), nl = min(ld_dev(&J->nlinks), J->link_cap);
+    const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap), nl = min(ld_dev(&J->nlinks), J->link_cap),
+                   nflag = ld_dev(&J->nflag);
     if (J->hand) {
         GLOBAL uint64_t *hand = G(J->hand);
         for (int i = threadIdx.x; i < J->H * J->Wd; i += blockDim.x)
             hand[i] = 0ull;
     }
-    if (nr <= (uint32_t)C && ld_dev(&J->nflag) == 0u) {
+    // a tracked frame's covering run, looked up beside the forest's loads by
+    // the last wave's first lane
+    __shared__ uint32_t s_cover;
+    TrackState was{};
+    if (J->track && !defer) {
+        was = *J->track;
+        if (threadIdx.x == blockDim.x - kWave)
+            s_cover = was.valid ? covering_run(J, was.x, was.y) : kNoRoot;
+    }
+    if (nr <= (uint32_t)C && nflag == 0u) {
         const LdsForest<C> f{lds.runs};
         const Components c = resolve_lds(J, lds.runs, nr, nl);
         if (defer) {
@@ -2807,11 +2950,11 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
                 st_wg(g.areas + i, lds.runs.area[i]);
             }
         }
-        resolve_zone(J, f, c, inv, defer);
+        resolve_zone(J, f, c, inv, defer, was, s_cover);
     } else {
         const GlobalForest f(J);
-        const Components c = resolve_global(J, lds.areas, nr, nl);
-        resolve_zone(J, f, c, inv, defer);
+        const Components c = resolve_global(J, lds.areas, nr, nl, nflag);
+        resolve_zone(J, f, c, inv, defer, was, s_cover);
     }
     __syncthreads();
 }
@@ -3237,7 +3380,7 @@ hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job
     return hipGetLastError();
 }
 
-hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max_ops, int n_cu,
+hipError_t launch_morph(const Table *d_tab, int total_tiles, int items, int max_wd, int max_ops, int n_cu,
                         const Tuning &t, hipStream_t s, StageEvents ev)
 {
     if (total_tiles <= 0)
@@ -3249,21 +3392,21 @@ hipError_t launch_morph(const Table *d_tab, int total_tiles, int max_wd, int max
     if (morph_in_regs(t.morph_rows, max_wd, max_ops)) {
         if (t.morph_rows == 16) {
             if (wide)
-                FIZI_LAUNCH((k_morph_regs<16, 4, 2>), grid, 256, 0, s, ev, tab);
+                FIZI_LAUNCH((k_morph_regs<16, 4, 2>), grid, 256, 0, s, ev, tab, total_tiles, items);
             else if (!deep)
-                FIZI_LAUNCH((k_morph_regs<16, 4, 1>), grid, 256, 0, s, ev, tab);
+                FIZI_LAUNCH((k_morph_regs<16, 4, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
             else if (max_ops <= 8)
-                FIZI_LAUNCH((k_morph_regs<16, 8, 1>), grid, 256, 0, s, ev, tab);
+                FIZI_LAUNCH((k_morph_regs<16, 8, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
             else
-                FIZI_LAUNCH((k_morph_regs<16, 12, 1>), grid, 256, 0, s, ev, tab);
+                FIZI_LAUNCH((k_morph_regs<16, 12, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
         } else if (wide) {
-            FIZI_LAUNCH((k_morph_regs<8, 4, 2>), grid, 256, 0, s, ev, tab);
+            FIZI_LAUNCH((k_morph_regs<8, 4, 2>), grid, 256, 0, s, ev, tab, total_tiles, items);
         } else if (!deep) {
-            FIZI_LAUNCH((k_morph_regs<8, 4, 1>), grid, 256, 0, s, ev, tab);
+            FIZI_LAUNCH((k_morph_regs<8, 4, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
         } else if (max_ops <= 8) {
-            FIZI_LAUNCH((k_morph_regs<8, 8, 1>), grid, 256, 0, s, ev, tab);
+            FIZI_LAUNCH((k_morph_regs<8, 8, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
         } else {
-            FIZI_LAUNCH((k_morph_regs<8, 12, 1>), grid, 256, 0, s, ev, tab);
+            FIZI_LAUNCH((k_morph_regs<8, 12, 1>), grid, 256, 0, s, ev, tab, total_tiles, items);
         }
         return hipGetLastError();
     }
