@@ -339,7 +339,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         J.out = d_pointers ? d_pointers + f0 : internal;
         J.hout = c->d_ring;
         J.frame_index = fbase;
-        SpanJobs S = span_jobs(J, k, reinterpret_cast<uint32_t *>(c->d + c->L.arrived), c->tune);
+        SpanJobs S = span_jobs(J, k, reinterpret_cast<uint32_t *>(c->d + c->L.arrived));
         S.base = reinterpret_cast<const Job *>(c->d + c->L.base);
         if (!d_fizi_bits)
             S.fizi_words = c->L.slot_stride / sizeof(uint64_t);
@@ -347,7 +347,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         S.raw_bytes = pipelined && par ? c->L.raw2_stride : c->L.slot_stride;
         S.ring_mask = kRing - 1;
         Table *tab = take_table(c);
-        FIZI_TRY(span_front(tab, S, J, c->tune, c->n_cu, s, &c->clk));
+        FIZI_TRY(span_front(tab, S, J, c->n_cu, s, &c->clk));
         // the stream the chunk's back half goes to
         hipStream_t bs = s;
         if (pipelined) {

@@ -151,9 +151,8 @@ int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int ma
 
 // The same halves for consecutive frames of one stream (a context's launch):
 // the gain kernel builds the table. first: the first frame's job on the host.
-SpanJobs span_jobs(const Job &first, int n, uint32_t *arrived, const Tuning &t);
-int span_front(Table *d_tab, const SpanJobs &S, const Job &first, const Tuning &t, int n_cu, hipStream_t s,
-               StageClock *clk);
+SpanJobs span_jobs(const Job &first, int n, uint32_t *arrived);
+int span_front(Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s, StageClock *clk);
 int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &t, int n_cu, hipStream_t s,
               StageClock *clk, bool beside);
 

@@ -401,11 +401,11 @@ int device_cu_count(int *device, int *n_cu)
     return FIZI_OK;
 }
 
-SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived, const Tuning &t)
+SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived)
 {
     SpanJobs S{};
     const size_t px = (size_t)J.W * J.H;
-    const int ctile = cls_tile_px(t), bands = (J.H + J.band - 1) / J.band, per = 64 / J.mgroup;
+    const int bands = (J.H + J.band - 1) / J.band, per = 64 / J.mgroup;
     S.frame = J.frame;
     S.frame_bytes = px * 3;
     S.raw = J.raw;
@@ -423,7 +423,6 @@ SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived, const Tuning &t)
     S.rs = J.rs;
     S.band = J.band;
     S.mgroup = J.mgroup;
-    S.cls_tiles = (int)((px + ctile - 1) / ctile);
     S.mor_items = (bands + per - 1) / per;
     S.glo = J.glo;
     S.ghi = J.ghi;
@@ -432,17 +431,11 @@ SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived, const Tuning &t)
     return S;
 }
 
-int span_front(Table *d_tab, const SpanJobs &S, const Job &first, const Tuning &t, int n_cu, hipStream_t s,
-               StageClock *clk)
+int span_front(Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s, StageClock *clk)
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
     FIZI_HIP(launch_gain_span(d_tab, S, s, ev(FIZI_STAGE_GAIN)));
-    // a single frame keeps k_classify (1920x1080: 8.7 us against 9.8: nothing
-    // to share the box between)
-    if (S.n == 1)
-        FIZI_HIP(launch_classify(d_tab, S.cls_tiles, n_cu, t, s, ev(FIZI_STAGE_CLASSIFY)));
-    else
-        FIZI_HIP(launch_classify_span(d_tab, S, first, n_cu, s, ev(FIZI_STAGE_CLASSIFY)));
+    FIZI_HIP(launch_classify_span(d_tab, S, first, n_cu, s, ev(FIZI_STAGE_CLASSIFY)));
     return FIZI_OK;
 }
 
@@ -465,7 +458,7 @@ int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, cons
         Job J;
         fill_job(m, t.morph_rows, J, false);
         J.frame = frames + (size_t)f0 * px * 3;
-        SpanJobs S = span_jobs(J, k, arrived, t);
+        SpanJobs S = span_jobs(J, k, arrived);
         S.make_yref = reset && f0 == 0;
         FIZI_HIP(launch_gain_span(d_tab, S, s));
         const LearnSpan L{J.frame, px * 3, masks ? masks + (size_t)f0 * (px / 64) : nullptr, m.bgmin, m.bgmax,

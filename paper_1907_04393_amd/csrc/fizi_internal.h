@@ -224,7 +224,7 @@ struct SpanJobs {
     uint32_t ring_mask;
     int32_t n, W, H, rs;
     int32_t band, mgroup;
-    int32_t cls_tiles, mor_items;       // tiles of one frame
+    int32_t mor_items;                  // morphology items of one frame
     int32_t glo, ghi;
     uint32_t *arrived;                  // one count per frame (kArrivedStride), 0 between launches
     int32_t make_yref;                  // learning: the reference is frame 0, written to yref

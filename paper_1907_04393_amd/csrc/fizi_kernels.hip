@@ -197,8 +197,9 @@ __device__ __forceinline__ uint32_t wave_job_gain(const Job *J)
     return wave_gain(G(J->num)[threadIdx.x & (kWave - 1)], J->glo, J->ghi);
 }
 
-// A frame's inverse gain after the gain kernel: k_gain_span leaves it in the
-// job, after k_gain (batch steps) each wave takes it from the sums.
+// A frame's inverse gain after the gain kernel, where either may have run:
+// k_gain_span leaves it in the job, after k_gain (batch steps) each wave takes
+// it from the sums.
 constexpr uint32_t kGainKnown = 0x80000000u;
 
 __device__ __forceinline__ uint32_t frame_gain(const Job *J)
@@ -560,11 +561,10 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     // stores
     J->nruns = J->flags = J->nlinks = J->nflag = 0u;
     J->gain_done = J->morph_done = J->pick = 0u;
-    T->h.cls_pre[i + 1] = (i + 1) * S.cls_tiles;
     T->h.mor_pre[i + 1] = (i + 1) * S.mor_items;
     if (i == 0) {
         T->h.njobs = S.n;
-        T->h.cls_pre[0] = T->h.mor_pre[0] = 0;
+        T->h.mor_pre[0] = 0;
     }
 }
 
@@ -1005,7 +1005,7 @@ __device__ __forceinline__ void classify_tiles(Table *__restrict__ T, int nj, co
         while (s_pre[j + 1] <= t)
             ++j;
         if (j != jinv) {
-            inv = frame_gain(&T->jobs[j]);
+            inv = wave_job_gain(&T->jobs[j]);
             jinv = j;
         }
         classify_tile<ITERS>(T, j, t - s_pre[j], inv);
@@ -1031,9 +1031,13 @@ __global__ __launch_bounds__(256) void k_classify(Table *__restrict__ T)
 // box when Lo <= x <= Hi, Lo = max(bgmin - delta, 0) 2^16 and Hi the last x
 // of the upper bound (none when bgmax + delta >= 255: the correction
 // saturates there): one multiply-add and one unsigned compare of x - Lo
-// against Hi - Lo per channel. A frame on its own (k_classify) also takes the
-// whole unpacking of the model: 29 instructions per pixel in all, against 9
-// here plus the box (170 per lane) and the pixels outside it.
+// against Hi - Lo per channel. Frame by frame (k_classify) the model is
+// unpacked each time: 29 instructions per pixel in all, against 9 here plus
+// the box (170 per lane) and the pixels outside it.
+// A call of one frame takes it too: nothing to share the box between, but no
+// table lookups before the loads and a workgroup per 1024 pixels (k_classify
+// with 4 x 1024 before: 320x240 7.4 -> 3.5 us, 1920x1080 8.3 -> 5.9,
+// 3840x2160 16.3 -> 15.0, 7680x4320 46.3 -> 46.4).
 // Bound by HBM and the VALU together: 64 frames of 1920x1080 (398 MB) take 78
 // us (174 us frame by frame), moving 5.6 TB/s with the VALU two thirds busy.
 struct Box4 {

@@ -56,6 +56,13 @@ def test_ends_of_the_thresholds(delta, S, lo, hi, kind):
     _check(128, 13, 7, delta + S, chunk=7, bg_delta=delta, gray_S=S, gain_lo_q16=lo, gain_hi_q16=hi, **KINDS[kind])
 
 
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("W,H,chunk", [(64, 1, 8), (320, 3, 1), (704, 29, 1), (1920, 11, 8)])
+def test_one_frame(W, H, chunk, kind):
+    """One frame in a call, and calls cut into chunks of one frame."""
+    _check(W, H, 1 if chunk > 1 else 3, W + H, chunk=chunk, **KINDS[kind])
+
+
 def test_many_frames_take_the_largest_share():
     """Enough tiles that a workgroup takes 16 frames (7 workgroups per CU)."""
     _check(1920, 1080, 17, 5, chunk=17)
