@@ -355,7 +355,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
             FIZI_HIP(hipStreamWaitEvent(c->side, c->cls_ev[par], 0));
             bs = c->side;
         }
-        FIZI_TRY(span_back(tab, S, morph_ops(c->m.p), c->tune, c->n_cu, bs, &c->clk, pipelined));
+        FIZI_TRY(span_back(tab, S, J, morph_ops(c->m.p), c->tune, c->n_cu, bs, &c->clk, pipelined));
         // the ring holds a chunk's pointers once its back half is done
         fizi_ctx::Rec &r = c->recs[c->next_rec];
         c->next_rec = (c->next_rec + 1) % kRecs;

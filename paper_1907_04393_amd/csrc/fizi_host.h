@@ -153,7 +153,7 @@ int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int ma
 // the gain kernel builds the table. first: the first frame's job on the host.
 SpanJobs span_jobs(const Job &first, int n, uint32_t *arrived);
 int span_front(Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipStream_t s, StageClock *clk);
-int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &t, int n_cu, hipStream_t s,
-              StageClock *clk, bool beside);
+int span_back(const Table *d_tab, const SpanJobs &S, const Job &first, int max_ops, const Tuning &t, int n_cu,
+              hipStream_t s, StageClock *clk, bool beside);
 
 }  // namespace fizi

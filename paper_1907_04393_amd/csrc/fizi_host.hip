@@ -439,13 +439,34 @@ int span_front(Table *d_tab, const SpanJobs &S, const Job &first, int n_cu, hipS
     return FIZI_OK;
 }
 
-int span_back(const Table *d_tab, const SpanJobs &S, int max_ops, const Tuning &t, int n_cu, hipStream_t s,
-              StageClock *clk, bool beside)
+int span_back(const Table *d_tab, const SpanJobs &S, const Job &first, int max_ops, const Tuning &t, int n_cu,
+              hipStream_t s, StageClock *clk, bool beside)
 {
     auto ev = [&](int st) { return clk ? clk->next(st) : StageEvents{}; };
     FIZI_HIP(launch_morph(d_tab, S.n * S.mor_items, S.mor_items, S.W / 64, max_ops, n_cu, t, s, ev(FIZI_STAGE_MORPH)));
     // tracked consecutive frames are resolved in order
-    FIZI_HIP(launch_resolve(d_tab, S.n, s, ev(FIZI_STAGE_RESOLVE), S.n > 1 && S.track != nullptr, beside));
+    const bool tracked = S.n > 1 && S.track != nullptr;
+    ChainSpan C{};
+    if (tracked) {
+        C.out = S.out;
+        C.ring = S.ring;
+        C.track = S.track;
+        C.fizi = S.fizi;
+        C.fizi_words = S.fizi_words;
+        C.parent = first.parent;
+        C.index = first.index;
+        C.slot_bytes = S.slot_bytes;
+        C.frame_index = S.frame_index;
+        C.ring_mask = S.ring_mask;
+        C.run_cap = first.run_cap;
+        C.amin = (uint32_t)std::max(first.min_area, 0);
+        C.r2 = first.track_r2;
+        C.n = S.n;
+        C.W = S.W;
+        C.H = S.H;
+        C.debounce = first.debounce;
+    }
+    FIZI_HIP(launch_resolve(d_tab, S.n, s, ev(FIZI_STAGE_RESOLVE), tracked ? &C : nullptr, beside));
     return FIZI_OK;
 }
 
@@ -487,7 +508,7 @@ int run_back(const Table *d_tab, const Table &h, int njobs, int max_jobs, int ma
     const int big = INT_MAX / 2;
     FIZI_HIP(launch_morph(d_tab, fixed_grid ? big : h.h.mor_pre[njobs], 0, max_wd, max_ops, n_cu, t, s,
                           ev(FIZI_STAGE_MORPH)));
-    FIZI_HIP(launch_resolve(d_tab, fixed_grid ? max_jobs : njobs, s, ev(FIZI_STAGE_RESOLVE), false, beside));
+    FIZI_HIP(launch_resolve(d_tab, fixed_grid ? max_jobs : njobs, s, ev(FIZI_STAGE_RESOLVE), nullptr, beside));
     return FIZI_OK;
 }
 

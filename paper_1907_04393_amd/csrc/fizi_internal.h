@@ -242,6 +242,21 @@ struct LearnSpan {
     int32_t n, reset;
 };
 
+// Consecutive tracked frames of one stream for the tracking chain: frame j's
+// outputs and forest follow the first one's by the strides given, so that the
+// chain's loads need no job looked up before them.
+struct ChainSpan {
+    fizi_pointer *out, *ring;           // as SpanJobs
+    TrackState *track;
+    const uint64_t *fizi;
+    size_t fizi_words;
+    const uint32_t *parent, *index;     // of the first frame; run_cap parents, then the areas
+    size_t slot_bytes;
+    uint64_t frame_index;
+    uint32_t ring_mask, run_cap, amin, r2;
+    int32_t n, W, H, debounce;
+};
+
 // Kernel launchers (fizi_kernels.hip). Each returns the hipError_t of its launch.
 hipError_t launch_gain(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                        hipStream_t s, StageEvents ev = {});
@@ -260,7 +275,7 @@ hipError_t launch_morph(const Table *d_tab, int total_tiles, int items, int max_
 // serial: one workgroup takes the jobs in table order (consecutive frames of
 // one tracked stream); small: 256-thread workgroups, for a launch that runs
 // beside a streaming kernel.
-hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev = {}, bool serial = false,
+hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev = {}, const ChainSpan *chain = nullptr,
                           bool small = false);
 hipError_t launch_persistent(const Table *d_tab, int max_wd, int max_ops, int n_cu, const Tuning &t,
                              uint8_t *persist, hipStream_t s, StageEvents ev = {});
