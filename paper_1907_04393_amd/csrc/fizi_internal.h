@@ -202,15 +202,16 @@ struct StageEvents {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, s, __VA_ARGS__);                \
     } while (0)
 
+// Words between the arrival counts of two frames (a cache line each: sharing
+// lines cost 6 us over 64 frames)
+constexpr int kArrivedStride = 32;
+
 // A launch over n consecutive frames of one stream: the fields of its first
 // job that change from call to call, and the strides to the next ones. What
 // does not change lies in device memory (base: a job of the stream, its
 // scratch arrays those of frame slot 0). The gain kernel writes the job table
 // from both, so that nothing is uploaded. Kernel arguments are read from host
 // memory, so they are kept few: 700 bytes of them cost 8 to 15 us a launch.
-// words between the arrival counts of two frames (a cache line each: sharing
-// lines cost 6 us over 64 frames)
-constexpr int kArrivedStride = 32;
 struct SpanJobs {
     const Job *base;                    // null when learning: no table is written
     const uint8_t *frame;

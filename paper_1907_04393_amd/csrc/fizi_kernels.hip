@@ -12,14 +12,18 @@
 //   k_classify   gain correction (or thresholds scaled by the gain), I_R1
 //                (outside the learned box), I_R2 (not gray), I_R3 (skin hue),
 //                their AND, packed to bits by DPP row merges (Sections 3.1,
-//                3.2); HBM-bound, 4 pixels per lane
-//   k_morph      opening then closing with a 3x3 square, streamed through a
-//                register pipeline of bit rows (64 pixels per lane word), then
-//                runs and band-local components in LDS (Section 3.1, last
-//                paragraph)
-//   k_resolve    8-connected components by union-find over runs, hand-zone
-//                selection (largest, or tracked), the pointer (Section 2,
-//                Mouse module)
+//                3.2); HBM-bound, 4 pixels per lane. Frames of many streams
+//   k_classify_span  the same for consecutive frames of one stream, the box
+//                of a lane's pixels in registers across them
+//   k_morph_regs opening then closing with a 3x3 square on bands of bit rows
+//                held in registers (64 pixels per lane word), then runs and
+//                band-local components in LDS (Section 3.1, last paragraph)
+//   k_morph      the same streamed through a register pipeline, for taller
+//                bands and for wide frames with many stages
+//   k_resolve    8-connected components by union-find over runs (in LDS where
+//                a frame's runs fit), hand-zone selection (largest, or
+//                tracked), the pointer (Section 2, Mouse module)
+//   k_track_chain  settles the tracked frames of a launch in order
 //   k_flow       the persistent form of one step: gain tiles and row bands
 //                from one ordered queue, with bounded waits
 #include <hip/hip_ext.h>
