@@ -26,7 +26,7 @@ struct fizi_batch {
     hipStream_t cap = nullptr;                 // capture stream for graphs
     hipGraphExec_t graph[kTabSlots] = {};
     uint8_t *persist = nullptr;                // fused-kernel barrier state
-    uint32_t *arrived = nullptr;               // gain counts of the learning launches
+    uint32_t *arrived = nullptr;               // gain scratch of the learning launches
     hipEvent_t order_ev = nullptr;
     hipStream_t last_stream = nullptr;
     bool have_last = false;
@@ -82,7 +82,7 @@ BatchLayout batch_layout(int32_t n, const fizi_geom *geoms, const fizi_params *p
     L.persist = off;
     off += align256(persist_state_bytes());
     L.arrived = off;
-    off += align256(kArrivedWords * sizeof(uint32_t));
+    off += align256(kGainScratchBytes);
     L.model.resize(n);
     L.slot.resize(n);
     L.raw2.resize(n);

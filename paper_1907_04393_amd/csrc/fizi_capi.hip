@@ -13,7 +13,7 @@ namespace {
 constexpr int kRing = 65536;   // pointers kept for get_pointer (a power of two)
 constexpr int kRecs = 64;
 
-// State block: model | job tables | base job | gain counts | chunk
+// State block: model | job tables | base job | gain scratch | chunk
 // pointers | chunk scratch slots | a second raw-mask buffer per slot (consecutive chunks of a call alternate
 // between the two, so that a chunk's classify never writes the bits the
 // previous chunk's morphology is reading).
@@ -32,7 +32,7 @@ CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
     L.base = off;
     off += align256(sizeof(Job));
     L.arrived = off;
-    off += align256(kArrivedWords * sizeof(uint32_t));
+    off += align256(kGainScratchBytes);
     L.ptrs = off;
     off += align256((size_t)chunk * sizeof(fizi_pointer));
     L.slot_stride = align256(slot_bytes(g));

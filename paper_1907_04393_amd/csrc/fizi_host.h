@@ -41,9 +41,6 @@ HueTest make_hue(int a1, int a2);
 Tuning tuning_for(int max_width, int max_ops, bool batch);
 int morph_ops(const fizi_params &p);
 
-// Arrival counts of the gain kernel, for as many frames as a launch may have.
-constexpr size_t kArrivedWords = (size_t)kMaxJobs * kArrivedStride;
-
 // Background model of one stream (Section 3.1 (i)) and its reference
 // luminance rows (Section 3.2), inside a device block.
 struct Model {
@@ -131,7 +128,8 @@ int device_cu_count(int *device, int *n_cu);
 // frames[0], model starts empty) and, with masks, partial re-learning (n
 // I_FIZI bit masks whose set bits keep a frame's pixels out of the model).
 // d_tab: a table in device memory that no enqueued work on another stream
-// than s still reads; arrived: kArrivedWords words, 0 between launches.
+// than s still reads; arrived: the gain kernel's scratch, its kArrivedWords
+// counts 0 between launches.
 int learn_model(Model &m, Table *d_tab, uint32_t *arrived, const Tuning &t, const uint8_t *frames, int n, int reset,
                 hipStream_t s, StageClock *clk, const uint64_t *masks = nullptr);
 

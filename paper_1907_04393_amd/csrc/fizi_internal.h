@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include "fizi.h"
+#include "fizi_shapes.h"
 
 namespace fizi {
 
@@ -99,11 +100,10 @@ struct Job {
     int32_t lum2;              // over-exposure filter: 2 lum_hi, 0 when off
     HueTest hue;
     // accumulators (zero when the table is uploaded)
-    // gain sums over usable sampled pixels, spread over kGainSlots slots:
-    // tiles of an uploaded table add to slot tile % kGainSlots (fewer
-    // same-address atomics), workgroup p of a span's frame stores slot p
-    // (32 bits hold a slot's share of the largest frame: 2^26 pixels of at
-    // most 1020, 2.1e9)
+    // gain sums over usable sampled pixels (tables uploaded by a batch):
+    // tile t adds to slot t % kGainSlots (fewer same-address atomics); 32 bits
+    // hold a slot's share of the largest frame, 2^21 pixels of at most 1020
+    // (64 tiles of 2^15). Spans sum in 64 bits elsewhere (SpanJobs).
     alignas(8) uint32_t num[kGainSlots];
     uint32_t den[kGainSlots];
     uint32_t nruns, nlinks;           // reserved together by one 64-bit add where both are known
@@ -202,9 +202,13 @@ struct StageEvents {
             hipLaunchKernelGGL(kern, dim3(grid), dim3(block), lds, s, __VA_ARGS__);                \
     } while (0)
 
-// Words between the arrival counts of two frames (a cache line each: sharing
-// lines cost 6 us over 64 frames)
+// Scratch of the gain kernel of spans: per frame an arrival count (a cache
+// line each: sharing lines cost 6 us over 64 frames), 0 between launches, then
+// the launch's partial sums, reference and frame luminance of part p of frame
+// i at pair i parts + p.
 constexpr int kArrivedStride = 32;
+constexpr size_t kArrivedWords = (size_t)kMaxJobs * kArrivedStride;
+constexpr size_t kGainScratchBytes = kArrivedWords * sizeof(uint32_t) + (size_t)kGainParts * 2 * sizeof(GainSum);
 
 // A launch over n consecutive frames of one stream: the fields of its first
 // job that change from call to call, and the strides to the next ones. What
@@ -227,7 +231,7 @@ struct SpanJobs {
     int32_t band, mgroup;
     int32_t mor_items;                  // morphology items of one frame
     int32_t glo, ghi;
-    uint32_t *arrived;                  // one count per frame (kArrivedStride), 0 between launches
+    uint32_t *arrived;                  // gain scratch, see kArrivedStride
     int32_t make_yref;                  // learning: the reference is frame 0, written to yref
     HueTest hue;
 };

@@ -76,8 +76,8 @@ __device__ __forceinline__ void st_wg(GLOBAL uint32_t *p, uint32_t v)
 // run count) are read with device-scope atomic loads, which bypass the
 // scalar cache; in the persistent step they are written earlier in the same
 // launch.
-template <typename T>
-__device__ __forceinline__ T ld_dev(const T *p)
+template <typename P>
+__device__ __forceinline__ auto ld_dev(P p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -261,6 +261,65 @@ __device__ __forceinline__ T wave_sum(T v)
         v += __shfl_xor(v, o, kWave);
     return v;
 }
+
+// Reductions by DPP: within rows of 16 lanes (shifts of 1, 2, 4, 8: lane 15 of a
+// row has its total), then across the rows (lane 63 has the wave's). Lanes a
+// move does not write contribute `none`. A step is a few instructions; as
+// shuffles through LDS, and with one thread walking the waves' results, the
+// largest component and the zone's sums took 6 of a component stage's 12 us.
+template <int CTRL, int ROWS, typename V, typename OP>
+__device__ __forceinline__ V dpp_step(V v, V none, OP op)
+{
+    if constexpr (sizeof(V) == 8) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)none, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(none >> 32), (int)(uint32_t)(v >> 32), CTRL,
+                                                                  ROWS, 0xF, false);
+        return op(v, ((unsigned long long)hi << 32) | lo);
+    } else {
+        return op(v, (V)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false));
+    }
+}
+
+template <typename V, typename OP>
+__device__ __forceinline__ V row_reduce(V v, V none, OP op)
+{
+    v = dpp_step<0x111, 0xF>(v, none, op);
+    v = dpp_step<0x112, 0xF>(v, none, op);
+    v = dpp_step<0x114, 0xF>(v, none, op);
+    return dpp_step<0x118, 0xF>(v, none, op);
+}
+
+template <typename V>
+__device__ __forceinline__ V from_lane(V v, int lane)
+{
+    if constexpr (sizeof(V) == 8)
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    else
+        return (V)__builtin_amdgcn_readlane((int)v, lane);
+}
+
+template <typename V, typename OP>
+__device__ __forceinline__ V wave_reduce(V v, V none, OP op)
+{
+    v = row_reduce(v, none, op);
+    v = dpp_step<0x142, 0xA>(v, none, op);
+    v = dpp_step<0x143, 0xC>(v, none, op);
+    return from_lane(v, kWave - 1);
+}
+
+struct OpMin {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return b < a ? b : a; }
+};
+struct OpMax {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return b > a ? b : a; }
+};
+struct OpSum {
+    template <typename V>
+    __device__ __forceinline__ V operator()(V a, V b) const { return a + b; }
+};
 
 // Lane l receives lane l + n of its row of 16 lanes (0 past the row's end,
 // by the bound control): DPP row_shl:n.
@@ -516,9 +575,10 @@ __global__ void k_put_job(Job *__restrict__ d, Job J)
 // Gain of consecutive frames of one stream: workgroup (p, i) sums part p of
 // frame i's sampled pixels, items of 16 pixels (4 where the frames are only
 // 4-byte aligned) taken p blockDim + thread, + gridDim.x blockDim, ..., and
-// stores its sums in slot p of the frame's job: nothing to zero. The frame's
+// stores its sums, in 64 bits (see GainSum), as pair p of the frame: nothing
+// to zero. The frame's
 // last workgroup leaves the inverse gain in the job; every workgroup of the
-// kernels that follow would otherwise sum the slots and divide (6 us of
+// kernels that follow would otherwise sum the parts and divide (6 us of
 // classify over 64 frames, 22 us of minmax over 50). Its addresses come by
 // value, so that its loads wait for no table. Workgroup (0, n) writes the
 // jobs for the kernels that follow, thread i job i.
@@ -529,7 +589,7 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
 {
     Job *J = &T->jobs[i];
     const Job *B = S.base;
-    // every field but the gain sums, which other workgroups are writing
+    // every field but the accumulators
     const uint64_t *src = reinterpret_cast<const uint64_t *>(B);
     uint64_t *dst = reinterpret_cast<uint64_t *>(J);
     constexpr int kHead = (int)(offsetof(Job, num) / 8);
@@ -592,7 +652,7 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     const uint32_t W = (uint32_t)S.W, rows = (uint32_t)(S.H + S.rs - 1) / (uint32_t)S.rs;
     constexpr int kQ = WIDE ? 4 : 1;             // groups of four pixels per item
     const uint32_t per_row = W / (4 * kQ), items = rows * per_row;
-    uint32_t num = 0, den = 0;                   // at most 2^25 per lane
+    uint32_t num = 0, den = 0;                   // at most 2^25 per lane, 2^31 per wave
     for (uint32_t it = (uint32_t)part * blockDim.x + threadIdx.x; it < items; it += gridDim.x * blockDim.x) {
         const uint32_t row = it / per_row, g = it - row * per_row;
         const size_t fo = (size_t)row * (size_t)S.rs * W * 3u + 12u * kQ * g;
@@ -646,7 +706,7 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     if (wave != 0)
         return;
     // the first wave alone from here on, so that the others' places are free
-    uint32_t n = 0, d = 0;
+    GainSum n = 0, d = 0;
     for (int w = 0; w < (int)(blockDim.x / kWave); ++w) {
         n += s_num[w];
         d += s_den[w];
@@ -654,22 +714,25 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     // the frame's last workgroup turns the sums into its inverse gain: the
     // sums go through this XCD's L2, and are there before the count (which
     // wraps to 0 for the next launch)
-    Job *J = &T->jobs[i];
+    GLOBAL GainSum *sums = G(reinterpret_cast<GainSum *>(S.arrived + kArrivedWords)) + 2 * (size_t)i * gridDim.x;
     uint32_t before = 0;
     if (lane == 0) {
-        st_dev(G(&J->num[part]), n);
-        st_dev(G(&J->den[part]), d);
+        st_dev(sums + 2 * part, n);
+        st_dev(sums + 2 * part + 1, d);
         wait_own_memory();
         before = atomicInc(S.arrived + i * kArrivedStride, gridDim.x - 1);
     }
     if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != gridDim.x - 1)
         return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    // slots past the parts hold nothing of this launch
-    const uint32_t slot = (uint32_t)(lane & (kGainSlots - 1)) < gridDim.x ? ld_dev(&J->num[lane]) : 0u;
-    const uint32_t inv = wave_gain(slot, S.glo, S.ghi);
+    n = d = 0;
+    for (uint32_t p = lane; p < gridDim.x; p += kWave) {
+        n += ld_dev(sums + 2 * p);
+        d += ld_dev(sums + 2 * p + 1);
+    }
+    const uint32_t inv = inv_gain(wave_reduce(n, (GainSum)0, OpSum()), wave_reduce(d, (GainSum)0, OpSum()), S.glo, S.ghi);
     if (lane == 0)
-        J->ginv = kGainKnown | inv;
+        T->jobs[i].ginv = kGainKnown | inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -2420,52 +2483,6 @@ __device__ __forceinline__ void area_add(AreaTable &t, GLOBAL uint32_t *area, ui
     __hip_atomic_fetch_add(area + root, len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Reductions by DPP: within rows of 16 lanes (shifts of 1, 2, 4, 8: lane 15 of a
-// row has its total), then across the rows (lane 63 has the wave's). Lanes a
-// move does not write contribute `none`. A step is a few instructions; as
-// shuffles through LDS, and with one thread walking the waves' results, the
-// largest component and the zone's sums took 6 of a component stage's 12 us.
-template <int CTRL, int ROWS, typename V, typename OP>
-__device__ __forceinline__ V dpp_step(V v, V none, OP op)
-{
-    if constexpr (sizeof(V) == 8) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)none, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(none >> 32), (int)(uint32_t)(v >> 32), CTRL,
-                                                                  ROWS, 0xF, false);
-        return op(v, ((unsigned long long)hi << 32) | lo);
-    } else {
-        return op(v, (V)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false));
-    }
-}
-
-template <typename V, typename OP>
-__device__ __forceinline__ V row_reduce(V v, V none, OP op)
-{
-    v = dpp_step<0x111, 0xF>(v, none, op);
-    v = dpp_step<0x112, 0xF>(v, none, op);
-    v = dpp_step<0x114, 0xF>(v, none, op);
-    return dpp_step<0x118, 0xF>(v, none, op);
-}
-
-template <typename V>
-__device__ __forceinline__ V from_lane(V v, int lane)
-{
-    if constexpr (sizeof(V) == 8)
-        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) |
-               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
-    else
-        return (V)__builtin_amdgcn_readlane((int)v, lane);
-}
-
-template <typename V, typename OP>
-__device__ __forceinline__ V wave_reduce(V v, V none, OP op)
-{
-    v = row_reduce(v, none, op);
-    v = dpp_step<0x142, 0xA>(v, none, op);
-    v = dpp_step<0x143, 0xC>(v, none, op);
-    return from_lane(v, kWave - 1);
-}
-
 // Second half of a workgroup reduction: the at most 16 waves' results in s.
 template <typename V, typename OP>
 __device__ __forceinline__ V waves_reduce(const V *s, V none, OP op)
@@ -2473,19 +2490,6 @@ __device__ __forceinline__ V waves_reduce(const V *s, V none, OP op)
     const int lane = threadIdx.x & (kWave - 1), nw = blockDim.x / kWave;
     return from_lane(row_reduce(lane < nw ? s[lane] : none, none, op), 15);
 }
-
-struct OpMin {
-    template <typename V>
-    __device__ __forceinline__ V operator()(V a, V b) const { return b < a ? b : a; }
-};
-struct OpMax {
-    template <typename V>
-    __device__ __forceinline__ V operator()(V a, V b) const { return b > a ? b : a; }
-};
-struct OpSum {
-    template <typename V>
-    __device__ __forceinline__ V operator()(V a, V b) const { return a + b; }
-};
 
 // Workgroup reductions (every thread gets the result).
 template <typename V, typename OP>
@@ -3335,17 +3339,10 @@ template <int MODE>
 hipError_t launch_gain_span_mode(Table *tab, const SpanJobs &S, hipStream_t s, StageEvents ev)
 {
     const bool wide = reinterpret_cast<uintptr_t>(S.frame) % 16 == 0;
-    // waves per frame: one item per lane, but no more than about eight waves
-    // per SIMD over the launch; in parts of four waves, more (up to 16) where
-    // 32 parts would not hold them, and as many rounds as remain, the same
-    // for every part. Over 50 frames of 1920x1080 (learning) parts of 4 / 8 /
-    // 16 waves take 19 / 23 / 27 us, half the waves 22.
     const long long items = (long long)((S.H + S.rs - 1) / S.rs) * (S.W / (wide ? 16 : 4));
-    const int full = (int)((items + kWave - 1) / kWave), waves_f = std::min(full, std::max(32, 8192 / S.n));
-    const int parts = std::max(1, std::min(kGainSlots, (waves_f + 3) / 4));
-    const int most = std::min(16, (waves_f + parts - 1) / parts), rounds = (full + parts * most - 1) / (parts * most);
-    const int threads = kWave * ((full + parts * rounds - 1) / (parts * rounds));
-    const dim3 grid((unsigned)parts, (unsigned)S.n + (S.base ? 1u : 0u));
+    const GainShape g = gain_span_shape(items, S.n);
+    const int threads = g.threads;
+    const dim3 grid((unsigned)g.parts, (unsigned)S.n + (S.base ? 1u : 0u));
     if (S.make_yref) {
         if (wide)
             FIZI_LAUNCH((k_gain_span<MODE, true, true>), grid, threads, 0, s, ev, tab, S);
