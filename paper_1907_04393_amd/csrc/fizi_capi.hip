@@ -13,12 +13,12 @@ namespace {
 constexpr int kRing = 65536;   // pointers kept for get_pointer (a power of two)
 constexpr int kRecs = 64;
 
-// State block: model | job tables | base job | gain scratch | chunk
-// pointers | chunk scratch slots | a second raw-mask buffer per slot (consecutive chunks of a call alternate
+// State block: model | job tables | gain scratch | chunk pointers | chunk
+// scratch slots | a second raw-mask buffer per slot (consecutive chunks of a call alternate
 // between the two, so that a chunk's classify never writes the bits the
 // previous chunk's morphology is reading).
 struct CtxLayout {
-    size_t model, tables, base, arrived, ptrs, slots, slot_stride, raw2, raw2_stride, total;
+    size_t model, tables, arrived, ptrs, slots, slot_stride, raw2, raw2_stride, total;
 };
 
 CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
@@ -29,8 +29,6 @@ CtxLayout ctx_layout(const fizi_geom &g, const fizi_params &p, int chunk)
     off += align256(model_bytes(g, p));
     L.tables = off;
     off += TableRing::device_bytes();
-    L.base = off;
-    off += align256(sizeof(Job));
     L.arrived = off;
     off += align256(kGainScratchBytes);
     L.ptrs = off;
@@ -65,6 +63,9 @@ struct fizi_ctx {
     // its device-side address), so that no copy follows them
     fizi_pointer *h_ring = nullptr;
     fizi_pointer *d_ring = nullptr;
+    // behind them, what every job of this context has in common: read by the
+    // gain kernel, which builds the job tables (device-side address)
+    const Job *d_base = nullptr;
     // frames [f0, f1) are in the host pointer ring once `ev` (recorded after
     // the kernels that store them, default fences: the host reads what they
     // wrote) is done
@@ -222,10 +223,18 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
     c->tune = tuning_for(geom->width, morph_ops(*params), false);
     int rc = device_cu_count(&c->device, &c->n_cu);
     if (rc == FIZI_OK) {
-        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_ring), sizeof(fizi_pointer) * kRing,
+        static_assert(sizeof(fizi_pointer) * kRing % alignof(Job) == 0, "the base job follows the ring");
+        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_ring), sizeof(fizi_pointer) * kRing + sizeof(Job),
                                      hipHostMallocMapped | hipHostMallocCoherent);
         if (e == hipSuccess)
             e = hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_ring), c->h_ring, 0);
+        if (e == hipSuccess) {
+            Job J;
+            fill_job(c->m, c->tune.morph_rows, J, false);
+            set_scratch(J, slot_at(*geom, c->d + L.slots));
+            std::memcpy(static_cast<void *>(c->h_ring + kRing), &J, sizeof(J));
+            c->d_base = reinterpret_cast<const Job *>(c->d_ring + kRing);
+        }
         if (e == hipSuccess)
             e = hipEventCreateWithFlags(&c->order_ev, kDeviceOrderEvent);
         for (int i = 0; i < kRecs && e == hipSuccess; ++i)
@@ -234,16 +243,9 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
             e = hipEventCreateWithFlags(&c->cls_ev[k], kDeviceOrderEvent);
         if (e == hipSuccess)
             e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
-        if (e == hipSuccess) {
-            // what every job of this context has in common
-            Job J;
-            fill_job(c->m, c->tune.morph_rows, J, false);
-            set_scratch(J, slot_at(*geom, c->d + L.slots));
-            e = launch_put_job(reinterpret_cast<Job *>(c->d + L.base), J, static_cast<hipStream_t>(stream));
-            if (e == hipSuccess)
-                e = launch_fill_u32(reinterpret_cast<uint32_t *>(c->d + L.arrived), 0u, kArrivedWords,
-                                    static_cast<hipStream_t>(stream));
-        }
+        if (e == hipSuccess)
+            e = launch_fill_u32(reinterpret_cast<uint32_t *>(c->d + L.arrived), 0u, kArrivedWords,
+                                static_cast<hipStream_t>(stream));
         if (e != hipSuccess)
             rc = fail(FIZI_EHIP, std::string("fizi_create: ") + hipGetErrorString(e));
     }
@@ -340,7 +342,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         J.hout = c->d_ring;
         J.frame_index = fbase;
         SpanJobs S = span_jobs(J, k, reinterpret_cast<uint32_t *>(c->d + c->L.arrived));
-        S.base = reinterpret_cast<const Job *>(c->d + c->L.base);
+        S.base = c->d_base;
         if (!d_fizi_bits)
             S.fizi_words = c->L.slot_stride / sizeof(uint64_t);
         S.slot_bytes = c->L.slot_stride;

@@ -212,10 +212,12 @@ constexpr size_t kGainScratchBytes = kArrivedWords * sizeof(uint32_t) + (size_t)
 
 // A launch over n consecutive frames of one stream: the fields of its first
 // job that change from call to call, and the strides to the next ones. What
-// does not change lies in device memory (base: a job of the stream, its
-// scratch arrays those of frame slot 0). The gain kernel writes the job table
-// from both, so that nothing is uploaded. Kernel arguments are read from host
-// memory, so they are kept few: 700 bytes of them cost 8 to 15 us a launch.
+// does not change is the library's own, in host memory that the device reads
+// (base: a job of the stream, its scratch arrays those of frame slot 0): the
+// state block is the caller's, who may fill it from another context's, and
+// holds nothing that a kernel takes for an address. The gain kernel writes the
+// job table from both, so that nothing is uploaded. Kernel arguments are kept
+// few: 700 bytes of them cost 8 to 15 us a launch.
 struct SpanJobs {
     const Job *base;                    // null when learning: no table is written
     const uint8_t *frame;
@@ -265,7 +267,6 @@ struct ChainSpan {
 // Kernel launchers (fizi_kernels.hip). Each returns the hipError_t of its launch.
 hipError_t launch_gain(const Table *d_tab, int total_tiles, int n_cu, const Tuning &t,
                        hipStream_t s, StageEvents ev = {});
-hipError_t launch_put_job(Job *d_job, const Job &J, hipStream_t s);
 // Gain of a span's frames; builds its table.
 hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, StageEvents ev = {});
 hipError_t launch_minmax(const Table *d_tab, const LearnSpan &S, hipStream_t s, StageEvents ev = {});

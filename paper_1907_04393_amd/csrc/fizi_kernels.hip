@@ -566,12 +566,6 @@ __global__ __launch_bounds__(256) void k_gain(Table *__restrict__ T)
                     [&](int j, int tile) { gain_tile(T, j, tile, T->jobs[j].frame); });
 }
 
-__global__ void k_put_job(Job *__restrict__ d, Job J)
-{
-    if (threadIdx.x == 0)
-        *d = J;
-}
-
 // Gain of consecutive frames of one stream: workgroup (p, i) sums part p of
 // frame i's sampled pixels, items of 16 pixels (4 where the frames are only
 // 4-byte aligned) taken p blockDim + thread, + gridDim.x blockDim, ..., and
@@ -585,20 +579,20 @@ __global__ void k_put_job(Job *__restrict__ d, Job J)
 // Bound by the latency of its loads and, in between, the VALU: 64 frames of
 // 1920x1080 (50 MB of frame rows) take 19 us, 22 us tile by tile from a
 // table with atomic sums.
-__device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs &S, int i)
+// base: the stream's job up to the accumulators, as words.
+constexpr int kJobHead = (int)(offsetof(Job, num) / 8);
+static_assert(offsetof(Job, num) % 8 == 0, "whole 8-byte words");
+
+__device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs &S, const uint64_t *base, int i)
 {
     Job *J = &T->jobs[i];
-    const Job *B = S.base;
     // every field but the accumulators
-    const uint64_t *src = reinterpret_cast<const uint64_t *>(B);
     uint64_t *dst = reinterpret_cast<uint64_t *>(J);
-    constexpr int kHead = (int)(offsetof(Job, num) / 8);
-    static_assert(offsetof(Job, num) % 8 == 0, "whole 8-byte words");
     Job head;
     uint64_t *h = reinterpret_cast<uint64_t *>(&head);
 #pragma unroll
-    for (int q = 0; q < kHead; ++q)
-        h[q] = src[q];
+    for (int q = 0; q < kJobHead; ++q)
+        h[q] = base[q];
     const size_t so = (size_t)i * S.slot_bytes;
     const uint64_t index = S.frame_index + (uint64_t)i;
     auto moved = [&](auto *p, size_t bytes) {
@@ -619,7 +613,7 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     head.band = S.band;
     head.mgroup = S.mgroup;
 #pragma unroll
-    for (int q = 0; q < kHead; ++q)
+    for (int q = 0; q < kJobHead; ++q)
         dst[q] = h[q];
     // the accumulators but the inverse gain, which the frame's last workgroup
     // stores
@@ -641,9 +635,16 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int part = blockIdx.x, i = blockIdx.y;
     if (i == S.n) {
-        if (part == 0)
+        // the base lies in host memory: its words all in one access
+        __shared__ uint64_t s_base[kJobHead];
+        if (part == 0) {
+            static_assert(kJobHead <= kWave, "a word per thread of the smallest workgroup");
+            if (threadIdx.x < kJobHead)
+                s_base[threadIdx.x] = G(reinterpret_cast<const uint64_t *>(S.base))[threadIdx.x];
+            __syncthreads();
             for (int j = threadIdx.x; j < S.n; j += blockDim.x)
-                write_job(T, S, j);
+                write_job(T, S, s_base, j);
+        }
         return;
     }
     const GLOBAL uint8_t *frame0 = G(S.frame), *frame = frame0 + (size_t)i * S.frame_bytes;
@@ -3358,12 +3359,6 @@ hipError_t launch_gain_span_mode(Table *tab, const SpanJobs &S, hipStream_t s, S
 }
 
 }  // namespace
-
-hipError_t launch_put_job(Job *d_job, const Job &J, hipStream_t s)
-{
-    k_put_job<<<1, 64, 0, s>>>(d_job, J);
-    return hipGetLastError();
-}
 
 hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, StageEvents ev)
 {
