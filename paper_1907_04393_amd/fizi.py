@@ -219,7 +219,10 @@ class Context:
             check(L.fizi_validate(ctypes.byref(self.geom), ctypes.byref(self.params)))
             raise FiziError(FIZI_EINVAL, "chunk must be in [1, 256]")
         self.device = _device(device)
-        self.state = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        # initialised on `stream`: allocated there, so that nothing still
+        # pending on another stream's freed memory lands in it afterwards
+        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(self.device)):
+            self.state = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._pipelined = False
         # outputs a pipelined call is still writing (see set_pipelined)
         self._held = None
@@ -368,7 +371,9 @@ class Batch:
         if nbytes == 0:
             raise FiziError(FIZI_EINVAL, "invalid stream geometry or parameters")
         self.device = _device(device)
-        self.state = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        # initialised on the null stream: allocated there (see Context)
+        with torch.cuda.stream(torch.cuda.default_stream(self.device)):
+            self.state = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._h = ctypes.c_void_p()
         check(L.fizi_batch_create(self.n, self._g, self._p, _ptr(self.state), nbytes, ctypes.byref(self._h)))
         self._frames = (ctypes.c_void_p * self.n)()
