@@ -114,7 +114,14 @@ __device__ __forceinline__ void put_parent(GLOBAL uint32_t *p, uint32_t v)
         st_wg(p, v);
 }
 
-__device__ __forceinline__ void wait_own_memory() { __builtin_amdgcn_s_waitcnt(0); }
+// Waits for the wave's own memory operations. The signal fences keep the
+// compiler from moving any across the wait; they emit nothing.
+__device__ __forceinline__ void wait_own_memory()
+{
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
 
 __device__ __forceinline__ int find_job(const int32_t *pre, int nj, int t)
 {
