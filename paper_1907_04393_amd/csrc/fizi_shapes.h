@@ -22,16 +22,27 @@ struct GainShape {
 };
 
 // Waves per frame: one item per lane, but no more than about eight waves per
-// SIMD over the launch; in parts of four waves, more (up to 16) where 32 parts
-// would not hold them, and as many rounds as remain, the same for every part.
-// Over 50 frames of 1920x1080 (learning) parts of 4 / 8 / 16 waves take 19 /
-// 23 / 27 us, half the waves 22.
+// SIMD over the launch; in parts of four waves, more (up to kGainWaves) where
+// 32 parts would not hold them. Over 50 frames of 1920x1080 (learning) parts
+// of 4 / 8 / 16 waves take 19 / 23 / 27 us, half the waves 22. Frames too large
+// for 32 parts of kGainWaves take more of these parts, up to kGainBusy waves
+// over the launch, and as many rounds as remain, the same for every part: one
+// frame of 7680x4320 10.4 us (27.5 in 32 parts), with every row sampled 34
+// (197), one of 3840x2160 with every row 14 (52); with kGainBusy 2048 / 4096 /
+// 8192 four frames of 7680x4320 28.7 / 18.7 / 20.3, eight of 3840x2160 11.6 /
+// 11.5 / 13.2; parts of 4 / 8 / 16 waves, one frame of 7680x4320 20.9 / 13.5 /
+// 10.4.
+constexpr int kGainWaves = 16, kGainBusy = 4096;
+
 inline GainShape gain_span_shape(long long items, int n)
 {
-    const int full = (int)((items + kShapeWave - 1) / kShapeWave), waves_f = std::min(full, std::max(32, 8192 / n));
+    const int full = (int)((items + kShapeWave - 1) / kShapeWave);
+    int waves_f = std::min(full, std::max(32, 8192 / n));
+    if (waves_f > 32 * kGainWaves)
+        waves_f = std::min(waves_f, std::max(32 * kGainWaves, kGainBusy / n));
     GainShape g;
-    g.parts = std::max(1, std::min(32, (waves_f + 3) / 4));
-    const int most = std::min(16, (waves_f + g.parts - 1) / g.parts);
+    g.parts = std::max({1, std::min(32, (waves_f + 3) / 4), (waves_f + kGainWaves - 1) / kGainWaves});
+    const int most = std::min(kGainWaves, (waves_f + g.parts - 1) / g.parts);
     g.rounds = (full + g.parts * most - 1) / (g.parts * most);
     g.threads = kShapeWave * ((full + g.parts * g.rounds - 1) / (g.parts * g.rounds));
     return g;
