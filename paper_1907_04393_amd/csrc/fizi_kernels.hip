@@ -755,9 +755,11 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
 // Bound by HBM: 50 frames of 1920x1080 (323 MB) in 51 us, 6.3 TB/s (64 us
 // with every value corrected); 8 frames with masks on top of a model 12-15 us
 // (20).
-constexpr int kLearnAhead = 4;         // frames in flight per lane (two pairs)
-
-template <bool MASKED>
+// AHEAD: frames in flight per lane: two pairs, or the one or two frames of a
+// shorter call (with two pairs their loads came four or two times over:
+// learning one frame of 7680x4320 took 79 us instead of 55, two 78 instead of
+// 68).
+template <bool MASKED, int AHEAD>
 __global__ __launch_bounds__(256) void k_minmax(const Table *__restrict__ T, const LearnSpan S)
 {
     __shared__ uint32_t s_inv[kMaxJobs];
@@ -775,10 +777,10 @@ __global__ __launch_bounds__(256) void k_minmax(const Table *__restrict__ T, con
     auto skip_of = [&](int f) __attribute__((always_inline)) {
         return MASKED ? ((uint32_t)(masks + (size_t)f * (S.npx / 8u))[g >> 1] >> ((g & 1u) * 4u)) & 0xFu : 0u;
     };
-    u32x3 ring[kLearnAhead];
-    uint32_t skip[kLearnAhead];
+    u32x3 ring[AHEAD];
+    uint32_t skip[AHEAD];
 #pragma unroll
-    for (int q = 0; q < kLearnAhead; ++q) {
+    for (int q = 0; q < AHEAD; ++q) {
         ring[q] = load(min(q, last));
         skip[q] = skip_of(min(q, last));
     }
@@ -817,21 +819,21 @@ __global__ __launch_bounds__(256) void k_minmax(const Table *__restrict__ T, con
     // the loads of the loop are unconditional (past the end the last frame
     // again): a branch around them would make every wait one for all of them
     int f = 0;
-    for (; f + kLearnAhead < S.n; f += kLearnAhead) {
+    for (; f + AHEAD < S.n; f += AHEAD) {
 #pragma unroll
-        for (int q = 0; q < kLearnAhead; q += 2) {
+        for (int q = 0; q + 1 < AHEAD; q += 2) {
             widen(f + q, ring[q], ring[q + 1], skip[q], skip[q + 1]);
 #pragma unroll
             for (int r = q; r < q + 2; ++r) {
-                ring[r] = load(min(f + r + kLearnAhead, last));
-                skip[r] = skip_of(min(f + r + kLearnAhead, last));
+                ring[r] = load(min(f + r + AHEAD, last));
+                skip[r] = skip_of(min(f + r + AHEAD, last));
             }
         }
     }
 #pragma unroll
-    for (int q = 0; q < kLearnAhead; q += 2)
+    for (int q = 0; q < AHEAD; q += 2)
         if (f + q < S.n)
-            widen(f + q, ring[q], ring[q + 1], skip[q], skip[q + 1]);
+            widen(f + q, ring[q], ring[AHEAD > 1 ? q + 1 : 0], skip[q], skip[AHEAD > 1 ? q + 1 : 0]);
     GLOBAL u32x3 *pmin = reinterpret_cast<GLOBAL u32x3 *>(G(S.bgmin) + 12u * (size_t)g);
     GLOBAL u32x3 *pmax = reinterpret_cast<GLOBAL u32x3 *>(G(S.bgmax) + 12u * (size_t)g);
     u32x3 a = {~0u, ~0u, ~0u}, b = {0u, 0u, 0u};
@@ -3380,10 +3382,9 @@ hipError_t launch_gain_span(Table *d_tab, const SpanJobs &S, hipStream_t s, Stag
 hipError_t launch_minmax(const Table *d_tab, const LearnSpan &S, hipStream_t s, StageEvents ev)
 {
     const int grid = (int)((S.npx / 4u + 255u) / 256u);
-    if (S.masks)
-        FIZI_LAUNCH(k_minmax<true>, grid, 256, 0, s, ev, d_tab, S);
-    else
-        FIZI_LAUNCH(k_minmax<false>, grid, 256, 0, s, ev, d_tab, S);
+    const auto kernel = S.masks ? (S.n > 2 ? k_minmax<true, 4> : S.n == 2 ? k_minmax<true, 2> : k_minmax<true, 1>)
+                                : (S.n > 2 ? k_minmax<false, 4> : S.n == 2 ? k_minmax<false, 2> : k_minmax<false, 1>);
+    FIZI_LAUNCH(kernel, grid, 256, 0, s, ev, d_tab, S);
     return hipGetLastError();
 }
 
