@@ -1369,7 +1369,11 @@ __device__ __forceinline__ uint2 unpack_run(uint64_t v)
 }
 
 // A frame's forest in global memory: parents and areas by run, the run list.
+// A: runs or unions that a thread takes at once; 4 in the component stage, 1 in
+// the persistent step, whose registers are all taken.
+template <int A>
 struct GlobalForest {
+    static constexpr int kAhead = A;
     GLOBAL uint32_t *parent, *areas;
     const GLOBAL uint64_t *runs;
 
@@ -1399,6 +1403,7 @@ struct LdsRuns {
 
 template <int C>
 struct LdsForest {
+    static constexpr int kAhead = 1;
     LdsRuns<C> &t;
     __device__ __forceinline__ uint32_t par(uint32_t i) const
     {
@@ -1414,6 +1419,109 @@ struct LdsForest {
     __device__ __forceinline__ uint2 run(uint32_t i) const { return make_uint2(t.start[i], t.len[i]); }
 };
 
+// The roots of U runs at once, in their place, with path halving: where bands
+// were joined one below the other the path is as long as they are many, and
+// all runs' halving together shortens it in the logarithm of that.
+// This and the loops below that take several runs at once end for the wave as
+// a whole. With an exit per lane the compiler (ROCm 7.2.0) split this loop in
+// two around the last halving store and kept the outer one's condition in a
+// lane mask that the inner one's later rounds cleared for lanes that had left
+// it: they ended short of their roots.
+template <int U, typename F>
+__device__ __forceinline__ void find_roots(const F &f, uint32_t (&r)[U])
+{
+    for (;;) {
+        uint32_t p[U], g[U];
+        uint32_t more = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            p[u] = f.par(r[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            g[u] = f.par(p[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (g[u] != p[u])
+                f.set_par(r[u], g[u]);
+            more |= g[u] ^ p[u];
+            r[u] = g[u];
+        }
+        if (!__builtin_amdgcn_ballot_w64(more != 0u))
+            return;
+    }
+}
+
+// U unions at once (bit u of live: a[u] with b[u]; every a and b a run of the
+// list): the roots of all, their first pixels and then the links each in
+// flight together. In global memory a step of a union is a dependent access of
+// 0.6 us, so that a thread's unions one after the other, side after side,
+// would be nothing but waiting.
+template <int U, typename F>
+__device__ __forceinline__ void unite_at_once(const F &f, const uint32_t (&a)[U], const uint32_t (&b)[U],
+                                              uint32_t live)
+{
+    uint32_t r[2 * U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        r[u] = (live >> u) & 1u ? a[u] : 0u;
+        r[U + u] = (live >> u) & 1u ? b[u] : 0u;
+    }
+    for (;;) {
+        find_roots<2 * U>(f, r);
+        uint32_t start[2 * U], old[U];
+#pragma unroll
+        for (int u = 0; u < 2 * U; ++u)
+            start[u] = f.start(r[u]);
+        uint32_t linked = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // the later root under the earlier one
+            const bool swap = start[u] > start[U + u];
+            const uint32_t lo = swap ? r[U + u] : r[u], hi = swap ? r[u] : r[U + u];
+            r[u] = lo;
+            r[U + u] = hi;
+            if (lo != hi) {
+                linked |= 1u << u;
+                old[u] = f.link(hi, lo);
+            }
+        }
+        if (!__builtin_amdgcn_ballot_w64(linked != 0u))
+            return;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!((linked >> u) & 1u))
+                continue;
+            if (old[u] == r[U + u])
+                r[u] = r[U + u] = 0u;            // done
+            else
+                r[U + u] = old[u];
+        }
+    }
+}
+
+// The roots of U runs at once, r[u] from x[u], without writing (see root_of).
+template <int U, typename F>
+__device__ __forceinline__ void roots_of(const F &f, const uint32_t (&x)[U], uint32_t (&r)[U])
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        r[u] = x[u];
+    for (;;) {
+        uint32_t p[U];
+        uint32_t more = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            p[u] = f.par(r[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            more |= p[u] ^ r[u];
+            r[u] = p[u];
+        }
+        if (!__builtin_amdgcn_ballot_w64(more != 0u))
+            return;
+    }
+}
+
 // Joins run i (y, xs..xe) with every run of the row above that it touches
 // under 8-connectivity (columns xs-1 .. xe+1).
 template <typename F, typename P>
@@ -1427,7 +1535,8 @@ __device__ __forceinline__ void link_up(const F &f, const GLOBAL uint32_t *index
         if (xb < 0)
             break;
         const int bs = prev_zero(above, xb) + 1;
-        unite(f, i, index[(uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs]);
+        uint32_t a[1] = {i}, b[1] = {index[(uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs]};
+        unite_at_once<1>(f, a, b, 1u);
         pos = next_zero(above, Wd, xb) + 1;
     }
 }
@@ -1717,6 +1826,32 @@ __device__ __forceinline__ void touching_runs(const RowBits<NC> &U, const RowBit
     }
 }
 
+// Each pair met once (see holds_left2), for bands of more runs than a segment:
+// half the links, where the list would overflow.
+template <int NC, typename F>
+__device__ __forceinline__ void touching_runs_once(const RowBits<NC> &U, const RowBits<NC> &D, F f)
+{
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        for (uint64_t m = D.st[c]; m; m &= m - 1) {
+            const int b = __builtin_ctzll(m);
+            if (bit_at(b, U.w[c], U.lc[c], U.rc[c])) {
+                f(c, true, b, b);
+            } else {
+                if (bit_at(b - 1, U.w[c], U.lc[c], U.rc[c]))
+                    f(c, true, b, b - 1);
+                if (bit_at(b + 1, U.w[c], U.lc[c], U.rc[c]))
+                    f(c, true, b, b + 1);
+            }
+        }
+        for (uint64_t m = U.st[c]; m; m &= m - 1) {
+            const int b = __builtin_ctzll(m);
+            if (holds_left2<NC>(D, c, b))
+                f(c, false, b, b - 1);
+        }
+    }
+}
+
 __device__ __forceinline__ bool stage_erodes(int k, int oi, int ci) { return (k < oi) || (k >= 2 * oi + ci); }
 
 // Reserves n entries of the frame's run list (one atomic for the wave).
@@ -1850,12 +1985,13 @@ __device__ __forceinline__ void halo_row(const BandOut &B, RunState<NC> &S, cons
 
 // The joins of a row D (first pixel rowpx, per lane group) with the row P above
 // as pairs of run starts, from entry k of the frame's link list on (per lane).
-template <int NC, bool FLOW>
+// ONE: of a band known to fit one segment.
+template <int NC, bool FLOW, bool ONE>
 __device__ __forceinline__ void band_links(const BandOut &B, const RowBits<NC> &P, const RowBits<NC> &D,
                                            uint32_t rowpx, uint32_t k)
 {
     const uint32_t upx = rowpx - (uint32_t)B.W;
-    touching_runs<NC>(P, D, [&](int c, bool from_d, int b, int t) {
+    auto join = [&](int c, bool from_d, int b, int t) {
         const uint32_t wb = 64u * (uint32_t)(B.word + kWave * c);
         const uint32_t a = from_d ? rowpx + wb + (uint32_t)b : upx + wb + (uint32_t)b;
         const uint32_t o = from_d ? upx + (uint32_t)start_at<NC>(P, c, t, B.lg)
@@ -1865,7 +2001,11 @@ __device__ __forceinline__ void band_links(const BandOut &B, const RowBits<NC> &
             put<FLOW>(B.linkw + 2 * (size_t)k + 1, o);
         }
         ++k;
-    });
+    };
+    if constexpr (ONE)
+        touching_runs<NC>(P, D, join);
+    else
+        touching_runs_once<NC>(P, D, join);
 }
 
 // A final I_FIZI row with pixels (jrow per lane group): its runs and their
@@ -1900,7 +2040,7 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
     uint32_t flag = 0u;
     if (!ONE && prev_valid && (!prev_in_seg || direct)) {
         uint32_t cnt = 0;
-        touching_runs<NC>(P, D, [&](int, bool, int, int) { ++cnt; });
+        touching_runs_once<NC>(P, D, [&](int, bool, int, int) { ++cnt; });
         const uint32_t inc = wave_incl_scan(cnt);
         const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
         uint32_t base = 0;
@@ -1908,7 +2048,7 @@ __device__ __forceinline__ void run_row(const BandOut &B, RunState<NC> &S, WaveL
             base = atomicAdd(&J->nlinks, n);
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         const uint32_t k = base + inc - cnt;
-        band_links<NC, FLOW>(B, P, D, rowpx, k);
+        band_links<NC, FLOW, false>(B, P, D, rowpx, k);
         if (base + n > link_cap) {
             // the list is full: the component stage joins this row to
             // the row above by reading I_FIZI
@@ -2360,7 +2500,7 @@ __device__ __forceinline__ void morph_regs(Job *J, int item, WaveLds &L)
             row_of(0, v0);
             (void)row_bits<NC>(S.P, x[KT], Wd, en, lg);
             const uint32_t first = row_bits<NC>(D0, v0, Wd, en, lg);
-            band_links<NC, false>(B, S.P, D0, (uint32_t)max(y0, 0) * (uint32_t)B.W, lbase + inc - cnt);
+            band_links<NC, false, true>(B, S.P, D0, (uint32_t)max(y0, 0) * (uint32_t)B.W, lbase + inc - cnt);
             if (lbase + nlink > B.link_cap) {
                 // the list is full: the component stage joins the row's runs
                 // to the row above by reading I_FIZI
@@ -2452,11 +2592,13 @@ constexpr int kMaxWaves = 16;
 // Component areas of one frame, summed in LDS: an open-addressing table from
 // root to area. A component's runs all add to its root, and same-address
 // atomics serialise far less in LDS than in the cache (a hand is a thousand
-// runs on a 4K frame). A root that finds no free slot in its probe window
-// adds in global memory instead, and so do all of its runs, since slots are
-// only ever taken: the table and the global array never share a root.
+// runs on a 4K frame). A root that finds no free slot in its bucket adds in
+// global memory instead, and so do all of its runs, since slots are only ever
+// taken, the first free one of a bucket first: the table and the global array
+// never share a root. A bucket is read at once (slot by slot over a window of
+// 32, a frame of noise spent half of its components' time here).
 constexpr int kAreaSlots = 2048;
-constexpr int kAreaProbe = 32;
+constexpr int kAreaBucket = 8;
 constexpr uint32_t kAreaEmpty = 0xFFFFFFFFu;
 struct AreaTable {
     uint32_t key[kAreaSlots];
@@ -2478,16 +2620,31 @@ static_assert(sizeof(ResolveLds<kForestRunsFlow>) <= 4 * sizeof(WaveLds), "the f
 
 __device__ __forceinline__ void area_add(AreaTable &t, GLOBAL uint32_t *area, uint32_t root, uint32_t len)
 {
-    uint32_t slot = (root * 2654435761u) >> (32 - 11);
-    for (int p = 0; p < kAreaProbe; ++p) {
-        uint32_t k = __hip_atomic_load(&t.key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (k == kAreaEmpty)
-            k = atomicCAS(&t.key[slot], kAreaEmpty, root);
-        if (k == kAreaEmpty || k == root) {
-            atomicAdd(&t.val[slot], len);
-            return;
+    const uint32_t first = ((root * 2654435761u) >> (32 - 11)) & ~(uint32_t)(kAreaBucket - 1);
+    for (;;) {
+        uint32_t k[kAreaBucket], slot = kAreaBucket;
+#pragma unroll
+        for (int q = 0; q < kAreaBucket; ++q)
+            k[q] = __hip_atomic_load(&t.key[first + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the root's slot, else the first free one
+#pragma unroll
+        for (int q = kAreaBucket - 1; q >= 0; --q)
+            slot = k[q] == kAreaEmpty ? (uint32_t)q : slot;
+        bool found = false;
+#pragma unroll
+        for (int q = 0; q < kAreaBucket; ++q) {
+            found |= k[q] == root;
+            slot = k[q] == root ? (uint32_t)q : slot;
         }
-        slot = (slot + 1u) & (uint32_t)(kAreaSlots - 1);
+        if (slot == kAreaBucket)
+            break;
+        if (!found) {
+            const uint32_t was = atomicCAS(&t.key[first + slot], kAreaEmpty, root);
+            if (was != kAreaEmpty && was != root)
+                continue;               // another root took it
+        }
+        atomicAdd(&t.val[first + slot], len);
+        return;
     }
     t.overflow = 1u;
     __hip_atomic_fetch_add(area + root, len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2617,14 +2774,85 @@ __device__ __forceinline__ Components resolve_lds(Job *J, LdsRuns<C> &t, uint32_
     return largest_of(best, root, count);
 }
 
+// Joins the flagged runs of the list with the row above by reading I_FIZI
+// (whole workgroup). kAhead runs of a thread at once: a short run's columns in
+// the row above, one to either side included, are a window of at most 64 bits,
+// whose runs of ones are taken from the left; the runs' next ones are united
+// together. Longer runs go one by one.
+template <typename F>
+__device__ __forceinline__ void link_flagged(const F &f, const GLOBAL uint32_t *index,
+                                             const GLOBAL uint64_t *fz, int Wd, int W, uint32_t nr)
+{
+    constexpr int U = F::kAhead;
+    for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+        uint64_t rv[U], t[U];
+        uint32_t up[U];                          // row above
+        int base[U];                             // window's first column
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            rv[u] = f.runs[min(i + u * blockDim.x, nr - 1u)];
+        uint32_t todo = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint2 rn = unpack_run(rv[u]);
+            const uint32_t y = rn.x / (uint32_t)W, xs = rn.x - y * (uint32_t)W;
+            const bool join = i + u * blockDim.x < nr && ((uint32_t)(rv[u] >> 32) & kLinkUp) && y > 0;
+            up[u] = max(y, 1u) - 1u;
+            base[u] = max((int)xs - 1, 0);
+            const int n = min((int)(xs + rn.y), W - 1) - base[u] + 1;
+            const GLOBAL uint64_t *above = fz + (size_t)up[u] * Wd;
+            const int w = base[u] >> 6, b = base[u] & 63;
+            const uint64_t m0 = above[w], m1 = above[min(w + 1, Wd - 1)];
+            const uint64_t v = (m0 >> b) | ((m1 << 1) << (63 - b));
+            t[u] = join && n <= 64 ? v & (~0ull >> (64 - n)) : 0ull;
+            todo |= (uint32_t)(join && n > 64) << u;
+        }
+        for (;;) {
+            uint64_t left = 0ull;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                left |= t[u];
+            if (!__builtin_amdgcn_ballot_w64(left != 0ull))
+                break;
+            uint32_t a[U], b[U], live = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = b[u] = 0u;
+                if (t[u]) {
+                    int x = base[u] + __builtin_ctzll(t[u]);
+                    if (x == base[u])            // its run may start further left
+                        x = prev_zero(fz + (size_t)up[u] * Wd, x) + 1;
+                    a[u] = i + u * blockDim.x;
+                    b[u] = index[up[u] * (uint32_t)W + (uint32_t)x];
+                    live |= 1u << u;
+                    t[u] &= t[u] + (t[u] & (0ull - t[u]));
+                }
+            }
+            unite_at_once<U>(f, a, b, live);
+        }
+        for (; todo; todo &= todo - 1u) {
+            const uint32_t k = i + (uint32_t)__builtin_ctz(todo) * blockDim.x;
+            const uint2 rn = f.run(k);
+            const int y = (int)(rn.x / (uint32_t)W), xs = (int)(rn.x - (uint32_t)y * W);
+            link_up(f, index, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xs + (int)rn.y - 1, k);
+        }
+    }
+}
+
 // The same in global memory, for frames with more runs or an overflown join
 // list (its flagged runs are joined by reading I_FIZI). Afterwards the areas
 // hold every root's area and each other run's parent is one of its ancestors
 // (see root_of).
+// Bound by the latency of its dependent accesses, one workgroup to a frame: a
+// thread takes A runs or joins at once. One frame of 1920x1088 of noise of
+// density 0.02 / 0.2 / 0.5: 106 / 1810 / 7860 us; one by one, in 512 threads,
+// 383 / 6770 / 16240, in 1024 with the runs known by their first pixel 343 /
+// 3950 / 9050.
+template <int A>
 __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uint32_t nr, uint32_t nl, uint32_t nflag)
 {
     const int W = J->W, Wd = J->Wd;
-    const GlobalForest f(J);
+    const GlobalForest<A> f(J);
     const GLOBAL uint64_t *links = G(reinterpret_cast<const uint64_t *>(J->links));
     const GLOBAL uint32_t *index = G(J->index);
     const GLOBAL uint64_t *fz = G(J->fizi);
@@ -2637,33 +2865,58 @@ __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uin
     for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
         st_wg(f.areas + i, 0u);
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nl; i += blockDim.x) {
-        const uint64_t l = links[i];
-        unite(f, index[(uint32_t)l], index[(uint32_t)(l >> 32)]);
+    constexpr int U = A;
+    for (uint32_t i = threadIdx.x; i < nl; i += U * blockDim.x) {
+        uint64_t l[U];
+        uint32_t a[U], b[U], live = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            live |= (uint32_t)(i + u * blockDim.x < nl) << u;
+            l[u] = links[min(i + u * blockDim.x, nl - 1u)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = index[(uint32_t)l[u]];
+            b[u] = index[(uint32_t)(l[u] >> 32)];
+        }
+        unite_at_once<U>(f, a, b, live);
     }
     if (nflag)
-        for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-            const uint64_t rv = f.runs[i];
-            if (!((uint32_t)(rv >> 32) & kLinkUp))
-                continue;
-            const uint2 rn = unpack_run(rv);
-            const int y = (int)(rn.x / (uint32_t)W);
-            if (y == 0)
-                continue;
-            const int xs = (int)(rn.x - (uint32_t)y * W), xe = xs + (int)rn.y - 1;
-            link_up(f, index, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xe, i);
-        }
+        link_flagged(f, index, fz, Wd, W, nr);
     __syncthreads();
-    // roots and areas
-    uint32_t count = 0;
-    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        const uint32_t r = find_root(f, i);
-        if (r == i)
-            ++count;
-        else
-            f.set_par(i, r);
-        area_add(tab, f.areas, r, f.run(i).y);
+    // roots and areas; a thread's runs of one root in a row are added together
+    // (most of a frame's runs may be one component's)
+    uint32_t count = 0, held = kNoRoot, sum = 0;
+    for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+        uint32_t x[U], r[U], len[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = min(i + u * blockDim.x, nr - 1u);
+            len[u] = f.run(x[u]).y;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            r[u] = x[u];
+        find_roots<U>(f, r);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + u * blockDim.x >= nr)
+                break;
+            if (r[u] == x[u])
+                ++count;
+            else
+                f.set_par(x[u], r[u]);
+            if (r[u] != held) {
+                if (held != kNoRoot)
+                    area_add(tab, f.areas, held, sum);
+                held = r[u];
+                sum = 0;
+            }
+            sum += len[u];
+        }
     }
+    if (held != kNoRoot)
+        area_add(tab, f.areas, held, sum);
     __syncthreads();
     // the table's areas go to the global array (tracking and the chain read
     // it); the largest component from the table, or from every run when some
@@ -2683,12 +2936,22 @@ __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uin
     }
     if (tab.overflow) {
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-            if (f.par(i) == i) {
-                const unsigned long long key = size_key(f.area(i), f.start(i));
-                if (key > best) {
+        for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+            uint32_t p[U], area[U], start[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t k = min(i + u * blockDim.x, nr - 1u);
+                p[u] = f.par(k);
+                area[u] = f.area(k);
+                start[u] = f.start(k);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t k = min(i + u * blockDim.x, nr - 1u);
+                const unsigned long long key = size_key(area[u], start[u]);
+                if (p[u] == k && key > best) {
                     best = key;
-                    root = i;
+                    root = k;
                 }
             }
         }
@@ -2803,19 +3066,32 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
     const int W = J->W, Wd = J->Wd;
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
     ZoneStats z{0, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, 0};
-    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        if (root_of(f, i) != kstar)
-            continue;
-        const uint2 rn = f.run(i);
-        const uint32_t y = rn.x / (uint32_t)W, xs = rn.x - y * (uint32_t)W;
-        const uint32_t xe = xs + rn.y - 1;
-        z.sx += (unsigned long long)rn.y * xs + (unsigned long long)rn.y * (rn.y - 1) / 2;
-        z.sy += (unsigned long long)rn.y * y;
-        z.x0 = min(z.x0, xs);
-        z.x1 = max(z.x1, xe);
-        z.y0 = min(z.y0, y);
-        z.y1 = max(z.y1, y);
-        if (hand) {
+    constexpr int U = F::kAhead;
+    for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+        uint32_t x[U], r[U], hit = 0;
+        uint2 rn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = min(i + u * blockDim.x, nr - 1u);
+            rn[u] = f.run(x[u]);
+        }
+        roots_of<U>(f, x, r);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r[u] != kstar || i + u * blockDim.x >= nr)
+                continue;
+            hit |= 1u << u;
+            const uint32_t y = rn[u].x / (uint32_t)W, xs = rn[u].x - y * (uint32_t)W, n = rn[u].y;
+            z.sx += (unsigned long long)n * xs + (unsigned long long)n * (n - 1) / 2;
+            z.sy += (unsigned long long)n * y;
+            z.x0 = min(z.x0, xs);
+            z.x1 = max(z.x1, xs + n - 1);
+            z.y0 = min(z.y0, y);
+            z.y1 = max(z.y1, y);
+        }
+        for (; hand && hit; hit &= hit - 1u) {
+            const uint2 run = f.run(i + (uint32_t)__builtin_ctz(hit) * blockDim.x);
+            const uint32_t y = run.x / (uint32_t)W, xs = run.x - y * (uint32_t)W, xe = xs + run.y - 1;
             GLOBAL uint64_t *hr = hand + (size_t)y * Wd;
             const int wa = (int)(xs >> 6), wb = (int)(xe >> 6);
             for (int w = wa; w <= wb; ++w) {
@@ -2945,7 +3221,7 @@ __device__ __forceinline__ void resolve_zone(Job *J, const F &f, const Component
 }
 
 // One workgroup per frame: its components, the hand zone, and the pointer.
-template <int C>
+template <int C, int A>
 __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool same_launch, ResolveLds<C> &lds,
                                             bool defer = false)
 {
@@ -2972,7 +3248,7 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
         const Components c = resolve_lds(J, lds.runs, nr, nl);
         if (defer) {
             // the chain reads the forest
-            const GlobalForest g(J);
+            const GlobalForest<1> g(J);
             for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
                 st_wg(g.parent + i, lds.runs.par[i]);
                 st_wg(g.areas + i, lds.runs.area[i]);
@@ -2980,8 +3256,8 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
         }
         resolve_zone(J, f, c, inv, defer, was, s_cover);
     } else {
-        const GlobalForest f(J);
-        const Components c = resolve_global(J, lds.areas, nr, nl, nflag);
+        const GlobalForest<A> f(J);
+        const Components c = resolve_global<A>(J, lds.areas, nr, nl, nflag);
         resolve_zone(J, f, c, inv, defer, was, s_cover);
     }
     __syncthreads();
@@ -2993,7 +3269,7 @@ __global__ __launch_bounds__(NT) void k_resolve(Table *__restrict__ T, int defer
     __shared__ ResolveLds<kForestRuns> s_lds;
     const int nj = T->h.njobs;
     for (int j = blockIdx.x; j < nj; j += gridDim.x)
-        resolve_job(T, j, false, s_lds, defer != 0);
+        resolve_job<kForestRuns, 4>(T, j, false, s_lds, defer != 0);
 }
 
 // Tracking of consecutive frames of one stream after a deferred component
@@ -3145,7 +3421,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_track_chain(Table *__restri
         if (j >= nj)
             break;
         Job *J = &T->jobs[j];
-        const GlobalForest f(J);
+        const GlobalForest<4> f(J);
         uint32_t pick = s_pick;
         if (!s_zone)
             pick = nearest_root(J, f, s_ax, s_ay, amin, r2);
@@ -3310,7 +3586,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX == 4 &
                 acquire_for_block();
                 // the waves' morphology tables are free again: the components
                 // take their place
-                resolve_job(T, j, true, *reinterpret_cast<ResolveLds<kForestRunsFlow> *>(&s_wl[0]));
+                resolve_job<kForestRunsFlow, 1>(T, j, true, *reinterpret_cast<ResolveLds<kForestRunsFlow> *>(&s_wl[0]));
             }
         }
     }
