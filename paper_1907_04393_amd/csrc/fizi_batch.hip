@@ -468,12 +468,13 @@ int fizi_batch_step(fizi_batch *b, const uint8_t *const *h_frames, uint64_t *con
             short_waves += (size_t)((b->m[i].g.height + kShortBand - 1) / kShortBand);
     const bool short_chain =
         b->tune.short_bands && !is_persistent(b->mode) && short_waves <= (size_t)b->n_cu * 4;
-    const bool pack = !short_chain && morph_in_regs(b->tune.morph_rows, b->max_wd, b->max_ops);
     int k = 0;
     for (int i = 0; i < b->n; ++i) {
         if (!h_frames[i])
             continue;
         Job &J = T.jobs[k++];
+        const bool pack =
+            !short_chain && morph_in_regs(b->tune.morph_rows, b->max_wd, b->max_ops, morph_ops(b->m[i].p));
         fill_job(b->m[i], short_chain ? kShortBand : b->tune.morph_rows, J, pack);
         set_scratch(J, b->slot[i]);
         if (pipelined && b->parity)

@@ -330,7 +330,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         // the launch's first job, and the strides to the next ones
         Job J;
         fill_job(c->m, short_chain ? kShortBand : c->tune.morph_rows, J,
-                 !short_chain && morph_in_regs(c->tune.morph_rows, (int)(W / 64), morph_ops(c->m.p)));
+                 !short_chain && morph_in_regs(c->tune.morph_rows, (int)(W / 64), morph_ops(c->m.p), morph_ops(c->m.p)));
         set_scratch(J, slot_at(c->m.g, c->d + c->L.slots));
         if (pipelined && par)
             J.raw = reinterpret_cast<uint64_t *>(c->d + c->L.raw2);

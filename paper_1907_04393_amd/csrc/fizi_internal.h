@@ -163,14 +163,15 @@ struct Tuning {
 };
 
 // Whether the morphology of a launch (tuned band height, widest frame in
-// words, most stages of a job) holds its bands in registers with their halo:
-// bands of 8 or 16 rows, and of the short height in such a launch, but frames
-// of more than 64 words only with the default four stages. Other launches
-// stream their bands. Only bands in registers share a wave on narrow frames.
-inline bool morph_in_regs(int morph_rows, int max_wd, int max_ops)
+// words, most stages of a job) holds a job's bands (ops stages) in registers
+// with their halo: bands of 8 or 16 rows, and of the short height in such a
+// launch, but in launches of frames of more than 64 words and of more than four
+// stages only jobs of at most four. The others stream their bands. Only bands
+// in registers share a wave on narrow frames.
+inline bool morph_in_regs(int morph_rows, int max_wd, int max_ops, int ops)
 {
     const bool wide = max_wd > 64, deep = max_ops > 4;
-    return (morph_rows == 8 || morph_rows == 16) && !(wide && deep);
+    return (morph_rows == 8 || morph_rows == 16) && !(wide && deep && ops > 4);
 }
 
 inline int cls_tile_px(const Tuning &t) { return 1024 * t.cls_iters; }

@@ -18,6 +18,7 @@
 //   k_morph_regs opening then closing with a 3x3 square on bands of bit rows
 //                held in registers (64 pixels per lane word), then runs and
 //                band-local components in LDS (Section 3.1, last paragraph)
+//   k_morph_mixed  either, by job, for batches of wide frames and deep streams
 //   k_morph      the same streamed through a register pipeline, for taller
 //                bands and for wide frames with many stages
 //   k_resolve    8-connected components by union-find over runs (in LDS where
@@ -2579,6 +2580,42 @@ __global__ __launch_bounds__(256) void k_morph_regs(Table *__restrict__ T, int t
     }
 }
 
+// Steps of a batch with wide frames and, of any stream, more than four stages:
+// jobs of at most four stages hold their bands in registers as above, the
+// others stream them. 32 streams of 1920x1080 but for a deep one of 7680x1080,
+// pipelined in 16-row bands: 116 us of morphology, 170 with every band streamed
+// by a wave of its own (125 with narrow ones sharing it); 63 of 1024x768 beside
+// that one 114, 186 and 122.
+template <int R>
+__global__ __launch_bounds__(256) void k_morph_mixed(Table *__restrict__ T)
+{
+    __shared__ WaveLds s_wl[256 / kWave];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int nj = T->h.njobs;
+    const int total = T->h.mor_pre[nj];
+    for (int t = blockIdx.x * (256 / kWave) + wave; t < total; t += gridDim.x * (256 / kWave)) {
+        const int j = find_job(T->h.mor_pre, nj, t);
+        Job *J = &T->jobs[j];
+        const int item = t - T->h.mor_pre[j];
+        const bool wide = J->Wd > kWave;
+        if (2 * (J->open_it + J->close_it) > 4) {
+            if (wide)
+                morph_band<4 * kMaxMorphIters, 2, false>(J, item, s_wl[wave]);
+            else
+                morph_band<4 * kMaxMorphIters, 1, false>(J, item, s_wl[wave]);
+        } else if (J->band == kShortBand) {
+            if (wide)
+                morph_regs<kShortBand, 4, 2>(J, item, s_wl[wave]);
+            else
+                morph_regs<kShortBand, 4, 1>(J, item, s_wl[wave]);
+        } else if (wide) {
+            morph_regs<R, 4, 2>(J, item, s_wl[wave]);
+        } else {
+            morph_regs<R, 4, 1>(J, item, s_wl[wave]);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Workgroup of the component stage: 512 threads when it runs on its own (one
 // frame of 1920x1080 in 1024 / 512 / 256 threads: 9.9 / 8.9 / 8.0 us, eight of
@@ -3730,7 +3767,15 @@ hipError_t launch_morph(const Table *d_tab, int total_tiles, int items, int max_
     const int grid = min((total_tiles + waves - 1) / waves, n_cu * t.grid_per_cu);
     Table *tab = const_cast<Table *>(d_tab);
     const bool wide = max_wd > kWave, deep = max_ops > 4;
-    if (morph_in_regs(t.morph_rows, max_wd, max_ops)) {
+    const bool regs = t.morph_rows == 8 || t.morph_rows == 16;
+    if (regs && wide && deep && !items) {
+        if (t.morph_rows == 16)
+            FIZI_LAUNCH(k_morph_mixed<16>, grid, 256, 0, s, ev, tab);
+        else
+            FIZI_LAUNCH(k_morph_mixed<8>, grid, 256, 0, s, ev, tab);
+        return hipGetLastError();
+    }
+    if (regs && !(wide && deep)) {
         if (t.morph_rows == 16) {
             if (wide)
                 FIZI_LAUNCH((k_morph_regs<16, 4, 2>), grid, 256, 0, s, ev, tab, total_tiles, items);
