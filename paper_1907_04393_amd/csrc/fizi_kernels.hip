@@ -15,6 +15,7 @@
 //                3.2); HBM-bound, 4 pixels per lane. Frames of many streams
 //   k_classify_span  the same for consecutive frames of one stream, the box
 //                of a lane's pixels in registers across them
+//   k_classify_one  the same for one frame of one stream
 //   k_morph_regs opening then closing with a 3x3 square on bands of bit rows
 //                held in registers (64 pixels per lane word), then runs and
 //                band-local components in LDS (Section 3.1, last paragraph)
@@ -1112,10 +1113,6 @@ __global__ __launch_bounds__(256) void k_classify(Table *__restrict__ T)
 // against Hi - Lo per channel. Frame by frame (k_classify) the model is
 // unpacked each time: 29 instructions per pixel in all, against 9 here plus
 // the box (170 per lane) and the pixels outside it.
-// A call of one frame takes it too: nothing to share the box between, but no
-// table lookups before the loads and a workgroup per 1024 pixels (k_classify
-// with 4 x 1024 before: 320x240 7.4 -> 3.5 us, 1920x1080 8.3 -> 5.9,
-// 3840x2160 16.3 -> 15.0, 7680x4320 46.3 -> 46.4).
 // Bound by HBM and the VALU together: 64 frames of 1920x1080 (398 MB) take 78
 // us (174 us frame by frame), moving 5.6 TB/s with the VALU two thirds busy.
 struct Box4 {
@@ -1243,6 +1240,38 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
     for (int q = 0; q < kSpanAhead; ++q)
         if (f + q < nf)
             test(f + q, ring[q]);
+}
+
+// One frame of a stream: nothing to share a box between, so the pixels are
+// corrected and tested as they are in k_classify; by value, without table
+// lookups before the loads, a workgroup per 1024 pixels. Bound by its launch
+// and load latency on small frames, by HBM on large ones: 320x240 / 1920x1080 /
+// 3840x2160 / 7680x4320 4.2 / 4.7 / 12.4 / 43.1 us (5.8 to 6.9 TB/s), full of
+// noise 4.2 / 5.6 / 15.2 / 50.9; k_classify_span on it 4.2 / 5.6 / 14.7 / 45.6
+// and 4.4 / 6.9 / 18.8 / 60.7, k_classify 7.4 / 8.6 / 15.7 / 47.4 and 7.5 / 9.5
+// / 18.3 / 53.2.
+template <int KIND>
+__global__ __launch_bounds__(256) void k_classify_one(const Table *__restrict__ T, const FrameSpan F, const HueTest h)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint32_t base = blockIdx.x * 1024u + (uint32_t)wave * 256u;
+    if (base >= F.npx)
+        return;
+    ClsJob c;
+    c.fr = G(reinterpret_cast<const uint32_t *>(F.frames));
+    c.mn = G(reinterpret_cast<const uint32_t *>(F.bgmin));
+    c.mx = G(reinterpret_cast<const uint32_t *>(F.bgmax));
+    c.raw = G(F.raw);
+    c.delta = F.delta;
+    c.S1 = F.S1;
+    c.scaled = F.scaled;
+    c.S_q16 = F.S_q16;
+    c.S0 = F.S0;
+    c.lum2 = F.lum2;
+    c.h = h;
+    Px4 x;
+    load_px4(c, base + 4u * (threadIdx.x & (kWave - 1)), F.npx, x);
+    classify_px4<false, KIND>(c, base, F.npx, T->jobs[0].ginv & ~kGainKnown, x);
 }
 
 // ---------------------------------------------------------------------------
@@ -3749,6 +3778,15 @@ hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job
         per /= 2;
     per = std::min(per, F.n);
     const dim3 grid((unsigned)tiles, (unsigned)((F.n + per - 1) / per));
+    if (F.n == 1) {
+        if (F.scaled)
+            FIZI_LAUNCH(k_classify_one<kScaled>, tiles, 256, 0, s, ev, d_tab, F, J.hue);
+        else if (F.lum2)
+            FIZI_LAUNCH(k_classify_one<kCorrectedLum>, tiles, 256, 0, s, ev, d_tab, F, J.hue);
+        else
+            FIZI_LAUNCH(k_classify_one<kCorrected>, tiles, 256, 0, s, ev, d_tab, F, J.hue);
+        return hipGetLastError();
+    }
     if (F.scaled)
         FIZI_LAUNCH(k_classify_span<kScaled>, grid, 256, 0, s, ev, d_tab, F, per);
     else if (F.lum2)
