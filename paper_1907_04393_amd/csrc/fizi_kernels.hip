@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(256) void k_classify_span(const Table *__restrict__
 // corrected and tested as they are in k_classify; by value, without table
 // lookups before the loads, a workgroup per 1024 pixels. Bound by its launch
 // and load latency on small frames, by HBM on large ones: 320x240 / 1920x1080 /
-// 3840x2160 / 7680x4320 4.2 / 4.7 / 12.4 / 43.1 us (5.8 to 6.9 TB/s), full of
+// 3840x2160 / 7680x4320 4.2 / 4.7 / 12.4 / 43.1 us (7.0 TB/s), full of
 // noise 4.2 / 5.6 / 15.2 / 50.9; k_classify_span on it 4.2 / 5.6 / 14.7 / 45.6
 // and 4.4 / 6.9 / 18.8 / 60.7, k_classify 7.4 / 8.6 / 15.7 / 47.4 and 7.5 / 9.5
 // / 18.3 / 53.2.
@@ -1400,7 +1400,9 @@ __device__ __forceinline__ uint2 unpack_run(uint64_t v)
 
 // A frame's forest in global memory: parents and areas by run, the run list.
 // A: runs or unions that a thread takes at once; 4 in the component stage, 1 in
-// the persistent step, whose registers are all taken.
+// the persistent step, whose registers are all taken (its code for several,
+// which masks of few runs never reach, cost a step of 32 streams of 1920x1080
+// 5 to 9%).
 template <int A>
 struct GlobalForest {
     static constexpr int kAhead = A;
@@ -1485,7 +1487,9 @@ __device__ __forceinline__ void find_roots(const F &f, uint32_t (&r)[U])
 // list): the roots of all, their first pixels and then the links each in
 // flight together. In global memory a step of a union is a dependent access of
 // 0.6 us, so that a thread's unions one after the other, side after side,
-// would be nothing but waiting.
+// would be nothing but waiting. Where the two sides' paths meet they are one
+// set: most pairs come twice, and a pair of joined neighbours in a tall
+// component would else climb to its top.
 template <int U, typename F>
 __device__ __forceinline__ void unite_at_once(const F &f, const uint32_t (&a)[U], const uint32_t (&b)[U],
                                               uint32_t live)
@@ -1497,7 +1501,31 @@ __device__ __forceinline__ void unite_at_once(const F &f, const uint32_t (&a)[U]
         r[U + u] = (live >> u) & 1u ? b[u] : 0u;
     }
     for (;;) {
-        find_roots<2 * U>(f, r);
+        for (;;) {
+            uint32_t p[2 * U], g[2 * U], more = 0;
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u)
+                p[u] = f.par(r[u]);
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u)
+                g[u] = f.par(p[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int v = U + u;
+                // one set already: the two sides' paths meet
+                const bool met = (r[u] == r[v]) | (r[u] == p[v]) | (r[u] == g[v]) | (p[u] == r[v]) | (p[u] == p[v]) |
+                                 (p[u] == g[v]) | (g[u] == r[v]) | (g[u] == p[v]) | (g[u] == g[v]);
+                if (g[u] != p[u])
+                    f.set_par(r[u], g[u]);
+                if (g[v] != p[v])
+                    f.set_par(r[v], g[v]);
+                more |= met ? 0u : (g[u] ^ p[u]) | (g[v] ^ p[v]);
+                r[u] = met ? 0u : g[u];
+                r[v] = met ? 0u : g[v];
+            }
+            if (!__builtin_amdgcn_ballot_w64(more != 0u))
+                break;
+        }
         uint32_t start[2 * U], old[U];
 #pragma unroll
         for (int u = 0; u < 2 * U; ++u)
@@ -1565,8 +1593,7 @@ __device__ __forceinline__ void link_up(const F &f, const GLOBAL uint32_t *index
         if (xb < 0)
             break;
         const int bs = prev_zero(above, xb) + 1;
-        uint32_t a[1] = {i}, b[1] = {index[(uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs]};
-        unite_at_once<1>(f, a, b, 1u);
+        unite(f, i, index[(uint32_t)(y - 1) * (uint32_t)W + (uint32_t)bs]);
         pos = next_zero(above, Wd, xb) + 1;
     }
 }
@@ -2840,16 +2867,33 @@ __device__ __forceinline__ Components resolve_lds(Job *J, LdsRuns<C> &t, uint32_
     return largest_of(best, root, count);
 }
 
-// Joins the flagged runs of the list with the row above by reading I_FIZI
-// (whole workgroup). kAhead runs of a thread at once: a short run's columns in
-// the row above, one to either side included, are a window of at most 64 bits,
-// whose runs of ones are taken from the left; the runs' next ones are united
-// together. Longer runs go one by one.
+// Joins a run of the list with the row above by reading I_FIZI.
 template <typename F>
-__device__ __forceinline__ void link_flagged(const F &f, const GLOBAL uint32_t *index,
-                                             const GLOBAL uint64_t *fz, int Wd, int W, uint32_t nr)
+__device__ __forceinline__ void link_run(const F &f, const GLOBAL uint32_t *index, const GLOBAL uint64_t *fz, int Wd,
+                                         int W, uint32_t i)
+{
+    const uint2 rn = f.run(i);
+    const int y = (int)(rn.x / (uint32_t)W), xs = (int)(rn.x - (uint32_t)y * W);
+    if (y > 0)
+        link_up(f, index, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xs + (int)rn.y - 1, i);
+}
+
+// Joins the flagged runs of the list with the row above (whole workgroup).
+// kAhead runs of a thread at once: a short run's columns in the row above, one
+// to either side included, are a window of at most 64 bits, whose runs of ones
+// are taken from the left; the runs' next ones are united together. Longer
+// runs go one by one.
+template <typename F>
+__device__ __forceinline__ void link_flagged(const F &f, const GLOBAL uint32_t *index, const GLOBAL uint64_t *fz,
+                                             int Wd, int W, uint32_t nr)
 {
     constexpr int U = F::kAhead;
+    if constexpr (U == 1) {
+        for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
+            if ((uint32_t)(f.runs[i] >> 32) & kLinkUp)
+                link_run(f, index, fz, Wd, W, i);
+        return;
+    }
     for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
         uint64_t rv[U], t[U];
         uint32_t up[U];                          // row above
@@ -2896,12 +2940,8 @@ __device__ __forceinline__ void link_flagged(const F &f, const GLOBAL uint32_t *
             }
             unite_at_once<U>(f, a, b, live);
         }
-        for (; todo; todo &= todo - 1u) {
-            const uint32_t k = i + (uint32_t)__builtin_ctz(todo) * blockDim.x;
-            const uint2 rn = f.run(k);
-            const int y = (int)(rn.x / (uint32_t)W), xs = (int)(rn.x - (uint32_t)y * W);
-            link_up(f, index, fz + (size_t)(y - 1) * Wd, Wd, W, y, xs, xs + (int)rn.y - 1, k);
-        }
+        for (; todo; todo &= todo - 1u)
+            link_run(f, index, fz, Wd, W, i + (uint32_t)__builtin_ctz(todo) * blockDim.x);
     }
 }
 
@@ -2911,7 +2951,7 @@ __device__ __forceinline__ void link_flagged(const F &f, const GLOBAL uint32_t *
 // (see root_of).
 // Bound by the latency of its dependent accesses, one workgroup to a frame: a
 // thread takes A runs or joins at once. One frame of 1920x1088 of noise of
-// density 0.02 / 0.2 / 0.5: 106 / 1810 / 7860 us; one by one, in 512 threads,
+// density 0.02 / 0.2 / 0.5: 102 / 1830 / 7740 us; one by one, in 512 threads,
 // 383 / 6770 / 16240, in 1024 with the runs known by their first pixel 343 /
 // 3950 / 9050.
 template <int A>
@@ -2945,7 +2985,10 @@ __device__ __forceinline__ Components resolve_global(Job *J, AreaTable &tab, uin
             a[u] = index[(uint32_t)l[u]];
             b[u] = index[(uint32_t)(l[u] >> 32)];
         }
-        unite_at_once<U>(f, a, b, live);
+        if constexpr (U == 1)
+            unite(f, a[0], b[0]);
+        else
+            unite_at_once<U>(f, a, b, live);
     }
     if (nflag)
         link_flagged(f, index, fz, Wd, W, nr);
