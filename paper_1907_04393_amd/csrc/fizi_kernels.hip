@@ -164,17 +164,16 @@ __device__ __forceinline__ uint32_t inv_gain(unsigned long long num, unsigned lo
     return (uint32_t)q;
 }
 
-// The frame's inverse gain from its gain accumulators. `same_launch`: the
-// sums were written earlier in the same launch (persistent step), so they
-// are read with device-scope atomic loads; after a kernel boundary plain
-// (scalar) loads see them. One thread; wave_job_gain is the whole wave's.
-__device__ __forceinline__ uint32_t job_gain(const Job *J, bool same_launch)
+// The frame's inverse gain from its gain accumulators, by one thread of the
+// launch that sums them (persistent step): device-scope loads. wave_job_gain
+// is the whole wave's, after a kernel boundary.
+__device__ __forceinline__ uint32_t job_gain(const Job *J)
 {
     unsigned long long n = 0, d = 0;
 #pragma unroll
     for (int i = 0; i < kGainSlots; ++i) {
-        n += same_launch ? ld_dev(&J->num[i]) : J->num[i];
-        d += same_launch ? ld_dev(&J->den[i]) : J->den[i];
+        n += ld_dev(&J->num[i]);
+        d += ld_dev(&J->den[i]);
     }
     return inv_gain(n, d, J->glo, J->ghi);
 }
@@ -3335,7 +3334,9 @@ __device__ __forceinline__ void resolve_job(Table *__restrict__ T, int j, bool s
                                             bool defer = false)
 {
     Job *J = &T->jobs[j];
-    const uint32_t inv = same_launch ? job_gain(J, true) : frame_gain(J);
+    // in the persistent step left by the frame's last gain tile before any of
+    // its bands
+    const uint32_t inv = same_launch ? ld_dev(&J->ginv) & ~kGainKnown : frame_gain(J);
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap), nl = min(ld_dev(&J->nlinks), J->link_cap),
                    nflag = ld_dev(&J->nflag);
     if (J->hand) {
@@ -3654,7 +3655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX == 4 &
             if (publish_add(&J->gain_done, 1u, &s_u) + 1u == ng && threadIdx.x == 0) {
                 // the frame's last gain tile: its inverse gain, once, for every band
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                st_dev(G(&J->ginv), kGainKnown | job_gain(J, true));
+                st_dev(G(&J->ginv), kGainKnown | job_gain(J));
             }
             continue;
         }
