@@ -3116,22 +3116,45 @@ __device__ __forceinline__ uint32_t nearest_root(const Job *J, const F &f, int t
         const unsigned long long d2 = (unsigned long long)((long long)dx * dx) + (unsigned long long)((long long)dy * dy);
         return d2 > 0xFFFFFFFEull ? 0xFFFFFFFEu : (uint32_t)d2;
     };
+    constexpr int U = F::kAhead;
     uint32_t dmin = 0xFFFFFFFFu;
-    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x)
-        if (f.area(root_of(f, i)) >= amin)
-            dmin = min(dmin, dist2(f.run(i)));
+    for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+        uint32_t x[U], r[U], area[U];
+        uint2 rn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = min(i + u * blockDim.x, nr - 1u);
+            rn[u] = f.run(x[u]);
+        }
+        roots_of<U>(f, x, r);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            area[u] = f.area(r[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (area[u] >= amin)
+                dmin = min(dmin, dist2(rn[u]));
+    }
     dmin = wg_reduce(dmin, 0xFFFFFFFFu, OpMin(), s_min);
     if (dmin > r2)
         return kNoRoot;
     unsigned long long key = 0ull;
-    for (uint32_t i = threadIdx.x; i < nr; i += blockDim.x) {
-        if (dist2(f.run(i)) != dmin)
-            continue;
-        const uint32_t r = root_of(f, i);
-        const uint32_t a = f.area(r);
-        if (a >= amin) {
-            const unsigned long long k = size_key(a, f.start(r));
-            key = k > key ? k : key;
+    for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
+        uint32_t hit = 0;
+        uint2 rn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            rn[u] = f.run(min(i + u * blockDim.x, nr - 1u));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            hit |= (uint32_t)(i + u * blockDim.x < nr && dist2(rn[u]) == dmin) << u;
+        for (; hit; hit &= hit - 1u) {
+            const uint32_t r = root_of(f, i + (uint32_t)__builtin_ctz(hit) * blockDim.x);
+            const uint32_t a = f.area(r);
+            if (a >= amin) {
+                const unsigned long long k = size_key(a, f.start(r));
+                key = k > key ? k : key;
+            }
         }
     }
     key = wg_reduce(key, 0ull, OpMax(), s_key);
@@ -3198,7 +3221,11 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
             z.y1 = max(z.y1, y);
         }
         for (; hand && hit; hit &= hit - 1u) {
-            const uint2 run = f.run(i + (uint32_t)__builtin_ctz(hit) * blockDim.x);
+            const int k = __builtin_ctz(hit);
+            uint2 run = rn[0];
+#pragma unroll
+            for (int u = 1; u < U; ++u)
+                run = k == u ? rn[u] : run;
             const uint32_t y = run.x / (uint32_t)W, xs = run.x - y * (uint32_t)W, xe = xs + run.y - 1;
             GLOBAL uint64_t *hr = hand + (size_t)y * Wd;
             const int wa = (int)(xs >> 6), wb = (int)(xe >> 6);
