@@ -38,6 +38,8 @@ HBM_PEAK_GBS = 8000.0
 # algorithmic bytes per pixel of the whole per-frame path: frame 3 +
 # background min/max 6 + reference luminance 2/8 + I_FIZI bits 1/8
 PATH_BYTES_PER_PX = 9.375
+# of consecutive frames of one stream: the model is read once per 16 frames
+PLAIN_BYTES_PER_PX = 3 + 6 / 16 + 2 / 8 + 1 / 8
 # of the classify kernel: frame 3 + background min/max 6 (its raw-mask
 # output is an intermediate, counted as overhead)
 CLASSIFY_BYTES_PER_PX = 9.0
@@ -243,7 +245,8 @@ def bench_plain(args, torch, fizi, scene):
                         f"{args.plain_batch} (internal launches of {scene.HD_CHUNK} frames; calls pipelined, "
                         "flushed at the end of the timed region)",
             "Mpixel_per_s": round(fps * W * H / 1e6, 1), "frames_per_s": round(fps, 1),
-            "path_roofline_frac": round(fps * W * H * PATH_BYTES_PER_PX / (HBM_PEAK_GBS * 1e9), 4),
+            "path_bytes_per_px": PLAIN_BYTES_PER_PX,
+            "path_roofline_frac": round(fps * W * H * PLAIN_BYTES_PER_PX / (HBM_PEAK_GBS * 1e9), 4),
             "tracking_frames_per_s": round(track_fps, 1),
             "latency_ms": {"p50": pct(lat, 50), "p99": pct(lat, 99),
                            "mode": "one frame per call, pointer read back on the host"}}

@@ -14,9 +14,9 @@ constexpr int kRing = 65536;   // pointers kept for get_pointer (a power of two)
 constexpr int kRecs = 64;
 
 // State block: model | job tables | gain scratch | chunk pointers | chunk
-// scratch slots | a second raw-mask buffer per slot (consecutive chunks of a call alternate
-// between the two, so that a chunk's classify never writes the bits the
-// previous chunk's morphology is reading).
+// scratch slots | a second raw-mask buffer per slot (consecutive chunks of a
+// call alternate between the two, so that a chunk's classify never writes the
+// bits the previous chunk's morphology is reading).
 struct CtxLayout {
     size_t model, tables, arrived, ptrs, slots, slot_stride, raw2, raw2_stride, total;
 };

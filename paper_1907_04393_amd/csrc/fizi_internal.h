@@ -279,11 +279,11 @@ hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job
 // to look a band's job up in the table.
 hipError_t launch_morph(const Table *d_tab, int total_tiles, int items, int max_wd, int max_ops, int n_cu,
                         const Tuning &t, hipStream_t s, StageEvents ev = {});
-// serial: one workgroup takes the jobs in table order (consecutive frames of
-// one tracked stream); small: 256-thread workgroups, for a launch that runs
-// beside a streaming kernel.
-hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev = {}, const ChainSpan *chain = nullptr,
-                          bool small = false);
+// chain: null, or the tracked frames of one stream that the jobs are, settled
+// in order by a kernel after the component stage; small: 256-thread
+// workgroups, for a launch that runs beside a streaming kernel.
+hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEvents ev = {},
+                          const ChainSpan *chain = nullptr, bool small = false);
 hipError_t launch_persistent(const Table *d_tab, int max_wd, int max_ops, int n_cu, const Tuning &t,
                              uint8_t *persist, hipStream_t s, StageEvents ev = {});
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);

@@ -3819,9 +3819,9 @@ hipError_t launch_classify(const Table *d_tab, int total_tiles, int n_cu, const 
 
 // Frames of one span workgroup: 16, so that a pixel's box is unpacked once
 // for 16 frames, unless that leaves fewer workgroups than about one resident
-// round (seven 256-thread workgroups per CU): then 8, or 4. Measured (when
-// 16 took 92 us) for 64 frames of 1920x1080 with 4 / 8 / 16 / 32 / 64 frames:
-// 124 / 98 / 92 / 98 / 118 us; for 16 frames of 1280x720 (900 tiles) with 8 / 16: 17 / 21 us.
+// round (seven 256-thread workgroups per CU): then 8, or 4. With 4 / 8 / 16 /
+// 32 frames 64 of 1920x1080 take 87 / 78 / 75 / 74 us (a longer list of inverse
+// gains for the last 1%), 16 of 1280x720 (900 tiles) 13.8 / 12.2 / 12.9.
 hipError_t launch_classify_span(const Table *d_tab, const SpanJobs &S, const Job &J, int n_cu, hipStream_t s,
                                 StageEvents ev)
 {
@@ -3940,8 +3940,8 @@ hipError_t launch_resolve(const Table *d_tab, int njobs, hipStream_t s, StageEve
 
 // Blocks per CU of the persistent step: what the kernel's registers and LDS
 // allow (wave64, 512 VGPRs per SIMD lane in granules of 8, four SIMDs and
-// 160 KiB of LDS per CU, eight waves per SIMD), capped at four so that the
-// whole grid is resident with room to spare.
+// 160 KiB of LDS per CU, eight waves per SIMD: four for the smallest form's 128
+// VGPRs and 34 KiB), so that the whole grid is resident; at most eight.
 template <int KMAX, int NC>
 int flow_blocks_per_cu()
 {
