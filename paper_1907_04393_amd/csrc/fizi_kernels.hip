@@ -178,14 +178,14 @@ __device__ __forceinline__ uint32_t job_gain(const Job *J)
     return inv_gain(n, d, J->glo, J->ghi);
 }
 
-// The same for a whole wave: lane l holds one of the 2 x 32 sums. Their
-// totals go through DPP adds of 16-bit halves (each
-// lane's half sums stay below 2^21): within rows of 16 lanes, then row 0 into
-// row 1 and row 2 into row 3, so that lane 31 holds the reference's total and
-// lane 63 the frame's.
+// The same for a whole wave: lanes 0 .. 31 hold parts of the reference's sum,
+// lanes 32 .. 63 of the frame's. Their totals go through DPP adds of the low 24
+// bits and of the rest (both stay below 2^29: no sum reaches 2^37): within rows
+// of 16 lanes, then row 0 into row 1 and row 2 into row 3, so that lane 31 holds
+// the reference's total and lane 63 the frame's.
 static_assert(kGainSlots == 32 && offsetof(Job, den) == offsetof(Job, num) + 4 * kGainSlots,
               "one gain sum per lane, num then den");
-__device__ __forceinline__ uint32_t wave_gain(uint32_t slot, int glo, int ghi)
+__device__ __forceinline__ uint32_t wave_gain(GainSum part, int glo, int ghi)
 {
     auto rows = [](uint32_t v) {
         v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
@@ -195,9 +195,9 @@ __device__ __forceinline__ uint32_t wave_gain(uint32_t slot, int glo, int ghi)
         v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
         return v;
     };
-    const uint32_t lo = rows(slot & 0xFFFFu), hi = rows(slot >> 16);
+    const uint32_t lo = rows((uint32_t)part & 0xFFFFFFu), hi = rows((uint32_t)(part >> 24));
     auto total = [&](int lane) {
-        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, lane) << 16) +
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, lane) << 24) +
                (uint32_t)__builtin_amdgcn_readlane((int)lo, lane);
     };
     return inv_gain(total(31), total(63), glo, ghi);
@@ -734,12 +734,10 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != gridDim.x - 1)
         return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    n = d = 0;
-    for (uint32_t p = lane; p < gridDim.x; p += kWave) {
-        n += ld_dev(sums + 2 * p);
-        d += ld_dev(sums + 2 * p + 1);
-    }
-    const uint32_t inv = inv_gain(wave_reduce(n, (GainSum)0, OpSum()), wave_reduce(d, (GainSum)0, OpSum()), S.glo, S.ghi);
+    GainSum of = 0;
+    for (uint32_t p = lane & 31; p < gridDim.x; p += 32)
+        of += ld_dev(sums + 2 * p + (lane >> 5));
+    const uint32_t inv = wave_gain(of, S.glo, S.ghi);
     if (lane == 0)
         T->jobs[i].ginv = kGainKnown | inv;
 }
@@ -3197,43 +3195,58 @@ __device__ __forceinline__ ZoneStats zone_stats(const Job *J, const F &f, uint32
     const int W = J->W, Wd = J->Wd;
     const uint32_t nr = min(ld_dev(&J->nruns), J->run_cap);
     ZoneStats z{0, 0, 0xFFFFFFFFu, 0xFFFFFFFFu, 0, 0};
+    auto add = [&](const uint2 run) __attribute__((always_inline)) {
+        const uint32_t y = run.x / (uint32_t)W, xs = run.x - y * (uint32_t)W, n = run.y;
+        z.sx += (unsigned long long)n * xs + (unsigned long long)n * (n - 1) / 2;
+        z.sy += (unsigned long long)n * y;
+        z.x0 = min(z.x0, xs);
+        z.x1 = max(z.x1, xs + n - 1);
+        z.y0 = min(z.y0, y);
+        z.y1 = max(z.y1, y);
+    };
+    auto mark = [&](const uint2 run) __attribute__((always_inline)) {
+        const uint32_t y = run.x / (uint32_t)W, xs = run.x - y * (uint32_t)W, xe = xs + run.y - 1;
+        GLOBAL uint64_t *hr = hand + (size_t)y * Wd;
+        const int wa = (int)(xs >> 6), wb = (int)(xe >> 6);
+        for (int w = wa; w <= wb; ++w) {
+            const int lo = (w == wa) ? (int)(xs & 63) : 0;
+            const int hi = (w == wb) ? (int)(xe & 63) : 63;
+            const uint64_t m = (hi == 63 ? ~0ull : ((2ull << hi) - 1ull)) & (~0ull << lo);
+            __hip_atomic_fetch_or(hr + w, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
     constexpr int U = F::kAhead;
     for (uint32_t i = threadIdx.x; i < nr; i += U * blockDim.x) {
-        uint32_t x[U], r[U], hit = 0;
-        uint2 rn[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            x[u] = min(i + u * blockDim.x, nr - 1u);
-            rn[u] = f.run(x[u]);
-        }
-        roots_of<U>(f, x, r);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (r[u] != kstar || i + u * blockDim.x >= nr)
+        if constexpr (U == 1) {
+            if (root_of(f, i) != kstar)
                 continue;
-            hit |= 1u << u;
-            const uint32_t y = rn[u].x / (uint32_t)W, xs = rn[u].x - y * (uint32_t)W, n = rn[u].y;
-            z.sx += (unsigned long long)n * xs + (unsigned long long)n * (n - 1) / 2;
-            z.sy += (unsigned long long)n * y;
-            z.x0 = min(z.x0, xs);
-            z.x1 = max(z.x1, xs + n - 1);
-            z.y0 = min(z.y0, y);
-            z.y1 = max(z.y1, y);
-        }
-        for (; hand && hit; hit &= hit - 1u) {
-            const int k = __builtin_ctz(hit);
-            uint2 run = rn[0];
+            const uint2 run = f.run(i);
+            add(run);
+            if (hand)
+                mark(run);
+        } else {
+            uint32_t x[U], r[U], hit = 0;
+            uint2 rn[U];
 #pragma unroll
-            for (int u = 1; u < U; ++u)
-                run = k == u ? rn[u] : run;
-            const uint32_t y = run.x / (uint32_t)W, xs = run.x - y * (uint32_t)W, xe = xs + run.y - 1;
-            GLOBAL uint64_t *hr = hand + (size_t)y * Wd;
-            const int wa = (int)(xs >> 6), wb = (int)(xe >> 6);
-            for (int w = wa; w <= wb; ++w) {
-                const int lo = (w == wa) ? (int)(xs & 63) : 0;
-                const int hi = (w == wb) ? (int)(xe & 63) : 63;
-                const uint64_t m = (hi == 63 ? ~0ull : ((2ull << hi) - 1ull)) & (~0ull << lo);
-                __hip_atomic_fetch_or(hr + w, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int u = 0; u < U; ++u) {
+                x[u] = min(i + u * blockDim.x, nr - 1u);
+                rn[u] = f.run(x[u]);
+            }
+            roots_of<U>(f, x, r);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (r[u] != kstar || i + u * blockDim.x >= nr)
+                    continue;
+                hit |= 1u << u;
+                add(rn[u]);
+            }
+            for (; hand && hit; hit &= hit - 1u) {
+                const int k = __builtin_ctz(hit);
+                uint2 run = rn[0];
+#pragma unroll
+                for (int u = 1; u < U; ++u)
+                    run = k == u ? rn[u] : run;
+                mark(run);
             }
         }
     }
