@@ -1,7 +1,6 @@
 // C ABI of the single-stream context: learn_background, process_frames,
 // get_pointer (include/fizi.h).
 #include <algorithm>
-#include <cstring>
 #include <new>
 
 #include "fizi_host.h"
@@ -63,9 +62,6 @@ struct fizi_ctx {
     // its device-side address), so that no copy follows them
     fizi_pointer *h_ring = nullptr;
     fizi_pointer *d_ring = nullptr;
-    // behind them, what every job of this context has in common: read by the
-    // gain kernel, which builds the job tables (device-side address)
-    const Job *d_base = nullptr;
     // frames [f0, f1) are in the host pointer ring once `ev` (recorded after
     // the kernels that store them, default fences: the host reads what they
     // wrote) is done
@@ -223,18 +219,10 @@ int fizi_create(const fizi_geom *geom, const fizi_params *params, int32_t chunk_
     c->tune = tuning_for(geom->width, morph_ops(*params), false);
     int rc = device_cu_count(&c->device, &c->n_cu);
     if (rc == FIZI_OK) {
-        static_assert(sizeof(fizi_pointer) * kRing % alignof(Job) == 0, "the base job follows the ring");
-        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_ring), sizeof(fizi_pointer) * kRing + sizeof(Job),
+        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_ring), sizeof(fizi_pointer) * kRing,
                                      hipHostMallocMapped | hipHostMallocCoherent);
         if (e == hipSuccess)
             e = hipHostGetDevicePointer(reinterpret_cast<void **>(&c->d_ring), c->h_ring, 0);
-        if (e == hipSuccess) {
-            Job J;
-            fill_job(c->m, c->tune.morph_rows, J, false);
-            set_scratch(J, slot_at(*geom, c->d + L.slots));
-            std::memcpy(static_cast<void *>(c->h_ring + kRing), &J, sizeof(J));
-            c->d_base = reinterpret_cast<const Job *>(c->d_ring + kRing);
-        }
         if (e == hipSuccess)
             e = hipEventCreateWithFlags(&c->order_ev, kDeviceOrderEvent);
         for (int i = 0; i < kRecs && e == hipSuccess; ++i)
@@ -342,7 +330,7 @@ int process_frames(fizi_ctx *c, const uint8_t *d_frames, int32_t n_frames, uint6
         J.hout = c->d_ring;
         J.frame_index = fbase;
         SpanJobs S = span_jobs(J, k, reinterpret_cast<uint32_t *>(c->d + c->L.arrived));
-        S.base = c->d_base;
+        S.table = 1;
         if (!d_fizi_bits)
             S.fizi_words = c->L.slot_stride / sizeof(uint64_t);
         S.slot_bytes = c->L.slot_stride;

@@ -200,12 +200,10 @@ Slot slot_at(const fizi_geom &g, uint8_t *base)
     s.index = reinterpret_cast<uint32_t *>(base + o);
     o += align256(px * 4);
     s.runs = reinterpret_cast<uint2 *>(base + o);
-    s.run_cap = (uint32_t)(px / 2);      // the most runs a mask can have
+    s.run_cap = run_capacity(g.width, g.height);
     o += align256((px / 2) * 8);
-    // joins across band and segment borders; beyond this many, runs are
-    // flagged for the component stage instead
     s.links = reinterpret_cast<uint2 *>(base + o);
-    s.link_cap = (uint32_t)(px / 8);
+    s.link_cap = link_capacity(g.width, g.height);
     o += align256((px / 8) * 8);
     s.bflag = reinterpret_cast<uint32_t *>(base + o);
     s.nflags = flag_words(g);
@@ -418,6 +416,16 @@ SpanJobs span_jobs(const Job &J, int n, uint32_t *arrived)
     S.out = J.out;
     S.ring = J.hout;
     S.track = J.track;
+    S.parent = J.parent;
+    S.index = J.index;
+    S.runs = J.runs;
+    S.links = J.links;
+    S.min_area = J.min_area;
+    S.fill_pm = J.fill_pm;
+    S.debounce = J.debounce;
+    S.track_r2 = J.track_r2;
+    S.open_it = (int16_t)J.open_it;
+    S.close_it = (int16_t)J.close_it;
     S.frame_index = J.frame_index;
     S.yref = const_cast<uint16_t *>(J.yref);
     S.n = n;

@@ -154,6 +154,12 @@ struct FrameSpan {
 };
 HueForm hue_form(const HueTest &h);
 
+// The most runs a mask can have.
+__host__ __device__ inline uint32_t run_capacity(int32_t W, int32_t H) { return (uint32_t)W * (uint32_t)H / 2u; }
+// Joins across band and segment borders that are kept; beyond this many, runs
+// are flagged for the component stage instead.
+__host__ __device__ inline uint32_t link_capacity(int32_t W, int32_t H) { return (uint32_t)W * (uint32_t)H / 8u; }
+
 // Launch shapes (tunable per resolution class).
 struct Tuning {
     int cls_iters;      // classify tile = 1024 * cls_iters pixels (1, 2, 4, 8)
@@ -211,25 +217,28 @@ constexpr int kArrivedStride = 32;
 constexpr size_t kArrivedWords = (size_t)kMaxJobs * kArrivedStride;
 constexpr size_t kGainScratchBytes = kArrivedWords * sizeof(uint32_t) + (size_t)kGainParts * 2 * sizeof(GainSum);
 
-// A launch over n consecutive frames of one stream: the fields of its first
-// job that change from call to call, and the strides to the next ones. What
-// does not change is the library's own, in host memory that the device reads
-// (base: a job of the stream, its scratch arrays those of frame slot 0): the
-// state block is the caller's, who may fill it from another context's, and
-// holds nothing that a kernel takes for an address. The gain kernel writes the
-// job table from both, so that nothing is uploaded. Kernel arguments are kept
-// few: 700 bytes of them cost 8 to 15 us a launch.
+// A launch over n consecutive frames of one stream: what the kernels after the
+// front read of its first job, and the strides to the next ones. The gain
+// kernel writes the job table from it, so that nothing is uploaded, and nothing
+// in the state block is taken for an address that the launch itself has not
+// written: the block is the caller's, who may fill it from another context's.
+// Kernel arguments are kept few: 700 bytes of them cost 8 to 15 us a launch.
 struct SpanJobs {
-    const Job *base;                    // null when learning: no table is written
     const uint8_t *frame;
     size_t frame_bytes;
     uint64_t *raw, *fizi, *hand;        // hand null: none
     size_t raw_bytes, fizi_words, hand_words, slot_bytes;
     fizi_pointer *out, *ring;           // ring[k & ring_mask]: the host ring's place of frame index k
     TrackState *track;
+    uint32_t *parent, *index;
+    uint2 *runs, *links;
     uint64_t frame_index;
     uint16_t *yref;
     uint32_t ring_mask;
+    int32_t table;                      // whether to write the table (not when learning)
+    int32_t min_area, fill_pm, debounce;
+    uint32_t track_r2;
+    int16_t open_it, close_it;
     int32_t n, W, H, rs;
     int32_t band, mgroup;
     int32_t mor_items;                  // morphology items of one frame

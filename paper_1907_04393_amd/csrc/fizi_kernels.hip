@@ -585,22 +585,21 @@ __global__ __launch_bounds__(256) void k_gain(Table *__restrict__ T)
 // value, so that its loads wait for no table. Workgroup (0, n) writes the
 // jobs for the kernels that follow, thread i job i.
 // Bound by the latency of its loads and, in between, the VALU: 64 frames of
-// 1920x1080 (50 MB of frame rows) take 19 us, 22 us tile by tile from a
+// 1920x1080 (50 MB of frame rows) take 17 us, 22 us tile by tile from a
 // table with atomic sums.
-// base: the stream's job up to the accumulators, as words.
-constexpr int kJobHead = (int)(offsetof(Job, num) / 8);
-static_assert(offsetof(Job, num) % 8 == 0, "whole 8-byte words");
-
-__device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs &S, const uint64_t *base, int i)
+__device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs &S, int i)
 {
     Job *J = &T->jobs[i];
-    // every field but the accumulators
+    // every field but the accumulators; those that only the front reads, which
+    // has them by value, are 0
     uint64_t *dst = reinterpret_cast<uint64_t *>(J);
+    constexpr int kHead = (int)(offsetof(Job, num) / 8);
+    static_assert(offsetof(Job, num) % 8 == 0, "whole 8-byte words");
     Job head;
     uint64_t *h = reinterpret_cast<uint64_t *>(&head);
 #pragma unroll
-    for (int q = 0; q < kJobHead; ++q)
-        h[q] = base[q];
+    for (int q = 0; q < kHead; ++q)
+        h[q] = 0ull;
     const size_t so = (size_t)i * S.slot_bytes;
     const uint64_t index = S.frame_index + (uint64_t)i;
     auto moved = [&](auto *p, size_t bytes) {
@@ -610,10 +609,23 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     head.raw = moved(S.raw, (size_t)i * S.raw_bytes);
     head.fizi = S.fizi + (size_t)i * S.fizi_words;
     head.hand = S.hand ? S.hand + (size_t)i * S.hand_words : nullptr;
-    head.parent = moved(head.parent, so);
-    head.index = moved(head.index, so);
-    head.runs = moved(head.runs, so);
-    head.links = moved(head.links, so);
+    head.parent = moved(S.parent, so);
+    head.index = moved(S.index, so);
+    head.runs = moved(S.runs, so);
+    head.links = moved(S.links, so);
+    head.W = S.W;
+    head.H = S.H;
+    head.Wd = S.W / 64;
+    head.run_cap = run_capacity(S.W, S.H);
+    head.link_cap = link_capacity(S.W, S.H);
+    head.open_it = S.open_it;
+    head.close_it = S.close_it;
+    head.min_area = S.min_area;
+    head.fill_pm = S.fill_pm;
+    head.debounce = S.debounce;
+    head.track_r2 = S.track_r2;
+    head.glo = S.glo;
+    head.ghi = S.ghi;
     head.out = S.out + i;
     head.hout = S.ring ? S.ring + (index & S.ring_mask) : nullptr;
     head.track = S.track;
@@ -621,7 +633,7 @@ __device__ __forceinline__ void write_job(Table *__restrict__ T, const SpanJobs 
     head.band = S.band;
     head.mgroup = S.mgroup;
 #pragma unroll
-    for (int q = 0; q < kJobHead; ++q)
+    for (int q = 0; q < kHead; ++q)
         dst[q] = h[q];
     // the accumulators but the inverse gain, which the frame's last workgroup
     // stores
@@ -643,16 +655,9 @@ __global__ __launch_bounds__(1024) void k_gain_span(Table *__restrict__ T, const
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int part = blockIdx.x, i = blockIdx.y;
     if (i == S.n) {
-        // the base lies in host memory: its words all in one access
-        __shared__ uint64_t s_base[kJobHead];
-        if (part == 0) {
-            static_assert(kJobHead <= kWave, "a word per thread of the smallest workgroup");
-            if (threadIdx.x < kJobHead)
-                s_base[threadIdx.x] = G(reinterpret_cast<const uint64_t *>(S.base))[threadIdx.x];
-            __syncthreads();
+        if (part == 0)
             for (int j = threadIdx.x; j < S.n; j += blockDim.x)
-                write_job(T, S, s_base, j);
-        }
+                write_job(T, S, j);
         return;
     }
     const GLOBAL uint8_t *frame0 = G(S.frame), *frame = frame0 + (size_t)i * S.frame_bytes;
@@ -3780,7 +3785,7 @@ hipError_t launch_gain_span_mode(Table *tab, const SpanJobs &S, hipStream_t s, S
     const long long items = (long long)((S.H + S.rs - 1) / S.rs) * (S.W / (wide ? 16 : 4));
     const GainShape g = gain_span_shape(items, S.n);
     const int threads = g.threads;
-    const dim3 grid((unsigned)g.parts, (unsigned)S.n + (S.base ? 1u : 0u));
+    const dim3 grid((unsigned)g.parts, (unsigned)S.n + (S.table ? 1u : 0u));
     if (S.make_yref) {
         if (wide)
             FIZI_LAUNCH((k_gain_span<MODE, true, true>), grid, threads, 0, s, ev, tab, S);
