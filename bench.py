@@ -56,8 +56,8 @@ TIMED_FORM = {0: 0, 1: 0, 2: 2, 3: 2, 4: 4, 5: 4}
 # rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (the factors a 1 GiB -> 1 GiB
 # elementwise kernel gives), with the code hash of the kernel they were
 # taken on (the build writes lib/kernel_hashes.json)
-TRAFFIC = {"_ZN4fizi12_GLOBAL__N_110k_classifyILi8EEEvPNS_5TableE": ("f0787cb49167837a", 1714.5e6),
-           "_ZN4fizi12_GLOBAL__N_110k_classifyILi4EEEvPNS_5TableE": ("fa8a8a788f7f1cb0", 1714.2e6)}
+TRAFFIC = {"_ZN4fizi12_GLOBAL__N_110k_classifyILi8EEEvPNS_5TableE": ("fbd09f4bb5765cd9", 1714.5e6),
+           "_ZN4fizi12_GLOBAL__N_110k_classifyILi4EEEvPNS_5TableE": ("d465864ad620088a", 1714.2e6)}
 
 
 def log(*a):
